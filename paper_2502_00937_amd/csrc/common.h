@@ -131,21 +131,24 @@ struct GemmArgs {
                       //   attention kernel reads); ldo is not used
 };
 
-// Applies one epilogue to a single accumulator; the caller guarantees row < M and col < N.
-template <int EPI, typename OutT>
-__device__ __forceinline__ void epilogue_store(const GemmArgs& a, int row, int col, float acc) {
-  float v = acc + a.bias[col];
-  if constexpr (EPI == EPI_BIAS) {
-    Elem<OutT>::store((OutT*)a.out + (size_t)row * a.ldo + col, v);
-  } else if constexpr (EPI == EPI_BIAS_GELU) {
-    Elem<OutT>::store((OutT*)a.out + (size_t)row * a.ldo + col, gelu_erf(v));
+// Applies one epilogue of the fp32 path to four neighbouring accumulators of one row; the caller guarantees
+// row < M, col < N, and that col, N and the leading dimensions are multiples of 4.
+template <int EPI>
+__device__ __forceinline__ void epilogue_store4_f32(const GemmArgs& a, int row, int col, const f32x4 acc) {
+  f32x4 v = acc + *(const f32x4*)(a.bias + col);
+  if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) {
+    if constexpr (EPI == EPI_BIAS_GELU) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
+    }
+    *(f32x4*)((float*)a.out + (size_t)row * a.ldo + col) = v;
   } else if constexpr (EPI == EPI_BIAS_RESIDUAL) {
-    float* p = a.resid + (size_t)row * a.ldo + col;
+    f32x4* p = (f32x4*)(a.resid + (size_t)row * a.ldo + col);
     *p += v;
   } else {  // EPI_PATCH
-    int tile = row / a.patches;
-    int tok = a.cls + (row - tile * a.patches);
-    a.resid[((size_t)tile * a.tokens + tok) * a.ldo + col] = v + a.pos[(size_t)tok * a.ldo + col];
+    const int tile = row / a.patches;
+    const int tok = a.cls + (row - tile * a.patches);
+    *(f32x4*)(a.resid + ((size_t)tile * a.tokens + tok) * a.ldo + col) = v + *(const f32x4*)(a.pos + (size_t)tok * a.ldo + col);
   }
 }
 

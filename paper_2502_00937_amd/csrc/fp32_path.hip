@@ -1,118 +1,202 @@
-// fp32 arithmetic mode: plain FMA matrix product and attention.  This mode exists for
-// exact-arithmetic parity runs on small encoders; it is not the throughput path.
+// fp32 arithmetic mode: matrix product and attention on the fp32 matrix instruction (products and sums in fp32
+// throughout).  This mode exists for exact-arithmetic parity runs on small encoders.
+//
+// Both kernels cut their contraction over the four waves of a workgroup and add the four partial results in LDS in a
+// fixed order: the shapes of this mode are a few hundred rows by a few hundred columns, so what bounds them is the
+// length of one wave's chain of dependent steps, not the rate of any unit.  Operands go from global memory straight to
+// registers (v_mfma_f32_32x32x2_f32 takes one fp32 value per lane and takes 64 clocks: the L1 delivers faster than
+// that), several k-blocks ahead; no LDS is written before the final sum.
 #include "common.h"
 
 namespace vitenc {
 
 namespace {
 
-// C[M, N] = A[M, K] . W[N, K]^T, 64x64 tile, 16-wide k-steps, 4x4 outputs per thread.
+// C[M, N] = A[M, K] . W[N, K]^T, tile 32 F x 32 F.  Wave w takes k-values [16w, 16w + 16) of every 64: two chunks of 8,
+// of which a lane half takes 4 consecutive values each (one 16-byte load per 32 rows).  The product is formed
+// transposed, so a lane holds four consecutive columns of one row per register quad.  A row's sums are formed in the
+// same order whatever F is, so a token does not depend on the tile size its launch took.
 // Operand rows are padded by the host so tile loads never leave the buffers.
-template <int EPI>
+// Measured on four 197-token images, width 192 (M = 788): out-proj and fc2 7.4 us on average, QKV 7.4, fc1 12.6; the
+// predecessor (64 x 64 tile, VALU multiply-adds, one 16-wide k-step in flight) took 34, 16.6 and 18.5.  The error of
+// the encoder against 64 bits is 3.5e-7 (6.5e-7 before: four shorter chains instead of one).
+template <int EPI, int F>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs a) {
-  __shared__ float sA[16][68];
-  __shared__ float sB[16][68];
-  const int tid = threadIdx.x;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const float* A = (const float*)a.A + (size_t)m0 * a.lda;
-  const float* W = (const float*)a.W + (size_t)n0 * a.ldw;
-  const int lrow = tid >> 2, lk = (tid & 3) * 4;
-  const int tx = tid & 15, ty = tid >> 4;  // thread computes rows ty*4.., cols tx + 16*j
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < a.K; k0 += 16) {
-    const f32x4 va = *(const f32x4*)(A + (size_t)lrow * a.lda + k0 + lk);
-    const f32x4 vb = *(const f32x4*)(W + (size_t)lrow * a.ldw + k0 + lk);
+  constexpr int DEPTH = F == 1 ? 4 : 2;  // k-blocks in flight per wave
+  constexpr int LD = 36;                 // LDS row: 32 columns and a pad that spreads the rows over the banks
+  __shared__ __attribute__((aligned(16))) float red[4][32 * F][LD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lrow = lane & 31, lk = lane >> 5;
+  const int m0 = blockIdx.y * 32 * F, n0 = blockIdx.x * 32 * F;
+  const float* pa[F];
+  const float* pw[F];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      sA[lk + e][lrow] = va[e];
-      sB[lk + e][lrow] = vb[e];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float ra[4], rb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) ra[i] = sA[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rb[j] = sB[k][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(ra[i], rb[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int i = 0; i < F; ++i) {
+    pa[i] = (const float*)a.A + (size_t)(m0 + i * 32 + lrow) * a.lda + wave * 16 + lk * 4;
+    pw[i] = (const float*)a.W + (size_t)(n0 + i * 32 + lrow) * a.ldw + wave * 16 + lk * 4;
   }
+  f32x4 fa[DEPTH][F][2], fw[DEPTH][F][2];
+  auto load = [&](int d, int kb) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    if (row >= a.M) continue;
+    for (int i = 0; i < F; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx + 16 * j;
-      if (col < a.N) epilogue_store<EPI, float>(a, row, col, acc[i][j]);
+      for (int c = 0; c < 2; ++c) {
+        fa[d][i][c] = *(const f32x4*)(pa[i] + kb * 64 + c * 8);
+        fw[d][i][c] = *(const f32x4*)(pw[i] + kb * 64 + c * 8);
+      }
+  };
+  f32x16 acc[F][F];
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  const int KB = a.K / 64;
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) load(d, min(d, KB - 1));
+  for (int k0 = 0; k0 < KB; k0 += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      if (k0 + d >= KB) break;
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int j = 0; j < F; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[d][j][c][e], fa[d][i][c][e], acc[i][j], 0, 0, 0);
+      if (k0 + d + DEPTH < KB) load(d, k0 + d + DEPTH);
+    }
+  }
+  // one 32-column block at a time: the four partial sums meet in LDS, eight lanes finish a row
+#pragma unroll
+  for (int j = 0; j < F; ++j) {
+    if (j > 0) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const f32x4 v = {acc[i][j][jj * 4], acc[i][j][jj * 4 + 1], acc[i][j][jj * 4 + 2], acc[i][j][jj * 4 + 3]};
+        *(f32x4*)&red[wave][i * 32 + lrow][jj * 8 + lk * 4] = v;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < F; ++i) {
+      const int r = i * 32 + (tid >> 3), c = (tid & 7) * 4;
+      const int row = m0 + r, col = n0 + j * 32 + c;
+      const f32x4 v = (*(const f32x4*)&red[0][r][c] + *(const f32x4*)&red[1][r][c]) +
+                      (*(const f32x4*)&red[2][r][c] + *(const f32x4*)&red[3][r][c]);
+      if (row < a.M && col < a.N) epilogue_store4_f32<EPI>(a, row, col, v);
     }
   }
 }
 
-// One workgroup = 64 query rows x one head; 4 adjacent lanes share a query row, each owning a
-// quarter of the head dimension.  Keys/values are staged in LDS 64 at a time; softmax is the
-// running-max / running-sum form, all in fp32.
-constexpr int F32_BK = 64, F32_DQ_MAX = 32;  // (the 64 query rows are what attention_q_block reports for fp32)
+// One workgroup = 32 query rows x one head (two workgroups to a work item's 64 rows); its four waves take every fourth
+// block of 32 keys each, with a running maximum and sum of their own, and are merged at the end.  Scores are formed
+// transposed (keys x queries), so a lane's column is its query: the running values are one register, and the weights
+// are already laid out as the operand of the second product, whose key order follows the accumulator's rows.
+// Measured at 4 x 197 tokens, 3 heads of 64: 12.2 us against 415 us of the predecessor (one key at a time, four lanes
+// to a query); the whole encode 634 against 6 378.
+constexpr int F32_BQ = 32, F32_BK = 32;
 
+template <int DHP>
 __global__ __launch_bounds__(256) void attention_f32_kernel(const AttnArgs a) {
-  extern __shared__ float smem_f[];
-  const int dhp = a.dh_pad, dq = dhp >> 2;
-  float* sK = smem_f;               // [64][dhp + 4]
-  float* sV = smem_f + F32_BK * (dhp + 4);
-  const int ldk = dhp + 4;
-  const AttnWork w = a.work[blockIdx.x];
+  constexpr int CH = DHP / 8, FB = (DHP + 31) / 32;  // 8-wide chunks of a head, 32-wide blocks of its columns
+  constexpr int LD = 36;
+  __shared__ __attribute__((aligned(16))) float red[4][F32_BQ][LD];
+  __shared__ float red_m[4][F32_BQ], red_l[4][F32_BQ];
+  const AttnWork w = a.work[blockIdx.x >> 1];
   const int head = blockIdx.y;
-  const int tid = threadIdx.x, qi = tid >> 2, part = tid & 3;
+  const int q0 = w.q0 + (blockIdx.x & 1) * F32_BQ;
   const int seg_end = w.seg_start + w.seg_len;
-  const int qrow = w.q0 + qi;
-  const bool qvalid = qrow < seg_end;
+  if (q0 >= seg_end) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lq = lane & 31, lk = lane >> 5;
   const float* base = (const float*)a.qkv;
-  const int qoff = head * dhp, koff = (a.heads + head) * dhp, voff = (2 * a.heads + head) * dhp;
-  float q[F32_DQ_MAX], o[F32_DQ_MAX];
+  const int qoff = head * DHP, koff = (a.heads + head) * DHP, voff = (2 * a.heads + head) * DHP;
   const float scale = 1.0f / sqrtf((float)a.dh);
+  f32x4 q[CH];
+  {
+    const float* qp = base + (size_t)min(q0 + lq, seg_end - 1) * a.ld_qkv + qoff + lk * 4;
 #pragma unroll
-  for (int i = 0; i < F32_DQ_MAX; ++i) {
-    o[i] = 0.f;
-    q[i] = (i < dq && qvalid) ? base[(size_t)qrow * a.ld_qkv + qoff + part * dq + i] * scale : 0.f;
+    for (int c = 0; c < CH; ++c) q[c] = *(const f32x4*)(qp + c * 8) * scale;
   }
-  float m = -INFINITY, l = 0.f;
-  for (int k0 = 0; k0 < w.seg_len; k0 += F32_BK) {
-    const int nk = min(F32_BK, w.seg_len - k0);
-    for (int idx = tid; idx < nk * dhp; idx += 256) {
-      const int r = idx / dhp, c = idx - r * dhp;
-      const size_t g = (size_t)(w.seg_start + k0 + r) * a.ld_qkv;
-      sK[r * ldk + c] = base[g + koff + c];
-      sV[r * ldk + c] = base[g + voff + c];
+  f32x16 o[FB];
+#pragma unroll
+  for (int b = 0; b < FB; ++b)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[b][v] = 0.f;
+  float m = -INFINITY, l = 0.f;  // of query lq; l over this lane's keys only until the end
+  for (int k0 = w.seg_start + wave * F32_BK; k0 < seg_end; k0 += 4 * F32_BK) {
+    f32x4 kf[CH];
+    const float* kp = base + (size_t)min(k0 + lq, seg_end - 1) * a.ld_qkv + koff + lk * 4;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) kf[c] = *(const f32x4*)(kp + c * 8);
+    float vf[FB][16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const float* vp = base + (size_t)min(k0 + (v >> 2) * 8 + lk * 4 + (v & 3), seg_end - 1) * a.ld_qkv + voff;
+#pragma unroll
+      for (int b = 0; b < FB; ++b) vf[b][v] = vp[min(b * 32 + lq, DHP - 1)];
+    }
+    f32x16 s;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[c][e], q[c][e], s, 0, 0, 0);
+    float mb = m;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      if (k0 + (v >> 2) * 8 + lk * 4 + (v & 3) >= seg_end) s[v] = -INFINITY;
+      mb = fmaxf(mb, s[v]);
+    }
+    mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
+    const float mref = mb == -INFINITY ? 0.f : mb;  // every score so far is -inf: their weights are 0, not NaN
+    const float corr = expf(m - mref);              // the library's exp: this mode is for exact-arithmetic parity
+    m = mb;
+    float ls = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      s[v] = expf(s[v] - mref);
+      ls += s[v];
+    }
+    l = l * corr + ls;
+#pragma unroll
+    for (int b = 0; b < FB; ++b) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[b][v] *= corr;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[b][v], s[v], o[b], 0, 0, 0);
+    }
+  }
+  l += __shfl_xor(l, 32, 64);
+  if (lk == 0) { red_m[wave][lq] = m; red_l[wave][lq] = l; }
+  __syncthreads();
+  float mt = -INFINITY, lt = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) mt = fmaxf(mt, red_m[i][lq]);
+  const float mref = mt == -INFINITY ? 0.f : mt;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) lt += red_l[i][lq] * expf(red_m[i][lq] - mref);
+  const float f = expf(m - mref) / lt;
+#pragma unroll
+  for (int b = 0; b < FB; ++b) {
+    if (b > 0) __syncthreads();
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const f32x4 v = {o[b][jj * 4], o[b][jj * 4 + 1], o[b][jj * 4 + 2], o[b][jj * 4 + 3]};
+      *(f32x4*)&red[wave][lq][jj * 8 + lk * 4] = v * f;
     }
     __syncthreads();
-    for (int j = 0; j < nk; ++j) {
-      float s = 0.f;
-#pragma unroll
-      for (int i = 0; i < F32_DQ_MAX; ++i)
-        if (i < dq) s = fmaf(q[i], sK[j * ldk + part * dq + i], s);
-      s += __shfl_xor(s, 1, 64);
-      s += __shfl_xor(s, 2, 64);
-      const float mn = fmaxf(m, s);
-      const float corr = expf(m - mn), p = expf(s - mn);  // the library's exp: this mode is for exact-arithmetic parity
-      l = l * corr + p;
-      m = mn;
-#pragma unroll
-      for (int i = 0; i < F32_DQ_MAX; ++i)
-        if (i < dq) o[i] = fmaf(p, sV[j * ldk + part * dq + i], o[i] * corr);
-    }
-    __syncthreads();
-  }
-  if (qvalid) {
-    const float inv = 1.0f / l;
-    float* out = (float*)a.out + (size_t)qrow * a.ld_o + head * dhp + part * dq;
-#pragma unroll
-    for (int i = 0; i < F32_DQ_MAX; ++i)
-      if (i < dq) out[i] = o[i] * inv;
+    const int r = tid >> 3, c = (tid & 7) * 4;
+    if (q0 + r < seg_end && b * 32 + c < DHP)
+      *(f32x4*)((float*)a.out + (size_t)(q0 + r) * a.ld_o + head * DHP + b * 32 + c) =
+          (*(const f32x4*)&red[0][r][c] + *(const f32x4*)&red[1][r][c]) + (*(const f32x4*)&red[2][r][c] + *(const f32x4*)&red[3][r][c]);
   }
 }
 
@@ -120,26 +204,42 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const AttnArgs a) {
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  if (a.K <= 0 || a.K % 16 != 0 || a.lda % 4 != 0 || a.ldw % 4 != 0) return hipErrorInvalidValue;
-  const dim3 grid((a.N + 63) / 64, (a.M + 63) / 64), block(256);
+  if (a.K <= 0 || a.K % 64 != 0 || a.lda % 4 != 0 || a.ldw % 4 != 0 || a.ldo % 4 != 0 || a.N % 4 != 0) return hipErrorInvalidValue;
+  // 64 x 64 tiles read half the operand bytes of 32 x 32 ones and pay from two to a compute unit on.  Whole encodes of
+  // the 12-block encoder of width 192, in us: 1 image 523 on 32 x 32 and 807 on 64 x 64 everywhere, 8 images 846 and 965,
+  // 64 images 3 650 and 3 330; the line at 256 tiles instead of 512: 8 images 870, 16 1 200 against 1 235, 32 2 010
+  // against 1 850.
+  const long tiles64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64);
+  const int t = tiles64 >= 512 ? 64 : 32;
+  const dim3 grid((a.N + t - 1) / t, (a.M + t - 1) / t), block(256);
+#define VIT_LAUNCH(EPI)                                                                        \
+  do {                                                                                         \
+    if (t == 64) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2>), grid, block, 0, s, a);          \
+    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1>), grid, block, 0, s, a);                  \
+  } while (0)
   switch (a.epilogue) {
-    case EPI_BIAS: hipLaunchKernelGGL(gemm_f32_kernel<EPI_BIAS>, grid, block, 0, s, a); break;
-    case EPI_BIAS_GELU: hipLaunchKernelGGL(gemm_f32_kernel<EPI_BIAS_GELU>, grid, block, 0, s, a); break;
-    case EPI_BIAS_RESIDUAL: hipLaunchKernelGGL(gemm_f32_kernel<EPI_BIAS_RESIDUAL>, grid, block, 0, s, a); break;
-    case EPI_PATCH: hipLaunchKernelGGL(gemm_f32_kernel<EPI_PATCH>, grid, block, 0, s, a); break;
+    case EPI_BIAS: VIT_LAUNCH(EPI_BIAS); break;
+    case EPI_BIAS_GELU: VIT_LAUNCH(EPI_BIAS_GELU); break;
+    case EPI_BIAS_RESIDUAL: VIT_LAUNCH(EPI_BIAS_RESIDUAL); break;
+    case EPI_PATCH: VIT_LAUNCH(EPI_PATCH); break;
     default: return hipErrorInvalidValue;
   }
+#undef VIT_LAUNCH
   return hipGetLastError();
 }
 
 hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s) {
   if (a.n_work <= 0) return hipSuccess;
-  if (a.dh_pad % 4 != 0 || a.dh_pad > 4 * F32_DQ_MAX) return hipErrorInvalidValue;
-  const size_t smem = 2 * F32_BK * (a.dh_pad + 4) * sizeof(float);
-  hipError_t e = hipFuncSetAttribute((const void*)attention_f32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)(2 * F32_BK * (4 * F32_DQ_MAX + 4) * sizeof(float)));
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attention_f32_kernel, dim3(a.n_work, a.heads), dim3(256), smem, s, a);
+  if (a.ld_qkv % 4 != 0 || a.ld_o % 4 != 0) return hipErrorInvalidValue;
+  const dim3 grid(2 * (unsigned)a.n_work, a.heads), block(256);
+  switch (a.dh_pad) {  // the padded head dims the host plans
+    case 64: hipLaunchKernelGGL(attention_f32_kernel<64>, grid, block, 0, s, a); break;
+    case 72: hipLaunchKernelGGL(attention_f32_kernel<72>, grid, block, 0, s, a); break;
+    case 80: hipLaunchKernelGGL(attention_f32_kernel<80>, grid, block, 0, s, a); break;
+    case 96: hipLaunchKernelGGL(attention_f32_kernel<96>, grid, block, 0, s, a); break;
+    case 128: hipLaunchKernelGGL(attention_f32_kernel<128>, grid, block, 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

@@ -1,0 +1,53 @@
+"""The fp32 mode's matrix product and attention at the sizes where their tiles end: segments around one 32-key block, one
+round of the four waves (128 keys) and a remainder, every head width the kernel is built for, and both tile sizes.
+
+Tolerance: the fp32 bar of the parity tests; the mode's own error against 64 bits at these depths is below 1e-6."""
+import numpy as np
+import pytest
+
+import gen
+from oracle import vit_oracle as O
+from parity_util import assert_parity, say
+from test_gpu_parity import gpu_encode
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(**kw):
+    cfg = {"image_size": 24, "patch_size": 4, "channels": 3, "hidden": 64, "heads": 1, "mlp": 128, "layers_local": 1,
+           "layers_global": 1, "has_cls": 1, "final_ln": 1, "ln_eps": 1e-6, "proj_layers": 0, "proj_dims": (), "dtype": "fp32",
+           "token_merge": 1}
+    cfg.update(kw)
+    return cfg
+
+
+@pytest.mark.parametrize("dh,heads,grid,has_cls,tiles", [
+    (64, 3, 2, 1, [6, 1, 13]),    # 5 tokens a tile; global segments of 30, 5 and 65 keys
+    (72, 2, 4, 0, [2, 8, 1, 9]),  # 16 tokens a tile; global segments of 32, 128, 16 and 144 keys
+    (80, 1, 8, 0, [1, 2, 4]),     # 64, 128 and 256 keys
+    (96, 2, 11, 1, [1, 3]),       # 122 and 366 keys
+    (128, 1, 14, 1, [1, 2]),      # 197 and 394 keys
+])
+def test_segment_lengths_and_head_dims(dh, heads, grid, has_cls, tiles):
+    cfg = _cfg(image_size=4 * grid, hidden=dh * heads, heads=heads, mlp=8 * (dh + 3), has_cls=has_cls)
+    say(f"case fp32 head dim {dh} x {heads}, {grid * grid + has_cls} tokens a tile, tiles {tiles}")
+    to = np.concatenate([[0], np.cumsum(tiles)]).astype(np.int32)
+    w, px = gen.make_weights(cfg, seed=dh), gen.make_pixels(cfg, int(to[-1]), seed=grid)
+    got, _ = gpu_encode(cfg, w, px, [len(tiles)], to)
+    want, _ = O.vit_oracle_encode(cfg, w, px, [len(tiles)], to)
+    assert_parity(got, want, "fp32", f"fp32 dh{dh}")
+
+
+def test_tile_sizes_give_the_same_bits():
+    """An image alone takes the 32 x 32 tiles in every product; 84 of them (5460 rows) take 64 x 64 in all but one."""
+    cfg = _cfg(image_size=32, hidden=384, heads=6, mlp=520, proj_layers=1, proj_dims=(200,))
+    say("case fp32 tile sizes")
+    n = 84
+    w, px = gen.make_weights(cfg, seed=1), gen.make_pixels(cfg, n, seed=2)
+    whole, _ = gpu_encode(cfg, w, px, [n], np.arange(n + 1, dtype=np.int32))
+    T = gen.tokens_per_tile(cfg)
+    for i in (0, 41, n - 1):
+        alone, _ = gpu_encode(cfg, w, px[i:i + 1], [1], np.array([0, 1], dtype=np.int32))
+        assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
+    want, _ = O.vit_oracle_encode(cfg, w, px[-2:], [2], np.arange(3, dtype=np.int32))
+    assert_parity(whole[-2 * T:], want, "fp32", "fp32 large tiles")

@@ -234,12 +234,14 @@ vit_status_t vit_profile_tiles_read(vit_encoder_t* enc, double* main_loop_us, do
  * Pull-style hand-off of finished image tokens (paper Sec. 4.3, "Image Token Transfer": the
  * transfer is deferred until all image tokens of a request are ready; the consumer then pulls
  * them from the producers' addresses).  Host-side table of device pointers and events; the
- * only device work is the copy queued by vit_handoff_pull.  All functions are thread-safe.
+ * only device work is the gather (or, for memory that is not `device`'s own, the copies) queued
+ * by vit_handoff_pull.  All functions are thread-safe.
  *
  *   vit_handoff_expect   announces request `request_id` with n_images (1 ... 65536) images.
  *   vit_handoff_publish  image `image_index` of the request lies at `tokens` (device memory,
  *                        `bytes` > 0 long) once the work queued so far on `stream` (hipStream_t;
- *                        NULL = null stream) has finished: an event is recorded there.  The
+ *                        NULL = null stream) has finished: an event is recorded there
+ *                        unless the stream has nothing left to do.  The
  *                        memory stays the producer's; it must stay valid and unchanged until
  *                        vit_handoff_release and until any pull that was queued has run.
  *   vit_handoff_complete 1 when every image has been published (device work may still be in

@@ -5,9 +5,8 @@
 //
 // Two kernels share the fragment layout and the epilogues; both move their operands global -> LDS
 // directly (global_load_lds_dwordx4) and are described where they are defined:
-// * gemm_bf16_ring_kernel (below 384 tiles of 256 x 256, and short last rounds of the large kernel): one 128 x 128
-//   (or 64 x 128) tile per workgroup, eight
-//   waves of 64 x 32, a ring of four (or two) 64-wide k-stages;
+// * gemm_bf16_ring_kernel (below 384 tiles of 256 x 256, and short last rounds of the large kernel): one 128 x 128,
+//   64 x 128 or 64 x 64 tile per workgroup, a ring of four (or two) 64-wide k-stages;
 // * gemm_bf16_dma_kernel (everything large): persistent, 256 x 256 tiles, eight waves of 128 x 64,
 //   two 64-wide k-stages.
 // * LDS tiles are [row][64 bf16] with the 16-byte chunks XOR-swizzled by (row >> 1) & 7:
@@ -17,9 +16,8 @@
 //   up with four consecutive output columns of one token row per register quad.  The
 //   epilogue adds bias, applies GELU / residual, converts, stages the 32 x TN block of a
 //   wave through LDS and writes rows back with 16 bytes per lane.
-// * Workgroup ids are dealt round-robin to the 8 XCDs; each XCD walks its own range of
-//   row blocks in 8 x 4 tile groups so the tiles in flight on one XCD share A and W
-//   slices in that XCD's L2.
+// * Workgroup ids are dealt round-robin to the 8 XCDs; each XCD walks its own tiles in blocks
+//   so the tiles in flight on one XCD share A and W slices in that XCD's L2.
 #include <type_traits>
 
 #include "common.h"
@@ -29,7 +27,7 @@ namespace vitenc {
 namespace {
 
 constexpr int BK = 64;  // bf16 elements per k-step = 128 bytes = 8 chunks of 16 bytes
-constexpr int GROUP_M = 8, GROUP_N = 4;
+constexpr int GROUP_M = 8;  // row blocks that the small-problem kernel walks together
 
 // Epilogue of one wave.  acc[i][j] is a transposed 32x32 block: the lane holds token row
 // row0 + 32i + (lane & 31); register 4jj + e holds output column ncol0 + 32j + 8jj + 4(lane >> 5) + e.
@@ -628,107 +626,91 @@ __global__ __launch_bounds__(512) void gemm_bf16_dma_kernel(const GemmArgs a, in
 
 // ---------------------------------------------------------------------------------------------
 // Small-problem kernel (fewer than 384 tiles of 256 x 256; also the short last round of a large product that is
-// one column band wide, see launch_gemm_bf16): one 128 x 128 tile per workgroup, eight
-// waves of 64 x 32 (two per SIMD), operands global -> LDS directly into a ring of R_NS 64-wide
-// k-stages (32 KiB each).  One wait + barrier per stage establishes that the stage has landed for
-// every wave and that the slot refilled next is dead; all fragments of a stage are read before
-// its MFMAs start (registers are plentiful here).
-// * R_NS = 4 when there are no more tiles than compute units: a workgroup is then alone on its
-//   unit and nothing but its own instruction order hides latency, so the loads run three stages
-//   ahead.
-// * R_NS = 2 (64 KiB) beyond that when it needs fewer rounds (see launch_ring): two workgroups share a unit
-//   and cover each other's waits, and a grid of 1.2 or 1.7 rounds no longer costs 2.
-// (The register-staged predecessor spent 2 800 clocks per k-stage on 512 clocks of MFMA work: LDS
-// writes, their waits and un-overlapped fragment reads.)
-// * BM = 64 (a 64 x 128 tile, waves of 32 x 32, 24 KiB stages) for the very smallest products, one or two
-//   images: twice the workgroups on the idle units, and a k-stage that is a third shorter because it
-//   moves a third less through LDS (a single image's fc2 is a chain of 64 stages on 40 units otherwise).
-//   A token's k-steps are added in the same order in every variant.
-constexpr int R_BN = 128;
-constexpr int ring_stage_bytes(int bm) { return (bm + R_BN) * D_ROW; }  // 32 KiB (BM = 128) or 24 KiB
-
-template <int EPI, int R_NS, int BM>
-__global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(const GemmArgs a, int tiles_m, int tiles_n,
-                                                             int mt_per_xcd, int n_bands) {
-  static_assert(BM == 128 || BM == 64, "tile heights: 128 or 64 rows");
-  constexpr int R_BM = BM, R_STAGE_BYTES = ring_stage_bytes(BM);
-  constexpr int FM = BM / 64, FN = 1, TM = BM / 2, TN = 32;
-  constexpr int LOADS = BM == 128 ? 4 : 3;  // direct-to-LDS instructions per wave and stage
-  static_assert(8 * 32 * (TN * 4 + 16) <= R_NS * R_STAGE_BYTES, "epilogue staging must fit in the ring");
+// one column band wide, see launch_gemm_bf16): one BM x BN tile per workgroup, waves of BM/2 x 32, operands
+// global -> LDS directly into a ring of NS 64-wide k-stages.  One wait + barrier per stage establishes that the
+// stage has landed for every wave and that the slot refilled next is dead; all fragments of a stage are read
+// before its MFMAs start.
+// What bounds it is the rate at which one compute unit gets operands: 45 to 70 GB/s whatever the tile, the depth of
+// the ring or the number of waves.  With every MFMA left out a single image's products take the same time to 1 %, with
+// every fragment read left out likewise, and without the loads half of it (24 of 45 us, fc2 on 128 x 128 tiles);
+// fragments read one stage ahead, between the MFMAs, gain 1 to 5 %.  So the tile is chosen for the number of units
+// that it keeps loading, and the cut over the XCDs for how often an XCD finds its operands in its own L2.
+// A token's k-steps are added in the same order in every variant.
+template <int EPI, int NS, int BM, int BN>
+__global__ __launch_bounds__(BN * 4) void gemm_bf16_ring_kernel(const GemmArgs a, int tiles_m, int tiles_n, int split_n,
+                                                                  int mt, int nt) {
+  constexpr int STAGE = (BM + BN) * D_ROW;
+  constexpr int WN = BN / 32, NW = 2 * WN, TM = BM / 2, FM = TM / 32;  // waves along the columns, in all; a wave's rows
+  constexpr int LA = BM / 8 / NW, LW = BN / 8 / NW, LOADS = LA + LW;  // direct-to-LDS instructions per wave and stage, 8 rows each
+  static_assert(LW == 2 && (LA == 1 || LA == 2), "tiles of 64 or 128 rows by 128 columns, or of 64 by 64");
+  static_assert(NW * 32 * (32 * 4 + 16) <= NS * STAGE, "epilogue staging must fit in the ring");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
-  // ---- tile assignment: workgroup ids are dealt round-robin to the 8 XCDs; each XCD walks its own range of
-  //      row blocks in 8 x 4 tile groups so the tiles in flight on one XCD share A and W slices in its L2
+  // ---- tile assignment: workgroup ids are dealt round-robin to the 8 XCDs; XCD (xr, xc) of the 8 / split_n x split_n
+  //      cut owns mt x nt tiles and walks them in blocks of 8 rows, column by column
   const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
-  const int blk = q / (GROUP_M * GROUP_N), r = q - blk * (GROUP_M * GROUP_N);
-  const int mb = blk / n_bands, nb = blk - mb * n_bands;
-  const int m_local = mb * GROUP_M + r / GROUP_N;
-  const int tile_m = xcd * mt_per_xcd + m_local, tile_n = nb * GROUP_N + (r % GROUP_N);
-  if (m_local >= mt_per_xcd || tile_m >= tiles_m || tile_n >= tiles_n) return;
-  const int m0 = tile_m * R_BM, n0 = tile_n * R_BN;
+  const int blk = q / (GROUP_M * nt), rem = q - blk * (GROUP_M * nt);
+  const int h = min(GROUP_M, mt - blk * GROUP_M);
+  const int tile_m = (xcd / split_n) * mt + blk * GROUP_M + rem % h, tile_n = (xcd % split_n) * nt + rem / h;
+  if (tile_m >= tiles_m || tile_n >= tiles_n) return;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = wave / WN, wn = wave % WN;
   const int lrow = lane & 31, lk = lane >> 5;
 
-  // ---- loader: an instruction fills 8 rows of 128 bytes; wave w moves rows [16w, 16w + 16) of a 128-row
-  //      operand tile (two instructions) or rows [8w, 8w + 8) of the 64-row A tile (one).  The chunk that
-  //      lands in LDS chunk c of row r is c ^ ((r >> 1) & 7).
-  const int ld_row = wave * 16 + (lane >> 3);
+  // ---- loader: an instruction fills 8 rows of 128 bytes; the chunk that lands in LDS chunk c of row r is
+  //      c ^ ((r >> 1) & 7), which for row 8i + lane / 8 is one of two per-lane offsets, by the parity of i
   const int ld_chunk = (lane & 7) ^ (lane >> 4);
-  const int a_row = BM == 128 ? ld_row : wave * 8 + (lane >> 3);
-  const int a_chunk = BM == 128 ? ld_chunk : ld_chunk ^ (4 * (wave & 1));
-  const uint32_t offA0 = (uint32_t)(a_row * a.lda + a_chunk * 8) * 2u;
-  const uint32_t offA1 = (uint32_t)((ld_row + 8) * a.lda + (ld_chunk ^ 4) * 8) * 2u;  // BM = 128 only
-  const uint32_t offW0 = (uint32_t)(ld_row * a.ldw + ld_chunk * 8) * 2u;
-  const uint32_t offW1 = (uint32_t)((ld_row + 8) * a.ldw + (ld_chunk ^ 4) * 8) * 2u;
-  const unsigned char* const baseA = (const unsigned char*)a.A + (size_t)m0 * a.lda * 2;
-  const unsigned char* const baseW = (const unsigned char*)a.W + (size_t)n0 * a.ldw * 2;
+  const int odd_a = LA == 1 ? 4 * (wave & 1) : 0;  // parity of the wave's first piece of A
+  const uint32_t offA0 = (uint32_t)((lane >> 3) * a.lda + (ld_chunk ^ odd_a) * 8) * 2u;
+  const uint32_t offA1 = (uint32_t)((lane >> 3) * a.lda + (ld_chunk ^ 4) * 8) * 2u;  // of the second, if there are two
+  const uint32_t offW0 = (uint32_t)((lane >> 3) * a.ldw + ld_chunk * 8) * 2u;
+  const uint32_t offW1 = (uint32_t)((lane >> 3) * a.ldw + (ld_chunk ^ 4) * 8) * 2u;
+  const unsigned char* const baseA = (const unsigned char*)a.A + (size_t)(m0 + wave * LA * 8) * a.lda * 2;
+  const unsigned char* const baseW = (const unsigned char*)a.W + (size_t)(n0 + wave * LW * 8) * a.ldw * 2;
+  const size_t a_step = (size_t)16 * a.lda, w_step = (size_t)16 * a.ldw;  // bytes per 8 rows
   auto dma16 = [&](const unsigned char* gbase, uint32_t goff, unsigned char* lptr) {
     const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lptr);
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(goff), "s"(gbase)
                  : "memory", "m0");
   };
-  auto issue_stage = [&](int slot, int kt) {  // LOADS instructions per wave
-    unsigned char* stage = smem + slot * R_STAGE_BYTES;
-    const unsigned char* ga = baseA + kt * D_ROW;
-    const unsigned char* gw = baseW + kt * D_ROW;
-    if constexpr (BM == 128) {
-      dma16(ga, offA0, stage + wave * 16 * D_ROW);
-      dma16(ga, offA1, stage + wave * 16 * D_ROW + 8 * D_ROW);
-    } else {
-      dma16(ga, offA0, stage + wave * 8 * D_ROW);
-    }
-    dma16(gw, offW0, stage + R_BM * D_ROW + wave * 16 * D_ROW);
-    dma16(gw, offW1, stage + R_BM * D_ROW + wave * 16 * D_ROW + 8 * D_ROW);
+  auto issue_stage = [&](int slot, int kt) {
+    unsigned char* const st = smem + slot * STAGE;
+#pragma unroll
+    for (int i = 0; i < LA; ++i)
+      dma16(baseA + kt * D_ROW + i * a_step, i ? offA1 : offA0, st + (wave * LA + i) * 8 * D_ROW);
+#pragma unroll
+    for (int i = 0; i < LW; ++i)
+      dma16(baseW + kt * D_ROW + i * w_step, i ? offW1 : offW0, st + (BM + (wave * LW + i) * 8) * D_ROW);
   };
 
   const int sw = (lrow >> 1) & 7;
   const uint32_t fa_off = (uint32_t)((wm * TM + lrow) * D_ROW + ((lk ^ sw) << 4));
-  const uint32_t fb_off = (uint32_t)(R_BM * D_ROW + (wn * TN + lrow) * D_ROW + ((lk ^ sw) << 4));
-
-  f32x16 acc[FM][FN];
+  const uint32_t fb_off = (uint32_t)((BM + wn * 32 + lrow) * D_ROW + ((lk ^ sw) << 4));
+  f32x16 acc[FM][1];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[i][0][v] = 0.f;
 
+  // ---- stages.  The tail re-reads the last one into slots nobody uses any more, so that every stage issues the same
+  //      loads and the wait can count them.
+  constexpr int AHEAD = LOADS * (NS - 2);  // loads that may be in flight at the wait: stages kt + 1 .. kt + NS - 2
+  static_assert(AHEAD < 16, "the low four bits of vmcnt");
   const int KT = a.K / D_BK;
-  // The tail re-reads the last k-stage into slots nobody uses any more, so that every stage issues
-  // the same four loads and the wait below can count them.
 #pragma unroll
-  for (int s = 0; s < R_NS - 1; ++s) issue_stage(s, min(s, KT - 1));
-
+  for (int s = 0; s < NS - 1; ++s) issue_stage(s, min(s, KT - 1));
   bf16x8 fa[4][FM], fb[4];  // all four sub-steps of a stage are read up front: registers are plentiful here
+  int slot = 0, fill = NS - 1;  // of the stage being multiplied, of the stage being loaded
   for (int kt = 0; kt < KT; ++kt) {
-    const int slot = kt & (R_NS - 1);
-    // this wave's loads of stage kt have landed (those of the two later stages may be in flight) and
-    // its LDS reads of stage kt - 1 are complete; then meet the other waves
-    __builtin_amdgcn_s_waitcnt(0x0070 | (LOADS * (R_NS - 2)));
+    // this wave's loads of stage kt have landed (those of later stages may be in flight) and its LDS reads of stage
+    // kt - 1 are complete; then meet the other waves
+    __builtin_amdgcn_s_waitcnt(0x0070 | AHEAD);
     __builtin_amdgcn_s_barrier();
-    issue_stage((kt + R_NS - 1) & (R_NS - 1), min(kt + R_NS - 1, KT - 1));
-    const unsigned char* st = smem + slot * R_STAGE_BYTES;
+    issue_stage(fill, min(kt + NS - 1, KT - 1));
+    const unsigned char* const st = smem + slot * STAGE;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
@@ -742,57 +724,42 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(const GemmArgs a, i
       for (int i = 0; i < FM; ++i)
         acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks], fa[ks][i], acc[i][0], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
+    fill = slot;
+    slot = slot + 1 == NS ? 0 : slot + 1;
   }
   // the trailing loads still write LDS, which the epilogue reuses
   __builtin_amdgcn_s_waitcnt(0x0070);
   __builtin_amdgcn_s_barrier();
-  wave_epilogue<EPI, FM, FN>(a, acc, smem, m0 + wm * TM, n0 + wn * TN, wave, lane);
+  wave_epilogue<EPI, FM, 1>(a, acc, smem, m0 + wm * TM, n0 + wn * 32, wave, lane);
 }
 
-hipError_t launch_ring(const GemmArgs& a, hipStream_t s) {
-  const int tiles_n = (a.N + R_BN - 1) / R_BN;
-  // At most 96 tiles of 128 x 128 (the N = 1024 products of one or two images): 64-row tiles, still fewer
-  // workgroups than units.  Measured at 577 and 1154 rows: 40 and 80 tiles gain 30-45 %, 120 tiles (QKV of
-  // one image) lose 15 %.  Products of at most eight tile columns (N <= 1024) keep gaining up to one 64-row tile
-  // per unit (three images: 112 tiles of 128 rows, 224 of 64: out-proj and fc2 18-22 % faster), and again where
-  // the 128-row tiles are a few more than the units and their second workgroups leave most units with one: there
-  // three 64-row workgroups with two-stage rings share a unit in a single round of up to 768 tiles (eight images,
-  // 296 tiles of 128 rows: 7 %).
-  const long tiles128 = (long)((a.M + 127) / 128) * tiles_n, tiles64 = (long)((a.M + 63) / 64) * tiles_n;
-  const bool narrow = tiles_n <= 8;
-  const bool half3 = narrow && tiles128 > 256 && tiles64 <= 768;  // three two-stage workgroups of 64 rows per unit
-  const bool half = tiles128 <= 96 || (narrow && tiles64 <= 256) || half3;
-  const int bm = half ? 64 : 128;
-  const int tiles_m = (a.M + bm - 1) / bm;
-  const int mt_per_xcd = (tiles_m + 7) / 8;
-  const int n_bands = (tiles_n + GROUP_N - 1) / GROUP_N;
-  const int m_blocks = (mt_per_xcd + GROUP_M - 1) / GROUP_M;
-  const long grid = 8L * m_blocks * n_bands * GROUP_M * GROUP_N;
+template <int NS, int BM, int BN>
+hipError_t launch_ring_as(const GemmArgs& a, hipStream_t s) {
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  // The cut over the XCDs, rows x columns: 2 x 4 unless another one deals the tiles out more than a tenth more evenly,
+  // then the most even one, then the one whose XCDs read the fewest operand rows.  Measured at 1731 to 5103 rows with
+  // N = 3072 to 4352: 2 x 4 is fastest or within 2 % of it everywhere, 8 x 1 (each XCD reads all of W) up to 20 % slower
+  // (5103 x 3456: 53 against 64 us), 4 x 2 up to 18 %, 1 x 8 up to 20 %.  At N = 1152 (9 tile columns, 60 tiles to an
+  // XCD against 45 of 8 x 1) it is 6 % slower.
+  auto tiles_of = [&](int sn) { return (long)((tiles_m + 8 / sn - 1) / (8 / sn)) * ((tiles_n + sn - 1) / sn); };
+  int split_n = 1;
+  long best = -1;
+  for (int sn = 1; sn <= 8; sn *= 2) {
+    const int sm = 8 / sn;
+    const long cost = tiles_of(sn) * 65536 + ((tiles_m + sm - 1) / sm * BM + (tiles_n + sn - 1) / sn * BN) / 64;
+    if (best < 0 || cost < best) { best = cost; split_n = sn; }
+  }
+  if (tiles_of(4) * 10 <= tiles_of(split_n) * 11) split_n = 4;
+  const int sm = 8 / split_n, mt = (tiles_m + sm - 1) / sm, nt = (tiles_n + split_n - 1) / split_n;
+  const long grid = 8L * mt * nt;
   if (grid > 0x7fffffffL) return hipErrorInvalidValue;
-  // Up to one tile per compute unit: the four-stage ring, whose loads run three stages ahead.  Beyond that either
-  // two-stage rings (64 KiB), two workgroups to a unit covering each other's waits, in rounds of 512 tiles, or the
-  // four-stage ring in rounds of 256: a k-stage of a workgroup takes 0.95 us when it shares its unit and 0.58 us
-  // when it has it alone (measured on the N = 1024 products), so whichever needs fewer rounds by that measure.
-  const long n_tiles = (long)tiles_m * tiles_n;
-  const bool two = !half && n_tiles > 256 && ((n_tiles + 511) / 512) * 95 < ((n_tiles + 255) / 256) * 58;
-#define VIT_LAUNCH_NS(EPI, NS, BM)                                                                                   \
-  do {                                                                                                               \
-    auto kfn = gemm_bf16_ring_kernel<EPI, NS, BM>;                                                                   \
-    constexpr int lds = NS * ring_stage_bytes(BM);                                                                   \
-    static LdsLimitOnce lds_limit;                                                                                   \
-    if (hipError_t e = lds_limit.ensure((const void*)kfn, lds); e != hipSuccess) return e;                           \
-    hipLaunchKernelGGL(kfn, dim3((unsigned)grid), dim3(512), lds, s, a, tiles_m, tiles_n, mt_per_xcd, n_bands);      \
-  } while (0)
-#define VIT_LAUNCH(EPI)            \
-  do {                             \
-    if (half3)                     \
-      VIT_LAUNCH_NS(EPI, 2, 64);   \
-    else if (half)                 \
-      VIT_LAUNCH_NS(EPI, 4, 64);   \
-    else if (two)                  \
-      VIT_LAUNCH_NS(EPI, 2, 128);  \
-    else                           \
-      VIT_LAUNCH_NS(EPI, 4, 128);  \
+  constexpr int lds = NS * (BM + BN) * D_ROW;
+#define VIT_LAUNCH(EPI)                                                                                               \
+  do {                                                                                                                \
+    auto kfn = gemm_bf16_ring_kernel<EPI, NS, BM, BN>;                                                           \
+    static LdsLimitOnce lds_limit;                                                                                    \
+    if (hipError_t e = lds_limit.ensure((const void*)kfn, lds); e != hipSuccess) return e;                            \
+    hipLaunchKernelGGL(kfn, dim3((unsigned)grid), dim3(BN * 4), lds, s, a, tiles_m, tiles_n, split_n, mt, nt);           \
   } while (0)
   switch (a.epilogue) {
     case EPI_BIAS: VIT_LAUNCH(EPI_BIAS); break;
@@ -803,8 +770,27 @@ hipError_t launch_ring(const GemmArgs& a, hipStream_t s) {
     default: return hipErrorInvalidValue;
   }
 #undef VIT_LAUNCH
-#undef VIT_LAUNCH_NS
   return hipGetLastError();
+}
+
+hipError_t launch_ring(const GemmArgs& a, hipStream_t s) {
+  // A product with few tiles of 128 x 128 leaves units idle, so the smallest products take smaller tiles: 64 x 64 (four stages,
+  // two workgroups to a unit) up to 384 of them, 64 x 128 (four stages) up to one per unit; 128 x 128 tiles with four
+  // stages up to one per unit, beyond that with two stages, two workgroups to a unit covering each other's waits.
+  // Measured, in us a launch: 577 rows, out-proj / fc2 / QKV / fc1 on 64 x 64 11.0 / 23.2 / 13.9 / 18.2, on 64 x 128
+  // 13.3 / 31.0 / 12.6 / 20.4, on 128 x 128 17.4 / 42.2 / 15.1 / 16.3; 1154 rows, out-proj / fc2 on 64 x 64 13.7 / 30.0,
+  // on 64 x 128 14.2 / 33.5; 1731 rows 15.4 / 35.5 and 14.2 / 32.8.  1154 rows, fc1 (320 tiles) on four stages 29.5, on
+  // two 21.8; 2885 rows, fc1 (736 tiles) 39.8 and 35.8, QKV (552) 36.8 and 31.8.  Between 513 and 768 tiles the four-stage
+  // ring needs three rounds to the other's two, and a stage takes 0.58 us alone on its unit and 0.95 shared: with many
+  // stages that decides (11540 rows, fc2, 728 tiles of 64 stages: 129 against 136), with 16 the epilogues do, which two
+  // workgroups on a unit cover for each other (out-proj 51 against 49).
+  const auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+  const long t128 = tiles(128, 128);
+  if (t128 > 512 && t128 <= 768 && a.K >= 2048) return launch_ring_as<4, 128, 128>(a, s);
+  if (t128 > 256) return launch_ring_as<2, 128, 128>(a, s);
+  if (tiles(64, 128) > 256) return launch_ring_as<4, 128, 128>(a, s);
+  if (tiles(64, 64) > 384) return launch_ring_as<4, 64, 128>(a, s);
+  return launch_ring_as<4, 64, 64>(a, s);
 }
 
 hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {

@@ -1,0 +1,30 @@
+"""Every tile of the small-problem matrix product: batch sizes at which the products of one encoder take 64 x 64, 64 x 128
+and 128 x 128 tiles with two and four stages, with ragged last row and column blocks.  An image's tokens must not depend on
+the tile (bit for bit against the image alone), and the image alone is held to the oracle at the bar of the parity tests."""
+import numpy as np
+import pytest
+
+import gen
+from oracle import vit_oracle as O
+from parity_util import assert_parity, say
+from test_gpu_parity import gpu_encode
+
+pytestmark = pytest.mark.gpu
+
+CFG = {"image_size": 60, "patch_size": 4, "channels": 3, "hidden": 512, "heads": 8, "mlp": 2056, "layers_local": 2,
+       "layers_global": 0, "has_cls": 1, "final_ln": 1, "ln_eps": 1e-6, "proj_layers": 1, "proj_dims": (1096,), "dtype": "bf16",
+       "token_merge": 1}
+
+
+@pytest.mark.parametrize("n", [2, 3, 5, 9, 20, 33, 80])
+def test_tokens_do_not_depend_on_the_tile(n):
+    say(f"case matrix-product tiles, {n} images of 226 tokens")
+    w, px = gen.make_weights(CFG, seed=3), gen.make_pixels(CFG, n, seed=n)
+    whole, _ = gpu_encode(CFG, w, px, [n], np.arange(n + 1, dtype=np.int32))
+    T = gen.tokens_per_tile(CFG)
+    one = np.array([0, 1], dtype=np.int32)
+    for i in sorted({0, n // 2, n - 1}):
+        alone, _ = gpu_encode(CFG, w, px[i:i + 1], [1], one)
+        assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
+    want, _ = O.vit_oracle_encode(CFG, w, px[-1:], [1], one)
+    assert_parity(whole[-T:], want, "bf16", f"tiles n={n}")

@@ -87,3 +87,34 @@ def test_preprocess_capacity_error_launches_nothing():
     assert e.value.status == -3
     torch.cuda.synchronize()
     assert (out == 7.0).all()
+
+
+@pytest.mark.parametrize("H,W,C,S,rows,cols,thumb,shift", [
+    (7, 5, 3, 8, 2, 2, True, 0),        # 8-byte windows reach past the last row's end in most columns
+    (3, 3, 1, 12, 1, 1, False, 0),      # 9 bytes in all
+    (2, 2, 2, 4, 2, 1, True, 0),        # exactly 8 bytes
+    (7, 1, 1, 8, 1, 1, True, 0),        # 7 bytes: the general kernel
+    (31, 29, 4, 20, 3, 2, True, 0),
+    (50, 33, 3, 10, 2, 3, True, 0),     # a side that is no multiple of 4
+    (64, 301, 3, 336, 1, 2, True, 0),
+    (40, 40, 3, 16, 2, 2, True, 1),     # an output buffer off 16-byte alignment
+])
+def test_preprocess_edges(H, W, C, S, rows, cols, thumb, shift):
+    import torch
+
+    import paper_2502_00937_amd as V
+
+    say(f"case preprocess edges {H}x{W}x{C} -> {rows}x{cols} tiles of {S}, output shifted by {shift}")
+    img = np.random.default_rng(H * W).integers(0, 256, (H, W, C), dtype=np.uint8)
+    n = rows * cols + (1 if thumb else 0)
+    flat = torch.zeros(shift + n * C * S * S + 4, device="cuda")
+    out = flat[shift:shift + n * C * S * S].view(n, C, S, S)
+    # the image ends where its allocation's used part ends: a marker behind it must not show in the result
+    raw = torch.full((img.size + 16,), 255, dtype=torch.uint8, device="cuda")
+    raw[:img.size] = torch.from_numpy(img.reshape(-1)).cuda()
+    V.preprocess_tiles(raw[:img.size].view(H, W, C), S, rows, cols, thumb, MEAN[:C], STD[:C], out=out)
+    torch.cuda.synchronize()
+    want = P.preprocess_tiles(img, S, rows, cols, thumb, MEAN[:C], STD[:C])
+    atol = 4e-7 * max(rows * S, cols * S) / min(STD[:C]) + 2e-6
+    assert np.abs(out.cpu().numpy() - want).max() <= atol
+    assert float(flat[:shift].abs().sum()) == 0 and float(flat[shift + n * C * S * S:].abs().sum()) == 0

@@ -130,8 +130,8 @@ __global__ __launch_bounds__(256) void patch_gather_kernel(const float* __restri
 // row is contiguous across the strip's patches), scattered into an LDS image of the strip's g output rows, and
 // written out in 16-byte pieces with the padding columns zero.  Every pixel is read once and every output byte
 // written once with full-width accesses; the element-per-thread form above read 3.2 times the pixel bytes.
-template <typename OutT>
-__global__ __launch_bounds__(256) void patch_gather_strip_kernel(const float* __restrict__ px, OutT* __restrict__ out,
+template <typename OutT, int NT>
+__global__ __launch_bounds__(NT) void patch_gather_strip_kernel(const float* __restrict__ px, OutT* __restrict__ out,
                                                                  int ld, int C, int S, int p, int g, int K, int Kpad) {
   extern __shared__ __attribute__((aligned(16))) unsigned char strip_raw[];
   OutT* strip = (OutT*)strip_raw;  // [g][Kpad]
@@ -140,14 +140,14 @@ __global__ __launch_bounds__(256) void patch_gather_strip_kernel(const float* __
   const int gy = blockIdx.x - (int)tile * g;
   // padding columns K .. Kpad - 1 of every row
   const int padc = Kpad - K;
-  for (int it = tid; it < g * padc; it += 256) strip[(it / padc) * Kpad + K + it % padc] = (OutT)0;
+  for (int it = tid; it < g * padc; it += NT) strip[(it / padc) * Kpad + K + it % padc] = (OutT)0;
   // image rows r = c * p + py, one wave per row at a time, 4 pixels per lane; pixels past the last whole patch
   // are dropped.  x / p by a float reciprocal (exact for x < 2^20 with the half added).
   const int quads = S >> 2, used = g * p;
   const float inv_p = 1.0f / (float)p;
   const float* base = px + ((tile * C) * S + (long)gy * p) * S;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  for (int r = wave; r < C * p; r += 4) {
+  for (int r = wave; r < C * p; r += NT / 64) {
     const int c = r / p, py = r - c * p;  // wave-uniform
     const float* row = base + ((long)c * S + py) * S;
     OutT* drow = strip + r * p;
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void patch_gather_strip_kernel(const float* __
   __syncthreads();
   const int chunks = Kpad * (int)sizeof(OutT) / 16;  // 16-byte pieces per output row
   unsigned char* orow = (unsigned char*)(out + (tile * g * g + (long)gy * g) * ld);
-  for (int it = tid; it < g * chunks; it += 256) {
+  for (int it = tid; it < g * chunks; it += NT) {
     const int row = it / chunks, ch = it - row * chunks;
     *(u32x4*)(orow + (long)row * ld * sizeof(OutT) + ch * 16) = *(const u32x4*)(strip_raw + ((long)row * Kpad * sizeof(OutT)) + ch * 16);
   }
@@ -264,18 +264,23 @@ hipError_t launch_patch_gather(const float* pixels, void* patches, int ld, int n
   const size_t es = out_bf16 ? 2 : 4, strip_bytes = (size_t)g * Kpad * es;
   if (S % 4 == 0 && (Kpad * es) % 16 == 0 && ((size_t)ld * es) % 16 == 0 && strip_bytes <= 64 * 1024 &&
       (long)n_tiles * g <= 0x7fffffffL) {
-    const dim3 sgrid((unsigned)(n_tiles * g)), sblock(256);
-    if (out_bf16) {
-      static LdsLimitOnce lim;
-      if (hipError_t e = lim.ensure((const void*)patch_gather_strip_kernel<bf16_t>, 64 * 1024); e != hipSuccess) return e;
-      hipLaunchKernelGGL(patch_gather_strip_kernel<bf16_t>, sgrid, sblock, strip_bytes, s, pixels, (bf16_t*)patches, ld, C, S,
-                         p, g, K, Kpad);
-    } else {
-      static LdsLimitOnce lim;
-      if (hipError_t e = lim.ensure((const void*)patch_gather_strip_kernel<float>, 64 * 1024); e != hipSuccess) return e;
-      hipLaunchKernelGGL(patch_gather_strip_kernel<float>, sgrid, sblock, strip_bytes, s, pixels, (float*)patches, ld, C, S, p,
-                         g, K, Kpad);
-    }
+    // A strip is a chain of loads per wave, 42 image rows dealt over the workgroup's waves: with no more strips than units
+    // nothing else hides their latency, and sixteen waves make the chain four times shorter (gather and CLS rows of one
+    // 336-pixel image 24 us with four waves, 15 with eight, 11 with sixteen; of 150, 3600 strips, 79, 67 and 80).
+    const bool wide = (long)n_tiles * g <= 512;
+    const dim3 sgrid((unsigned)(n_tiles * g));
+#define VIT_LAUNCH(T, NT)                                                                                              \
+  do {                                                                                                                 \
+    auto kfn = patch_gather_strip_kernel<T, NT>;                                                                       \
+    static LdsLimitOnce lim;                                                                                           \
+    if (hipError_t e = lim.ensure((const void*)kfn, 64 * 1024); e != hipSuccess) return e;                             \
+    hipLaunchKernelGGL(kfn, sgrid, dim3(NT), strip_bytes, s, pixels, (T*)patches, ld, C, S, p, g, K, Kpad);            \
+  } while (0)
+    if (out_bf16 && wide) VIT_LAUNCH(bf16_t, 1024);
+    else if (out_bf16) VIT_LAUNCH(bf16_t, 512);
+    else if (wide) VIT_LAUNCH(float, 1024);
+    else VIT_LAUNCH(float, 512);
+#undef VIT_LAUNCH
     return hipGetLastError();
   }
   const dim3 grid((unsigned)((total + 255) / 256)), block(256);

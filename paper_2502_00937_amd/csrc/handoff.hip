@@ -50,11 +50,22 @@ void drop(Request& r) {
     if (p.ready) (void)hipEventDestroy(p.ready);
 }
 
+// Whether `s` is a stream of `device`, on which that device's events can be recorded and its kernels launched.
+bool stream_of(hipStream_t s, int device) {
+  if (!s || s == hipStreamPerThread || s == hipStreamLegacy) return true;  // of whichever device is current
+  hipDevice_t d = -1;
+  const bool ok = hipStreamGetDevice(s, &d) == hipSuccess && (int)d == device;
+  if (!ok) (void)hipGetLastError();
+  return ok;
+}
+
 // Whether everything queued on `s` so far has finished.  A stream that is being captured must not be asked (it has no
 // progress to report, and the question would end the capture); relaxed mode keeps a capture elsewhere out of it.
-bool finished(hipStream_t s) {
+// A stream of another device never counts as finished, so that it is refused where its event is recorded, at work or not.
+bool finished(hipStream_t s, int device) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   bool idle = false;
+  if (!stream_of(s, device)) return false;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
     (void)hipGetLastError();
@@ -175,8 +186,8 @@ vit_status_t vit_handoff_publish(vit_handoff_t* h, int64_t request_id, int32_t i
   hipError_t e = hipSetDevice(h->device);
   // An event costs its stream 4 us on the GPU, in which neither the stream nor a consumer that waits for it gets on:
   // 130 us for the 32 images of a request.  Tokens that are there already need none.
-  if (e == hipSuccess && !r.busy) r.busy = !finished((hipStream_t)stream);
-  if (e == hipSuccess && r.busy) {
+  const bool busy = r.busy || (e == hipSuccess && !finished((hipStream_t)stream, h->device));
+  if (e == hipSuccess && busy) {
     e = hipEventCreateWithFlags(&p.ready, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventRecord(p.ready, (hipStream_t)stream);
   }
@@ -185,6 +196,7 @@ vit_status_t vit_handoff_publish(vit_handoff_t* h, int64_t request_id, int32_t i
     p.ready = nullptr;
     return set_error(VIT_EDEVICE, "vit_handoff_publish: %s", hipGetErrorString(e));
   }
+  r.busy = busy;
   p.ptr = tokens;
   p.bytes = bytes;
   p.published = true;
@@ -216,15 +228,9 @@ vit_status_t vit_handoff_pull(vit_handoff_t* h, int64_t request_id, void* dst, s
   hipError_t e = hipSetDevice(h->device);
   for (size_t i = 0; i < r.pieces.size() && e == hipSuccess; ++i)
     if (r.pieces[i].ready) e = hipStreamWaitEvent(s, r.pieces[i].ready, 0);
-  hipDevice_t stream_dev = -1;
   uintptr_t base = 0;
   size_t size = 0;
-  bool gather = e == hipSuccess;
-  if (gather && s && s != hipStreamPerThread && s != hipStreamLegacy) {
-    gather = hipStreamGetDevice(s, &stream_dev) == hipSuccess && (int)stream_dev == h->device;
-    if (!gather) (void)hipGetLastError();
-  }
-  gather = gather && on_device(dst, r.total, h->device, base, size);
+  const bool gather = e == hipSuccess && stream_of(s, h->device) && on_device(dst, r.total, h->device, base, size);
   base = size = 0;
   GatherArgs g;
   g.n = 0;

@@ -1,0 +1,105 @@
+"""The hand-off table's host side, built against a small HIP runtime on the host (tests/host_hip): what its calls accept, what
+they wait for and where the bytes arrive, with two devices and with producers that finish when the test says so."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CLANG = os.environ.get("HOST_CLANG", "/opt/rocm/llvm/bin/clang++")  # the kernel's vector types are clang's
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("handoff") / "libhandoff_host.so")
+    subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O2", "-fPIC", "-shared", "-I", os.path.join(HERE, "host_hip"),
+                    os.path.join(HERE, "host_hip", "handoff_host.cpp"), "-o", so], check=True)
+    lib = C.CDLL(so)
+    lib.host_alloc.restype = lib.host_stream.restype = C.c_void_p
+    lib.host_alloc.argtypes = [C.c_int, C.c_size_t]
+    lib.host_work.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_size_t]
+    lib.host_capture.argtypes = [C.c_void_p, C.c_int]
+    lib.host_captured.argtypes = [C.c_void_p, C.POINTER(C.c_int)]
+    lib.host_error.restype = C.c_char_p
+    lib.vit_handoff_create.argtypes = [C.c_int, C.POINTER(C.c_void_p)]
+    lib.vit_handoff_destroy.argtypes = [C.c_void_p]
+    lib.vit_handoff_expect.argtypes = [C.c_void_p, C.c_int64, C.c_int32]
+    lib.vit_handoff_publish.argtypes = [C.c_void_p, C.c_int64, C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p]
+    lib.vit_handoff_pull.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_size_t, C.c_void_p, C.POINTER(C.c_size_t)]
+    lib.vit_handoff_release.argtypes = [C.c_void_p, C.c_int64]
+    return lib
+
+
+class Table:
+    """A table on device 0, a request of the given images (each filled with its own bytes) and a destination."""
+
+    def __init__(self, lib, sizes, dst_device=0):
+        self.lib, self.sizes = lib, sizes
+        self.h = C.c_void_p()
+        assert lib.vit_handoff_create(0, C.byref(self.h)) == 0
+        assert lib.vit_handoff_expect(self.h, 1, len(sizes)) == 0
+        self.src = [lib.host_alloc(0, n) for n in sizes]
+        self.dst = lib.host_alloc(dst_device, sum(sizes))
+        self.want = np.random.default_rng(len(sizes)).integers(1, 256, sum(sizes), dtype=np.uint8)
+        at = 0
+        for p, n in zip(self.src, sizes):
+            C.memmove(p, self.want[at:].ctypes.data, n)
+            at += n
+
+    def publish(self, i, stream, ptr=None):
+        return self.lib.vit_handoff_publish(self.h, 1, i, ptr or self.src[i], self.sizes[i], stream)
+
+    def pull(self, stream, dst=None):
+        n = C.c_size_t()
+        rc = self.lib.vit_handoff_pull(self.h, 1, dst or self.dst, sum(self.sizes), stream, C.byref(n))
+        assert rc != 0 or n.value == sum(self.sizes)
+        return rc
+
+    def got(self, dst=None):
+        return np.ctypeslib.as_array((C.c_uint8 * sum(self.sizes)).from_address(dst or self.dst)).copy()
+
+    def image(self, i):
+        at = sum(self.sizes[:i])
+        return slice(at, at + self.sizes[i])
+
+    def counts(self):
+        out = (C.c_int * 4)()
+        self.lib.host_counts(out)
+        return dict(zip(("launches", "copies", "waits", "events"), out))
+
+
+CHUNK = 32768
+
+
+@pytest.mark.parametrize("sizes", [[1], [16, 17, CHUNK - 16, CHUNK, CHUNK + 16, 3 * CHUNK - 1, 15], [64] * 128, [64] * 129])
+def test_every_byte_arrives(lib, sizes):
+    t = Table(lib, sizes)
+    t.counts()
+    consumer = lib.host_stream(0, 0)
+    for i in range(len(sizes)):
+        assert t.publish(i, None) == 0
+    assert t.pull(consumer) == 0
+    lib.host_pump()
+    assert np.array_equal(t.got(), t.want)
+    if len(set(sizes)) == 1 and len(sizes) > 1:
+        c = t.counts()
+        assert (c["launches"], c["copies"]) == (-(-len(sizes) // 128), 0)
+    lib.vit_handoff_destroy(t.h)
+
+
+@pytest.mark.parametrize("busy", [False, True])
+def test_a_stream_of_another_device_is_refused(lib, busy):
+    """The table's events cannot be recorded on it: refused whether or not that stream has work left."""
+    t = Table(lib, [4096])
+    foreign = lib.host_stream(1, 0)
+    if busy:
+        lib.host_work(foreign, lib.host_alloc(1, 64), 1, 64)
+    assert t.publish(0, foreign) == -4, lib.host_error()
+    # nothing of the refused call stays behind: the image can still be published, and its stream is not taken to be at work
+    t.counts()
+    own = lib.host_stream(0, 0)
+    assert t.publish(0, own) == 0
+    assert t.counts()["events"] == 0
+    lib.vit_handoff_destroy(t.h)

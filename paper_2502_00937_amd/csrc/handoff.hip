@@ -59,22 +59,27 @@ bool stream_of(hipStream_t s, int device) {
   return ok;
 }
 
-// Whether everything queued on `s` so far has finished.  A stream that is being captured must not be asked (it has no
-// progress to report, and the question would end the capture); relaxed mode keeps a capture elsewhere out of it.
+// Whether an event recorded on `s` now would be behind nothing.  A stream that is being captured must not be asked (it has
+// no progress to report, and the question would end the capture); relaxed mode keeps a capture elsewhere out of it.
 // A stream of another device never counts as finished, so that it is refused where its event is recorded, at work or not.
+// What a blocking stream is given comes after the null stream's earlier work, of which a query of it says nothing.
 bool finished(hipStream_t s, int device) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  bool idle = false;
   if (!stream_of(s, device)) return false;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  if (hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone) idle = hipStreamQuery(s) == hipSuccess;
-  if (!idle) (void)hipGetLastError();  // "not ready" is an answer
+  auto idle = [](hipStream_t q) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(q, &st) == hipSuccess && st == hipStreamCaptureStatusNone && hipStreamQuery(q) == hipSuccess;
+  };
+  unsigned flags = hipStreamDefault;
+  bool done = idle(s);
+  if (done && s) done = hipStreamGetFlags(s, &flags) == hipSuccess && ((flags & hipStreamNonBlocking) || idle(nullptr));
+  if (!done) (void)hipGetLastError();  // "not ready" is an answer
   (void)hipThreadExchangeStreamCaptureMode(&mode);
-  return idle;
+  return done;
 }
 
 // ---- one launch for the images of a request ------------------------------------------------------

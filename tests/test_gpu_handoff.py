@@ -46,10 +46,10 @@ def test_pull_moves_every_byte(label, sizes, shift):
     h.close()
 
 
-@pytest.mark.parametrize("producer", ["own stream", "null stream behind a blocking stream"])
+@pytest.mark.parametrize("producer", ["own stream", "null stream behind a blocking stream", "blocking stream behind the null stream"])
 def test_pull_waits_for_a_producer_at_work(producer):
     """The tokens are written late: by the publishing stream itself, or by a blocking stream whose work the null stream, which
-    publishes them, comes after."""
+    publishes them, comes after, or the other way round."""
     import ctypes
 
     import torch
@@ -68,12 +68,12 @@ def test_pull_waits_for_a_producer_at_work(producer):
     h = V.TokenHandoff(0)
     for rid in range(3):
         h.expect(rid, 3)
-        with torch.cuda.stream(work):
+        with torch.cuda.stream(torch.cuda.default_stream() if producer.startswith("blocking") else work):
             torch.cuda._sleep(20_000_000)  # some milliseconds
             for i, t in enumerate(tokens):
                 t.fill_(10 * rid + i + 1)
         for i, t in enumerate(tokens):
-            h.publish(rid, i, t.data_ptr(), t.numel(), work.cuda_stream if producer == "own stream" else 0)
+            h.publish(rid, i, t.data_ptr(), t.numel(), 0 if producer.startswith("null") else work.cuda_stream)
         h.pull(rid, dst.data_ptr(), dst.numel(), consumer.cuda_stream)
         consumer.synchronize()
         got = dst.view(3, -1).cpu()

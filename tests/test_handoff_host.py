@@ -103,3 +103,29 @@ def test_a_stream_of_another_device_is_refused(lib, busy):
     assert t.publish(0, own) == 0
     assert t.counts()["events"] == 0
     lib.vit_handoff_destroy(t.h)
+
+
+def test_a_blocking_stream_behind_the_null_stream_is_waited_for(lib):
+    """An event recorded on an idle blocking stream comes after the work that the null stream was given before it; a query
+    of that stream says that it is idle."""
+    t = Table(lib, [4096])
+    blocking, consumer = lib.host_stream(0, 1), lib.host_stream(0, 0)
+    late = lib.host_work(None, t.src[0], 7, 4096)  # the tokens are still being written, on the null stream
+    assert t.publish(0, blocking) == 0
+    assert t.pull(consumer) == 0
+    lib.host_pump()
+    assert not t.got().any()
+    lib.host_end_work(late)
+    assert (t.got() == 7).all()
+    lib.vit_handoff_destroy(t.h)
+
+
+def test_a_stream_that_waits_for_nobody_needs_no_event(lib):
+    """A non-blocking stream does not come after the null stream: idle is idle."""
+    t = Table(lib, [4096])
+    late = lib.host_work(None, lib.host_alloc(0, 64), 7, 64)
+    t.counts()
+    assert t.publish(0, lib.host_stream(0, 0)) == 0
+    assert t.counts()["events"] == 0
+    lib.host_end_work(late)
+    lib.vit_handoff_destroy(t.h)

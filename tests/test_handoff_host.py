@@ -129,3 +129,35 @@ def test_a_stream_that_waits_for_nobody_needs_no_event(lib):
     assert t.counts()["events"] == 0
     lib.host_end_work(late)
     lib.vit_handoff_destroy(t.h)
+
+
+@pytest.mark.parametrize("shift", [2 * CHUNK, 3 * CHUNK, 5 * CHUNK])
+def test_a_destination_over_the_sources_is_filled_in_image_order(lib, shift):
+    """A request closed up towards the front of its own buffer: an image's place may be where an earlier image lay, which has
+    been moved by then."""
+    sizes = [2 * CHUNK] * 4
+    t = Table(lib, sizes)
+    step = 2 * CHUNK + shift
+    buf = lib.host_alloc(0, shift + 4 * step)
+    consumer = lib.host_stream(0, 0)
+    for i in range(4):
+        C.memmove(buf + shift + i * step, t.src[i], sizes[i])
+        assert t.publish(i, None, buf + shift + i * step) == 0
+    assert t.pull(consumer, buf) == 0
+    lib.host_pump()
+    assert np.array_equal(t.got(buf), t.want)
+    lib.vit_handoff_destroy(t.h)
+
+
+def test_tokens_already_in_place_are_gathered(lib):
+    """A source that is its own destination meets nobody else's."""
+    t = Table(lib, [2 * CHUNK] * 4)
+    C.memmove(t.dst, t.want.ctypes.data, t.want.size)
+    at = [t.dst + 2 * CHUNK * i for i in range(4)]
+    t.counts()
+    for i in range(4):
+        assert t.publish(i, None, at[i] if i % 2 else None) == 0
+    assert t.pull(lib.host_stream(0, 0)) == 0
+    lib.host_pump()
+    assert np.array_equal(t.got(), t.want) and t.counts()["copies"] == 0
+    lib.vit_handoff_destroy(t.h)

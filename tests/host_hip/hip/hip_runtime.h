@@ -4,8 +4,8 @@
 //
 // What is modelled: an event is the end of its last recording; the null stream and the blocking streams of a device come
 // after one another as they were queued; a query answers for the operations of that stream alone; an event belongs
-// to the device it was created on and only that device's streams take its recording; asking a stream under capture, or
-// anything while a capture in global mode is on and the thread has not said relaxed, ends the capture.
+// to the device it was created on and only that device's streams take its recording; asking a stream under capture or an
+// event recorded in it, or anything while a capture in global mode is on and the thread has not said relaxed, ends the capture.
 // Workgroups run in descending order: a launch promises none.
 #pragma once
 #include <cstddef>
@@ -46,7 +46,7 @@ struct Stream {
   std::deque<Op> ops;
   int recorded = 0;  // operations that went into a capture
 };
-struct Event { int device = 0; Done done; };
+struct Event { int device = 0; Done done; Stream* captured = nullptr; };
 struct Block { size_t bytes; int device; };
 
 constexpr int kDevices = 2;
@@ -136,7 +136,7 @@ inline hipError_t hipSetDevice(int d) {
   return hipSuccess;
 }
 inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
-  *e = new host_hip::Event{host_hip::device, nullptr};
+  *e = new host_hip::Event{host_hip::device};
   host_hip::live_events += 1;
   return hipSuccess;
 }
@@ -150,11 +150,12 @@ inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t stream) {
   if (s->device != e->device) return hipErrorInvalidHandle;
   auto done = std::make_shared<bool>(false);
   host_hip::enqueue(s, nullptr, {}, done);
-  e->done = s->capture == hipStreamCaptureStatusNone ? done : nullptr;
+  e->captured = s->capture == hipStreamCaptureStatusNone ? nullptr : s;
+  e->done = e->captured ? nullptr : done;
   return hipSuccess;
 }
 inline hipError_t hipEventQuery(hipEvent_t e) {
-  if (host_hip::breaks_capture(nullptr)) return hipErrorStreamCaptureUnsupported;
+  if (host_hip::breaks_capture(e->captured)) return hipErrorStreamCaptureUnsupported;
   host_hip::pump();
   return !e->done || *e->done ? hipSuccess : hipErrorNotReady;
 }

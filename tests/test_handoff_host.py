@@ -161,3 +161,69 @@ def test_tokens_already_in_place_are_gathered(lib):
     lib.host_pump()
     assert np.array_equal(t.got(), t.want) and t.counts()["copies"] == 0
     lib.vit_handoff_destroy(t.h)
+
+
+@pytest.mark.parametrize("earlier", ["finished before", "own launch before"])
+def test_finished_images_do_not_wait_for_the_last_one(lib, earlier):
+    """All but the last image are there when the consumer pulls, or come from an earlier launch: they are moved while the
+    last one is still being made."""
+    n, size = 10, 5 * (1 << 20)
+    t = Table(lib, [size] * n)
+    producer, consumer = lib.host_stream(0, 0), lib.host_stream(0, 0)
+    scratch = lib.host_alloc(0, 64)
+    first = lib.host_work(producer, scratch, 1, 64) if earlier == "own launch before" else None
+    for i in range(n - 1):
+        assert t.publish(i, producer) == 0
+    last = lib.host_work(producer, t.src[n - 1], 7, size)
+    assert t.publish(n - 1, producer) == 0
+    t.counts()
+    assert t.pull(consumer) == 0
+    assert t.counts()["launches"] < n  # not one launch per image
+    lib.host_pump()
+    if first is not None:
+        assert not t.got().any()
+        lib.host_end_work(first)
+    got = t.got()
+    there = [np.array_equal(got[t.image(i)], t.want[t.image(i)]) for i in range(n - 1)]
+    assert sum(there) >= n - 1 - (3 if first is not None else 0), there  # images of an unfinished event go in groups
+    assert not got[t.image(n - 1)].any()
+    lib.host_end_work(last)
+    got = t.got()
+    assert np.array_equal(got[:-size], t.want[:-size]) and (got[-size:] == 7).all()
+    lib.vit_handoff_destroy(t.h)
+
+
+@pytest.mark.parametrize("order", ["idle first", "at work first"])
+def test_idle_and_busy_publishes_in_one_request(lib, order):
+    t = Table(lib, [CHUNK + 16] * 3)
+    idle, producer, consumer = lib.host_stream(0, 0), lib.host_stream(0, 0), lib.host_stream(0, 0)
+    late = lib.host_work(producer, t.src[1], 9, CHUNK + 16)
+    for i, s in ((0, idle), (1, producer), (2, idle)) if order == "idle first" else ((1, producer), (0, idle), (2, idle)):
+        assert t.publish(i, s) == 0
+    assert t.pull(consumer) == 0
+    lib.host_pump()
+    assert not t.got()[t.image(1)].any()
+    lib.host_end_work(late)
+    got = t.got()
+    assert (got[t.image(1)] == 9).all() and all(np.array_equal(got[t.image(i)], t.want[t.image(i)]) for i in (0, 2))
+    lib.vit_handoff_destroy(t.h)
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("who", ["producer", "consumer", "another"])
+def test_a_capture_lives_through_publish_and_pull(lib, who, mode):
+    """Neither call asks a question that would end a capture, of the producer's stream, the consumer's or a third one."""
+    t = Table(lib, [4096] * 3)
+    s = {k: lib.host_stream(0, 0) for k in ("producer", "consumer", "another", "busy")}
+    late = lib.host_work(s["busy"], t.src[2], 5, 4096)
+    lib.host_capture(s[who], mode)
+    assert [t.publish(0, s["producer"]), t.publish(1, s["producer"]), t.publish(2, s["busy"])] == [0, 0, 0]
+    assert t.pull(s["consumer"]) == 0
+    recorded = C.c_int()
+    assert lib.host_captured(s[who], C.byref(recorded)) == 1
+    assert (recorded.value > 0) == (who != "another")
+    lib.host_capture(s[who], -1)
+    lib.host_end_work(late)
+    if who != "consumer":
+        assert (t.got()[t.image(2)] == 5).all()
+    lib.vit_handoff_destroy(t.h)

@@ -183,6 +183,7 @@ def vit_encode_packed_static(handle: int, pixels_ptr: int, images_per_request, t
 def _floats(values, n: int):
     """n host floats for the C side.  Two ctypes arrays cost a preprocessing call 3.5 us of its 10, packed bytes less
     than 1; the array still takes what packing refuses (another count, values that are not numbers yet)."""
+    values = tuple(values)  # an iterator can be read once only
     try:
         return struct.pack("%df" % n, *values)
     except (struct.error, OverflowError, TypeError):

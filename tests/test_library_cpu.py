@@ -2,6 +2,7 @@
 pure-host entry points behave.  No kernel is launched."""
 import os
 import re
+import struct
 
 import numpy as np
 import pytest
@@ -215,3 +216,16 @@ def test_handoff_table_logic_without_a_device():
     with pytest.raises(V.VitError):
         h.release(7)
     h.close()
+
+
+def test_preprocess_reads_mean_and_std_once():
+    """mean and std may be any iterable of what float() takes, an iterator among them: read once, whole or not at all."""
+    from paper_2502_00937_amd.binding import _floats
+
+    want = struct.pack("3f", 0.25, 0.5, 0.75)
+    for values in ([0.25, 0.5, 0.75], iter([0.25, 0.5, 0.75]), iter(["0.25", "0.5", "0.75"]), (v for v in np.float32([0.25, 0.5, 0.75])),
+                   iter([0.25, "0.5", 0.75])):
+        assert bytes(_floats(values, 3)) == want
+    assert bytes(_floats(iter([1e39, 0.5, 0.75]), 3)) == struct.pack("3f", float("inf"), 0.5, 0.75)
+    with pytest.raises(IndexError):
+        _floats(iter([0.25, 0.5, 0.75, 1.0]), 3)

@@ -194,9 +194,11 @@ def vit_preprocess_tiles(image_ptr: int, height: int, width: int, channels: int,
                          grid_cols: int, thumbnail: bool, mean, std, out_ptr: int, out_capacity_bytes: int,
                          stream: int = 0) -> None:
     """Raw pointers in, nothing returned: resize + rescale + normalise + tile on the current device."""
-    _check(load_library().vit_preprocess_tiles(image_ptr, height, width, channels, tile_size, grid_rows, grid_cols,
-                                               1 if thumbnail else 0, _floats(mean, channels), _floats(std, channels),
-                                               out_ptr, out_capacity_bytes, stream))
+    # c_void_p takes integers only; as an argument type it would take the address of a bytes object or a text, too
+    _check(load_library().vit_preprocess_tiles(C.c_void_p(image_ptr), height, width, channels, tile_size, grid_rows,
+                                               grid_cols, 1 if thumbnail else 0, _floats(mean, channels),
+                                               _floats(std, channels), C.c_void_p(out_ptr), out_capacity_bytes,
+                                               C.c_void_p(stream)))
 
 
 def preprocess_tiles(image, tile_size: int, grid_rows: int, grid_cols: int, thumbnail: bool, mean, std, out=None):

@@ -229,3 +229,13 @@ def test_preprocess_reads_mean_and_std_once():
     assert bytes(_floats(iter([1e39, 0.5, 0.75]), 3)) == struct.pack("3f", float("inf"), 0.5, 0.75)
     with pytest.raises(IndexError):
         _floats(iter([0.25, 0.5, 0.75, 1.0]), 3)
+
+
+@pytest.mark.parametrize("which", ["image", "out", "stream"])
+@pytest.mark.parametrize("value", [b"\0" * 192, "text", np.zeros(4).ctypes])
+def test_preprocess_takes_pointers_as_integers(which, value):
+    """Host objects are no device pointers: refused before the library sees an address of theirs."""
+    ptr = {"image": 4096, "out": 4096, "stream": 0}
+    ptr[which] = value
+    with pytest.raises(TypeError):
+        V.vit_preprocess_tiles(ptr["image"], 8, 8, 3, 4, 1, 1, False, [0.5] * 3, [0.2] * 3, ptr["out"], 0, ptr["stream"])

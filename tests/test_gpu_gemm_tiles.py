@@ -28,3 +28,20 @@ def test_tokens_do_not_depend_on_the_tile(n):
         assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
     want, _ = O.vit_oracle_encode(CFG, w, px[-1:], [1], one)
     assert_parity(whole[-T:], want, "bf16", f"tiles n={n}")
+
+
+@pytest.mark.parametrize("n", [30, 33, 37])
+def test_rows_alone_cut_over_the_xcds(n):
+    """Five tile columns: only the rows are dealt over the XCDs, and the last one has 4, 4 and 3 of the others' 7, 8 and 9
+    row blocks of 128."""
+    cfg = dict(CFG, hidden=576, heads=9, mlp=1160, layers_local=1)
+    say(f"case matrix-product tiles, {n} images of 226 tokens, width 576")
+    w, px = gen.make_weights(cfg, seed=4), gen.make_pixels(cfg, n, seed=n)
+    whole, _ = gpu_encode(cfg, w, px, [n], np.arange(n + 1, dtype=np.int32))
+    T = gen.tokens_per_tile(cfg)
+    one = np.array([0, 1], dtype=np.int32)
+    for i in (0, n // 2, n - 1):
+        alone, _ = gpu_encode(cfg, w, px[i:i + 1], [1], one)
+        assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
+    want, _ = O.vit_oracle_encode(cfg, w, px[-1:], [1], one)
+    assert_parity(whole[-T:], want, "bf16", f"row cut n={n}")

@@ -232,7 +232,7 @@ def test_preprocess_reads_mean_and_std_once():
 
 
 @pytest.mark.parametrize("which", ["image", "out", "stream"])
-@pytest.mark.parametrize("value", [b"\0" * 192, "text", np.zeros(4).ctypes])
+@pytest.mark.parametrize("value", [b"\0" * 192, "text", np.zeros(4).ctypes], ids=["bytes", "text", "array"])
 def test_preprocess_takes_pointers_as_integers(which, value):
     """Host objects are no device pointers: refused before the library sees an address of theirs."""
     ptr = {"image": 4096, "out": 4096, "stream": 0}

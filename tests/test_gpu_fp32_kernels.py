@@ -1,7 +1,9 @@
 """The fp32 mode's matrix product and attention at the sizes where their tiles end: segments around one 32-key block, one
 round of the four waves (128 keys) and a remainder, every head width the kernel is built for, and both tile sizes.
 
-Tolerance: the fp32 bar of the parity tests; the mode's own error against 64 bits at these depths is below 1e-6."""
+Tolerance: the fp32 bar of the parity tests allows for a dozen layers.  Two blocks round about fourteen times in a row (twice
+LayerNorm, four products, attention), each time by a few units of 2^-24 = 6e-8 of the token's largest value, which add up
+like random steps: 6e-8 x 3 x sqrt(14) = 7e-7.  Measured 3.7e-7 to 6.4e-7; the bar is four times the largest."""
 import numpy as np
 import pytest
 
@@ -11,6 +13,8 @@ from parity_util import assert_parity, say
 from test_gpu_parity import gpu_encode
 
 pytestmark = pytest.mark.gpu
+
+REL = 2.6e-6
 
 
 def _cfg(**kw):
@@ -35,19 +39,20 @@ def test_segment_lengths_and_head_dims(dh, heads, grid, has_cls, tiles):
     w, px = gen.make_weights(cfg, seed=dh), gen.make_pixels(cfg, int(to[-1]), seed=grid)
     got, _ = gpu_encode(cfg, w, px, [len(tiles)], to)
     want, _ = O.vit_oracle_encode(cfg, w, px, [len(tiles)], to)
-    assert_parity(got, want, "fp32", f"fp32 dh{dh}")
+    assert assert_parity(got, want, "fp32", f"fp32 dh{dh}")[0] <= REL
 
 
 def test_tile_sizes_give_the_same_bits():
-    """An image alone takes the 32 x 32 tiles in every product; 84 of them (5460 rows) take 64 x 64 in all but one."""
+    """An image alone takes the 32 x 32 tiles in every product; 86 of them (5590 rows, 5504 of patches) take 64 x 64 in all but
+    the projector (352 tiles; the line is at 512)."""
     cfg = _cfg(image_size=32, hidden=384, heads=6, mlp=520, proj_layers=1, proj_dims=(200,))
     say("case fp32 tile sizes")
-    n = 84
+    n = 86
     w, px = gen.make_weights(cfg, seed=1), gen.make_pixels(cfg, n, seed=2)
     whole, _ = gpu_encode(cfg, w, px, [n], np.arange(n + 1, dtype=np.int32))
     T = gen.tokens_per_tile(cfg)
-    for i in (0, 41, n - 1):
+    for i in (0, 43, n - 1):
         alone, _ = gpu_encode(cfg, w, px[i:i + 1], [1], np.array([0, 1], dtype=np.int32))
         assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
     want, _ = O.vit_oracle_encode(cfg, w, px[-2:], [2], np.arange(3, dtype=np.int32))
-    assert_parity(whole[-2 * T:], want, "fp32", "fp32 large tiles")
+    assert assert_parity(whole[-2 * T:], want, "fp32", "fp32 large tiles")[0] <= REL

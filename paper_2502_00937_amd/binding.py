@@ -194,11 +194,13 @@ def vit_preprocess_tiles(image_ptr: int, height: int, width: int, channels: int,
                          grid_cols: int, thumbnail: bool, mean, std, out_ptr: int, out_capacity_bytes: int,
                          stream: int = 0) -> None:
     """Raw pointers in, nothing returned: resize + rescale + normalise + tile on the current device."""
-    # c_void_p takes integers only; as an argument type it would take the address of a bytes object or a text, too
-    _check(load_library().vit_preprocess_tiles(C.c_void_p(image_ptr), height, width, channels, tile_size, grid_rows,
-                                               grid_cols, 1 if thumbnail else 0, _floats(mean, channels),
-                                               _floats(std, channels), C.c_void_p(out_ptr), out_capacity_bytes,
-                                               C.c_void_p(stream)))
+    # As an argument type c_void_p takes the address of a bytes object or a text, too; called, it refuses them.  Three calls
+    # cost the caller 0.5 us, a look at the types 0.1.
+    if not (type(image_ptr) is type(out_ptr) is type(stream) is int):
+        image_ptr, out_ptr, stream = C.c_void_p(image_ptr), C.c_void_p(out_ptr), C.c_void_p(stream)
+    _check(load_library().vit_preprocess_tiles(image_ptr, height, width, channels, tile_size, grid_rows, grid_cols,
+                                               1 if thumbnail else 0, _floats(mean, channels), _floats(std, channels),
+                                               out_ptr, out_capacity_bytes, stream))
 
 
 def preprocess_tiles(image, tile_size: int, grid_rows: int, grid_cols: int, thumbnail: bool, mean, std, out=None):

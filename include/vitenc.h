@@ -241,15 +241,19 @@ vit_status_t vit_profile_tiles_read(vit_encoder_t* enc, double* main_loop_us, do
  *   vit_handoff_publish  image `image_index` of the request lies at `tokens` (device memory,
  *                        `bytes` > 0 long) once the work queued so far on `stream` (hipStream_t;
  *                        NULL = null stream) has finished: an event is recorded there
- *                        unless the stream has nothing left to do.  The
- *                        memory stays the producer's; it must stay valid and unchanged until
- *                        vit_handoff_release and until any pull that was queued has run.
+ *                        unless it would be behind nothing (a stream with nothing left to do; for
+ *                        one that is not hipStreamNonBlocking, the null stream neither).  A stream
+ *                        of another device is refused.  The memory stays the producer's; it must
+ *                        stay valid and unchanged until vit_handoff_release and until any pull that
+ *                        was queued has run.
  *   vit_handoff_complete 1 when every image has been published (device work may still be in
  *                        flight), else 0; writes the byte total so far to *total_bytes if not NULL.
- *   vit_handoff_pull     queues on `stream` the copies of all images' tokens, in image order,
- *                        packed back to back into `dst` (device, `capacity` bytes), each behind
- *                        its producer's event; the host does not wait.  *bytes (may be NULL)
- *                        receives the total.  VIT_ENOTREADY if an image is missing,
+ *   vit_handoff_pull     queues on `stream` the move of all images' tokens, packed back to back in
+ *                        image order into `dst` (device, `capacity` bytes), each behind its
+ *                        producer's event; the host does not wait.  What has finished is moved
+ *                        first; if `dst` overlaps a source other than in that image's own place,
+ *                        the images are moved one after the other in image order.  *bytes (may be
+ *                        NULL) receives the total.  VIT_ENOTREADY if an image is missing,
  *                        VIT_ECAPACITY if dst is too small; nothing is queued then.
  *   vit_handoff_release  forgets the request and destroys its events.
  * Errors: VIT_EINVAL for NULL / unknown request / index out of range / duplicate publish or

@@ -630,11 +630,13 @@ __global__ __launch_bounds__(512) void gemm_bf16_dma_kernel(const GemmArgs a, in
 // global -> LDS directly into a ring of NS 64-wide k-stages.  One wait + barrier per stage establishes that the
 // stage has landed for every wave and that the slot refilled next is dead; all fragments of a stage are read
 // before its MFMAs start.
-// What bounds it is the rate at which one compute unit gets operands: 45 to 70 GB/s whatever the tile, the depth of
-// the ring or the number of waves.  With every MFMA left out a single image's products take the same time to 1 %, with
-// every fragment read left out likewise, and without the loads half of it (24 of 45 us, fc2 on 128 x 128 tiles);
-// fragments read one stage ahead, between the MFMAs, gain 1 to 5 %.  So the tile is chosen for the number of units
-// that it keeps loading, and the cut over the XCDs for how often an XCD finds its operands in its own L2.
+// What bounds it is time in which nothing is saturated: at one image (577 rows) the matrix cores are busy 4 to 16 % of a
+// layer's launches and the load-address units 21 to 36 %, at eight 20 to 36 and 38 to 58 %, while the waves wait for 34 to
+// 64 % of their cycles; 7 to 8 of 10 requests hit the L2, and one takes 340 to 540 clocks.  Of a 64 x 64 launch of 577 rows
+// 0.22 us belong to each k-stage and 5 us to none (out-proj, 16 stages, 8.7 us; fc2, 64 stages, 19.1): start, first
+// loads, epilogue.  A unit gets 23 to 55 GB/s of operands there, 27 to 49 at eight images, start and epilogue counted,
+// so the tile is chosen for the number of units that it keeps loading, and the cut over the XCDs for how often an XCD
+// finds its operands in its own L2.
 // A token's k-steps are added in the same order in every variant.
 template <int EPI, int NS, int BM, int BN>
 __global__ __launch_bounds__(BN * 4) void gemm_bf16_ring_kernel(const GemmArgs a, int tiles_m, int tiles_n, int split_n,

@@ -1,13 +1,13 @@
 // Pull-style hand-off of finished image tokens (paper Sec. 4.3, "Image Token Transfer").
 //
 // A producer (an encoder launch) publishes where the tokens of one image of a request lie in device
-// memory and, unless its stream has nothing left to do, records an event there; nothing is copied then.
+// memory and, unless it would be behind nothing, records an event on its stream; nothing is copied then.
 // When every image of the request has been published the consumer, which by now knows where the request
-// will run, pulls:
-// the copies of all images are queued on the consumer's stream behind the producers' events
+// will run, pulls: the images are moved on the consumer's stream behind the producers' events
 // (many-to-one aggregation, transfer deferred until the request is complete).  Images that lie on the
-// table's GPU are gathered by one kernel; anything else (another GPU's memory, pinned host memory,
-// pieces that do not meet 16-byte alignment) is a copy of its own.
+// table's GPU are gathered by one kernel, or a few if some are not finished yet; anything else (another
+// GPU's memory, pinned host memory, pieces that do not meet 16-byte alignment, a destination that overlaps
+// the sources) is a copy of its own.
 // No arithmetic of the encoder happens here.
 #include "../../include/vitenc.h"
 
@@ -100,8 +100,10 @@ bool finished(hipStream_t s, int device) {
 // Bound by HBM: every byte is read and written once.  A copy of its own per image costs the stream 6 us between the
 // copies on top of 3.9 us for an image of 4.7 MB, and one such copy is too short to reach the memory's rate.
 // The images are moved in no order, so none may lie where another one is to go (meets_destination).
-// Measured with 32 images of 577 x 4096 bf16 tokens (302 MB moved): 61 us a hand-off (4.9 TB/s), 74 without the
-// non-temporal hints, 270 with a copy and an event per image; three images of 1280 x 6144 20, 27 and 45 us.
+// Measured with 32 images of 577 x 4096 bf16 tokens that were finished (302 MB moved), handed off again and again: 50 us,
+// of which the kernel 49 (6.1 TB/s; a large copy reaches 4.9, but of these 302 MB part stays in the 256 MB memory-side
+// cache).  With a copy and an event per image 270 to 287; the gather brought 245 with an event per image, the
+// events' absence 79 and the non-temporal hints 61 on the machine of that day.
 // A workgroup moves one 32 KiB chunk, eight 16-byte loads in flight per lane; the table of images travels as the
 // kernel's argument (no staging buffer), so that a launch holds at most kGatherPieces of them.
 typedef uint32_t chunk_t __attribute__((ext_vector_type(4)));

@@ -264,9 +264,13 @@ hipError_t launch_patch_gather(const float* pixels, void* patches, int ld, int n
   const size_t es = out_bf16 ? 2 : 4, strip_bytes = (size_t)g * Kpad * es;
   if (S % 4 == 0 && (Kpad * es) % 16 == 0 && ((size_t)ld * es) % 16 == 0 && strip_bytes <= 64 * 1024 &&
       (long)n_tiles * g <= 0x7fffffffL) {
-    // A strip is a chain of loads per wave, 42 image rows dealt over the workgroup's waves: with no more strips than units
-    // nothing else hides their latency, and sixteen waves make the chain four times shorter (gather and CLS rows of one
-    // 336-pixel image 24 us with four waves, 15 with eight, 11 with sixteen; of 150, 3600 strips, 79, 67 and 80).
+    // A strip is a chain of loads per wave, its image rows (42 for 14-pixel patches) dealt over the workgroup's waves.
+    // Two workgroups of sixteen waves fill a unit: up to 512 strips are one round of 256 units, in which nothing else hides
+    // the chain's latency and sixteen waves make it shortest; the 513th starts a second round.  In us with four,
+    // eight and sixteen waves: 336-pixel tiles, 24 strips 17.1, 10.5, 7.2; 504 strips 19.8, 14.1, 11.8; 528 strips 22.2,
+    // 16.1, 17.3; 3600 strips 76, 67, 71; 384-pixel tiles, 378 strips 20.0, 14.0, 11.7; 513 strips 22.0, 15.9, 19.1.  Beyond
+    // that neither eight nor sixteen lead throughout (560-pixel tiles, 640 strips 25.0 and 25.2, 1000 41 and 35, 2080 68
+    // and 69; 384-pixel tiles, 1539 strips 35 and 39).
     const bool wide = (long)n_tiles * g <= 512;
     const dim3 sgrid((unsigned)(n_tiles * g));
 #define VIT_LAUNCH(T, NT)                                                                                              \

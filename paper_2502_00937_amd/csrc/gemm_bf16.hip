@@ -5,10 +5,11 @@
 //
 // Two kernels share the fragment layout and the epilogues; both move their operands global -> LDS
 // directly (global_load_lds_dwordx4) and are described where they are defined:
-// * gemm_bf16_ring_kernel (below 384 tiles of 256 x 256, and short last rounds of the large kernel): one 128 x 128,
-//   64 x 128 or 64 x 64 tile per workgroup, a ring of four (or two) 64-wide k-stages;
-// * gemm_bf16_dma_kernel (everything large): persistent, 256 x 256 tiles, eight waves of 128 x 64,
+// * gemm_bf16_pipe_kernel (most products, and the last rows of the other one's): one tile of 64 to 256 rows by 64 or
+//   128 columns per workgroup, a ring of two to four 64-wide k-stages;
+// * gemm_bf16_dma_kernel (products of many whole rounds of tiles): persistent, 256 x 256 tiles, eight waves of 128 x 64,
 //   two 64-wide k-stages.
+// Which of them, and which tile, a product takes is decided by the time that each is expected to need (launch_gemm_bf16).
 // * LDS tiles are [row][64 bf16] with the 16-byte chunks XOR-swizzled by (row >> 1) & 7:
 //   LDS serves a 16-byte-per-lane read 16 lanes at a time over 64 banks, and this
 //   swizzle makes any 16 consecutive rows of one logical chunk hit 16 distinct bank groups.
@@ -18,6 +19,7 @@
 //   wave through LDS and writes rows back with 16 bytes per lane.
 // * Workgroup ids are dealt round-robin to the 8 XCDs; each XCD walks its own tiles in blocks
 //   so the tiles in flight on one XCD share A and W slices in that XCD's L2.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -27,121 +29,139 @@ namespace vitenc {
 namespace {
 
 constexpr int BK = 64;  // bf16 elements per k-step = 128 bytes = 8 chunks of 16 bytes
-constexpr int GROUP_M = 8;  // row blocks that the small-problem kernel walks together
+constexpr int GROUP_M = 4;  // row blocks that gemm_bf16_pipe_kernel walks together
 
 // Epilogue of one wave.  acc[i][j] is a transposed 32x32 block: the lane holds token row
 // row0 + 32i + (lane & 31); register 4jj + e holds output column ncol0 + 32j + 8jj + 4(lane >> 5) + e.
-// `smem` is free LDS (all waves are past their last tile read); each wave stages its own rows.
-template <int EPI, int FM, int FN>
-__device__ __forceinline__ void wave_epilogue(const GemmArgs& a, f32x16 (&acc)[FM][FN], unsigned char* smem, int row0,
-                                              int ncol0, int wave, int lane) {
-  constexpr int TN = FN * 32;
-  constexpr int STAGE_BF16 = TN * 2 + 16, STAGE_F32 = TN * 4 + 16;  // bytes per staged row (padded)
-  const int lrow = lane & 31, lk = lane >> 5;
-  f32x4 bias[FN][4];
-#pragma unroll
-  for (int j = 0; j < FN; ++j)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) bias[j][jj] = *(const f32x4*)(a.bias + ncol0 + j * 32 + jj * 8 + lk * 4);
+// prefetch() asks ahead of the k-loop for what finish() will need: the bias and, if AHEAD, the residual rows.  Loaded pass by
+// pass behind the k-loop, each behind the store of the pass before it, the residual rows of a launch of one round were
+// a chain of four to sixteen memory latencies: a launch of K = 64 took 3.5, 5.0 and 7.2 us on tiles of 64 x 64, 128 x 128 and
+// 256 x 128, and takes 3.2, 4.5 and 6.3.  Where two workgroups share a unit the other one covers that, and the registers
+// would cost a workgroup its place: there (AHEAD = false) a 32-row block's rows are asked for together in finish().
+// finish() needs free LDS (all waves past their last tile read), in which each wave stages its own rows.
+// Rows and columns past the matrix are read at a valid address and never stored.
+template <int EPI, int FM, int FN, bool AHEAD>
+struct WaveEpilogue {
+  static constexpr bool RESID = EPI == EPI_BIAS_RESIDUAL;
+  static constexpr int TN = FN * 32;
+  static constexpr int LPR = TN / (RESID ? 4 : 8), RPI = 64 / LPR, PASSES = 32 / RPI;  // lanes per staged row (16 bytes each), rows per pass
+  static constexpr int STAGE_ROW = TN * (RESID ? 4 : 2) + 16;                           // bytes per staged row (padded)
+  f32x4 bias[RESID ? 1 : FN][RESID ? 1 : 4];
+  f32x4 x[RESID && AHEAD ? FM : 1][RESID ? PASSES : 1];
 
-  if constexpr (EPI == EPI_PATCH) {
-    // rows are (tile, patch); the residual stream row is tile*T + cls + patch and the position row is added
+  __device__ __forceinline__ void load_rows(const GemmArgs& a, int i, int row0, int col, int lane) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int row = row0 + i * 32 + lrow;
-      if (row >= a.M) continue;
-      const int tile = row / a.patches, tok = a.cls + (row - tile * a.patches);
-      float* xr = a.resid + ((size_t)tile * a.tokens + tok) * a.ldo;
-      const float* pr = a.pos + (size_t)tok * a.ldo;
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const int col = ncol0 + j * 32 + jj * 8 + lk * 4;
-          if (col < a.N) {
-            const f32x4 p = *(const f32x4*)(pr + col);
-            f32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = acc[i][j][jj * 4 + e] + bias[j][jj][e] + p[e];
-            *(f32x4*)(xr + col) = v;
-          }
-        }
-    }
-  } else if constexpr (EPI == EPI_BIAS_RESIDUAL) {
-    unsigned char* st = smem + wave * 32 * STAGE_F32;  // this wave's private staging rows
-    constexpr int LPR = TN / 4;                        // lanes per staged row (16 bytes each)
-    constexpr int RPI = 64 / LPR;                      // rows per pass
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          f32x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[i][j][jj * 4 + e] + bias[j][jj][e];
-          *(f32x4*)(st + lrow * STAGE_F32 + (j * 32 + jj * 8 + lk * 4) * 4) = v;
-        }
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int p = 0; p < 32 / RPI; ++p) {
-        const int sr = p * RPI + lane / LPR, sc = (lane % LPR) * 4;
-        const int row = row0 + i * 32 + sr, col = ncol0 + sc;
-        const f32x4 v = *(const f32x4*)(st + sr * STAGE_F32 + sc * 4);
-        if (row < a.M && col < a.N) {
-          float* xp = a.resid + (size_t)row * a.ldo + col;
-          f32x4 x = *(const f32x4*)xp;
-          x += v;
-          *(f32x4*)xp = x;
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
-  } else {  // EPI_BIAS, EPI_BIAS_GELU: bf16 output
-    float cs[FN][4];  // scale of each accumulator quad: the query columns' (see GemmArgs::q_cols), 1/2 ahead of GELU; the bias is scaled with it
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        cs[j][jj] = EPI == EPI_BIAS_GELU ? 0.5f : ncol0 + j * 32 + jj * 8 + lk * 4 < a.q_cols ? a.q_scale : 1.0f;
-        bias[j][jj] *= cs[j][jj];
-      }
-    unsigned char* st = smem + wave * 32 * STAGE_BF16;
-    constexpr int LPR = TN / 8;  // lanes per staged row (16 bytes = 8 bf16 each)
-    constexpr int RPI = 64 / LPR;
-    // EPI_BIAS_HEADS: heads of 64 or 128 columns stored one after the other, so the wave's TN columns lie inside
-    // one head: a row stride and the offset of column ncol0, both wave-uniform
-    const int hm_blk = EPI == EPI_BIAS_HEADS ? ncol0 / a.hm_dh : 0;
-    const int rs = EPI == EPI_BIAS_HEADS ? a.hm_dh : a.ldo;
-    const size_t col0_off =
-        EPI == EPI_BIAS_HEADS ? (size_t)hm_blk * a.hm_rows * a.hm_dh + (ncol0 - hm_blk * a.hm_dh) : (size_t)ncol0;
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] = fmaf(acc[i][j][jj * 4 + e], cs[j][jj], bias[j][jj][e]);
-            if constexpr (EPI == EPI_BIAS_GELU) v[e] = gelu_fast_half(v[e]);
-          }
-          const u32x2 pk = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-          *(u32x2*)(st + lrow * STAGE_BF16 + (j * 32 + jj * 8 + lk * 4) * 2) = pk;
-        }
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int p = 0; p < 32 / RPI; ++p) {
-        const int sr = p * RPI + lane / LPR, sc = (lane % LPR) * 8;
-        const int row = row0 + i * 32 + sr, col = ncol0 + sc;
-        const u32x4 v = *(const u32x4*)(st + sr * STAGE_BF16 + sc * 2);
-        if (row < a.M && col < a.N) *(u32x4*)((bf16_t*)a.out + (size_t)row * rs + col0_off + sc) = v;
-      }
-      __builtin_amdgcn_wave_barrier();
+    for (int p = 0; p < PASSES; ++p) {
+      const int row = min(row0 + i * 32 + p * RPI + lane / LPR, a.M - 1);
+      x[AHEAD ? i : 0][p] = *(const f32x4*)(a.resid + (size_t)row * a.ldo + col);
     }
   }
-}
+
+  __device__ __forceinline__ void prefetch(const GemmArgs& a, int row0, int ncol0, int lane) {
+    if constexpr (RESID) {
+      const int col = min(ncol0 + lane % LPR * 4, a.N - 4);
+      bias[0][0] = *(const f32x4*)(a.bias + col);
+      if constexpr (AHEAD)
+#pragma unroll
+        for (int i = 0; i < FM; ++i) load_rows(a, i, row0, col, lane);
+    } else {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) bias[j][jj] = *(const f32x4*)(a.bias + ncol0 + j * 32 + jj * 8 + (lane >> 5) * 4);
+    }
+  }
+
+  __device__ __forceinline__ void finish(const GemmArgs& a, f32x16 (&acc)[FM][FN], unsigned char* smem, int row0, int ncol0,
+                                         int wave, int lane) {
+    const int lrow = lane & 31, lk = lane >> 5;
+    unsigned char* st = smem + wave * 32 * STAGE_ROW;
+    if constexpr (EPI == EPI_PATCH) {
+      // rows are (tile, patch); the residual stream row is tile*T + cls + patch and the position row is added
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        const int row = row0 + i * 32 + lrow;
+        if (row >= a.M) continue;
+        const int tile = row / a.patches, tok = a.cls + (row - tile * a.patches);
+        float* xr = a.resid + ((size_t)tile * a.tokens + tok) * a.ldo;
+        const float* pr = a.pos + (size_t)tok * a.ldo;
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) {
+            const int col = ncol0 + j * 32 + jj * 8 + lk * 4;
+            if (col < a.N) {
+              const f32x4 p = *(const f32x4*)(pr + col);
+              f32x4 v;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = acc[i][j][jj * 4 + e] + bias[j][jj][e] + p[e];
+              *(f32x4*)(xr + col) = v;
+            }
+          }
+      }
+    } else if constexpr (RESID) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        if constexpr (!AHEAD) load_rows(a, i, row0, min(ncol0 + lane % LPR * 4, a.N - 4), lane);
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj)
+            *(f32x4*)(st + lrow * STAGE_ROW + (j * 32 + jj * 8 + lk * 4) * 4) =
+                f32x4{acc[i][j][jj * 4], acc[i][j][jj * 4 + 1], acc[i][j][jj * 4 + 2], acc[i][j][jj * 4 + 3]};
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+          const int sr = p * RPI + lane / LPR, sc = lane % LPR * 4;
+          const int row = row0 + i * 32 + sr, col = ncol0 + sc;
+          const f32x4 v = *(const f32x4*)(st + sr * STAGE_ROW + sc * 4);
+          if (row < a.M && col < a.N) *(f32x4*)(a.resid + (size_t)row * a.ldo + col) = x[AHEAD ? i : 0][p] + (v + bias[0][0]);
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    } else {  // EPI_BIAS, EPI_BIAS_HEADS, EPI_BIAS_GELU: bf16 output
+      float cs[FN][4];  // scale of each accumulator quad: the query columns' (see GemmArgs::q_cols), 1/2 ahead of GELU; the bias is scaled with it
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          cs[j][jj] = EPI == EPI_BIAS_GELU ? 0.5f : ncol0 + j * 32 + jj * 8 + lk * 4 < a.q_cols ? a.q_scale : 1.0f;
+          bias[j][jj] *= cs[j][jj];
+        }
+      // EPI_BIAS_HEADS: heads of 64 or 128 columns stored one after the other, so the wave's TN columns lie inside
+      // one head: a row stride and the offset of column ncol0, both wave-uniform
+      const int hm_blk = EPI == EPI_BIAS_HEADS ? ncol0 / a.hm_dh : 0;
+      const int rs = EPI == EPI_BIAS_HEADS ? a.hm_dh : a.ldo;
+      const size_t col0_off =
+          EPI == EPI_BIAS_HEADS ? (size_t)hm_blk * a.hm_rows * a.hm_dh + (ncol0 - hm_blk * a.hm_dh) : (size_t)ncol0;
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              v[e] = fmaf(acc[i][j][jj * 4 + e], cs[j][jj], bias[j][jj][e]);
+              if constexpr (EPI == EPI_BIAS_GELU) v[e] = gelu_fast_half(v[e]);
+            }
+            const u32x2 pk = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+            *(u32x2*)(st + lrow * STAGE_ROW + (j * 32 + jj * 8 + lk * 4) * 2) = pk;
+          }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+          const int sr = p * RPI + lane / LPR, sc = lane % LPR * 8;
+          const int row = row0 + i * 32 + sr, col = ncol0 + sc;
+          const u32x4 v = *(const u32x4*)(st + sr * STAGE_ROW + sc * 2);
+          if (row < a.M && col < a.N) *(u32x4*)((bf16_t*)a.out + (size_t)row * rs + col0_off + sc) = v;
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  }
+};
 
 // ---------------------------------------------------------------------------------------------
 // Large-problem kernel: persistent, 256 x 256 tile, eight waves (two per SIMD), 128 x 64 per wave.
@@ -625,149 +645,207 @@ __global__ __launch_bounds__(512) void gemm_bf16_dma_kernel(const GemmArgs a, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// Small-problem kernel (fewer than 384 tiles of 256 x 256; also the short last round of a large product that is
-// one column band wide, see launch_gemm_bf16): one BM x BN tile per workgroup, waves of BM/2 x 32, operands
-// global -> LDS directly into a ring of NS 64-wide k-stages.  One wait + barrier per stage establishes that the
-// stage has landed for every wave and that the slot refilled next is dead; all fragments of a stage are read
-// before its MFMAs start.
-// What bounds it is time in which nothing is saturated: at one image (577 rows) the matrix cores are busy 4 to 16 % of a
-// layer's launches and the load-address units 21 to 36 %, at eight 20 to 36 and 38 to 58 %, while the waves wait for 34 to
-// 64 % of their cycles; 7 to 8 of 10 requests hit the L2, and one takes 340 to 540 clocks.  Of a 64 x 64 launch of 577 rows
-// 0.22 us belong to each k-stage and 5 us to none (out-proj, 16 stages, 8.7 us; fc2, 64 stages, 19.1): start, first
-// loads, epilogue.  A unit gets 23 to 55 GB/s of operands there, 27 to 49 at eight images, start and epilogue counted,
-// so the tile is chosen for the number of units that it keeps loading, and the cut over the XCDs for how often an XCD
-// finds its operands in its own L2.
-// A token's k-steps are added in the same order in every variant.
-template <int EPI, int NS, int BM, int BN>
-__global__ __launch_bounds__(BN * 4) void gemm_bf16_ring_kernel(const GemmArgs a, int tiles_m, int tiles_n, int split_n,
-                                                                  int mt, int nt) {
-  constexpr int STAGE = (BM + BN) * D_ROW;
-  constexpr int WN = BN / 32, NW = 2 * WN, TM = BM / 2, FM = TM / 32;  // waves along the columns, in all; a wave's rows
+// One BM x BN tile per workgroup, WM x WN waves of BM/WM x BN/WN, operands global -> LDS directly into a ring of NS 64-wide
+// k-stages.  A stage is multiplied in groups of G 16-wide sub-steps; a group's fragments are read while the group before it
+// is multiplied, into the other of two register sets.  Ahead of a stage's last group one wait + barrier establishes that
+// the next stage has landed for every wave and that nobody reads this one's LDS any more; from there on the loads of the
+// stage that takes its place go out, one after every few MFMAs, for as long as it takes to come round to the next barrier.
+// What bounds it: alone on its unit (few workgroups) a stage takes 1.3 to 1.5 times its MFMAs, or its loads at 64 bytes
+// per clock if those are more (64 x 64: 0.18 us a stage against 0.11); with all units at work the shader clock falls under
+// the power cap (a 256 x 128 stage 0.53 us with 24 workgroups, 0.75 with 224, the same with every operand in the L2).  Its
+// predecessor read all of a stage's fragments and then multiplied, and issued a stage's loads back to back, so that loads,
+// reads and MFMAs added up: fc2 of 577 rows (1024 x 4096, 160 tiles of 64 x 64) 19.2 us, now 14.5; of 1154 rows 26.1 and
+// 19.9; out-proj of 577 rows 7.6 and 6.1.
+// Beyond one round of tiles their height decides: a product of 4616 x 1024 x 4096 took 61 us on tiles of 128 x 128 (296 of
+// them on 256 units) and takes 44 on 200 of 192 x 128.  Hence heights of 64 to 256 rows, chosen by pipe_time below.
+// Tiles are dealt to the XCDs in eight runs of equal length (workgroup id mod 8 = XCD) of an order that walks four row blocks
+// at a time, column by column: an XCD's tiles share A and W rows in its L2, and none has a tile more than another, which
+// the former cut into rectangles could not give (5103 x 1152 x 4352 on tiles of 192 x 128: 85 us so, 54 in runs; groups
+// of eight row blocks are up to 3 % slower).
+// A token's k-steps are added in the same order in every variant, and as in the persistent kernel.
+
+// vmcnt(N) lgkmcnt(0): N of this wave's vector-memory operations may be in flight, none of its LDS operations
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
+}
+
+// n / d and the remainder, both wave-uniform, for 0 <= n < 2^31 and d > 0: a quarter of the instructions of the division
+__device__ __forceinline__ int div_uniform(int n, int d, int& rem) {
+  const float inv = __builtin_amdgcn_rcpf((float)d);
+  int c = (int)((float)n * inv);  // off by at most n / d * 2^-22 + 1
+  rem = n - c * d;
+  const int more = (int)((float)rem * inv);  // by at most 1
+  c += more;
+  rem -= more * d;
+  if (rem < 0) { --c; rem += d; }
+  if (rem >= d) { ++c; rem -= d; }
+  rem = __builtin_amdgcn_readfirstlane(rem);
+  return __builtin_amdgcn_readfirstlane(c);
+}
+
+template <int EPI, int NS, int BM, int BN, int WM, int WN, int G>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_pipe_kernel(const GemmArgs a, int tiles_m, int tiles_n, int n_tiles) {
+  constexpr int STAGE = (BM + BN) * D_ROW, NW = WM * WN, TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32;
   constexpr int LA = BM / 8 / NW, LW = BN / 8 / NW, LOADS = LA + LW;  // direct-to-LDS instructions per wave and stage, 8 rows each
-  static_assert(LW == 2 && (LA == 1 || LA == 2), "tiles of 64 or 128 rows by 128 columns, or of 64 by 64");
-  static_assert(NW * 32 * (32 * 4 + 16) <= NS * STAGE, "epilogue staging must fit in the ring");
+  static_assert(LA * NW * 8 == BM && LW * NW * 8 == BN && FM * 32 * WM == BM && FN * 32 * WN == BN, "whole pieces and blocks");
+  static_assert(256 % BN == 0 && 64 % TN == 0, "W rows are padded to 256; the epilogue's lanes share a row evenly");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
-  // ---- tile assignment: workgroup ids are dealt round-robin to the 8 XCDs; XCD (xr, xc) of the 8 / split_n x split_n
-  //      cut owns mt x nt tiles and walks them in blocks of 8 rows, column by column.  Where only the rows are cut, an XCD
-  //      counts the rows that it has: the last one has fewer, and with empty workgroups between its tiles some of its
-  //      units got a tile more and others one less (8019 x 1152 x 4352, 63 row blocks: 138 us so, 122 counted; 8005 x 1280
-  //      x 5120 162 and 153; out-proj of the same rows 52 and 45, 57 and 52).  In the other cuts counting rows and
-  //      columns changed nothing beyond 1 to 2 %, in either direction: left as they are.
+  // ---- tile assignment: XCD x takes n_tiles / 8 tiles, one more if x < n_tiles % 8
   const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
-  const int xr = xcd / split_n, xc = xcd % split_n;
-  const int rows = split_n == 1 ? min(mt, tiles_m - xr * mt) : mt;
-  const int blk = q / (GROUP_M * nt), rem = q - blk * (GROUP_M * nt), h = min(GROUP_M, rows - blk * GROUP_M);
-  if (h <= 0) return;
-  const int c = rem / h, tile_m = xr * mt + blk * GROUP_M + rem - c * h, tile_n = xc * nt + c;
-  if (c >= nt || tile_m >= tiles_m || tile_n >= tiles_n) return;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int per = n_tiles >> 3, more = n_tiles & 7;
+  if (q >= per + (xcd < more ? 1 : 0)) return;
+  int rem, r;
+  const int group = div_uniform(xcd * per + min(xcd, more) + q, GROUP_M * tiles_n, rem);
+  const int tile_n = div_uniform(rem, min(GROUP_M, tiles_m - group * GROUP_M), r);
+  const int m0 = (group * GROUP_M + r) * BM, n0 = tile_n * BN;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int lrow = lane & 31, lk = lane >> 5;
 
-  // ---- loader: an instruction fills 8 rows of 128 bytes; the chunk that lands in LDS chunk c of row r is
-  //      c ^ ((r >> 1) & 7), which for row 8i + lane / 8 is one of two per-lane offsets, by the parity of i
+  // ---- loader: an instruction fills 8 rows of 128 bytes (a piece); the chunk that lands in LDS chunk c of row r is
+  //      c ^ ((r >> 1) & 7).  Rows of A past the matrix are its last row again: tile heights need not divide the padding.
   const int ld_chunk = (lane & 7) ^ (lane >> 4);
-  const int odd_a = LA == 1 ? 4 * (wave & 1) : 0;  // parity of the wave's first piece of A
-  const uint32_t offA0 = (uint32_t)((lane >> 3) * a.lda + (ld_chunk ^ odd_a) * 8) * 2u;
-  const uint32_t offA1 = (uint32_t)((lane >> 3) * a.lda + (ld_chunk ^ 4) * 8) * 2u;  // of the second, if there are two
-  const uint32_t offW0 = (uint32_t)((lane >> 3) * a.ldw + ld_chunk * 8) * 2u;
-  const uint32_t offW1 = (uint32_t)((lane >> 3) * a.ldw + (ld_chunk ^ 4) * 8) * 2u;
-  const unsigned char* const baseA = (const unsigned char*)a.A + (size_t)(m0 + wave * LA * 8) * a.lda * 2;
-  const unsigned char* const baseW = (const unsigned char*)a.W + (size_t)(n0 + wave * LW * 8) * a.ldw * 2;
-  const size_t a_step = (size_t)16 * a.lda, w_step = (size_t)16 * a.ldw;  // bytes per 8 rows
-  auto dma16 = [&](const unsigned char* gbase, uint32_t goff, unsigned char* lptr) {
-    const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lptr);
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(goff), "s"(gbase)
-                 : "memory", "m0");
+  uint32_t offA[LA], offW[LW];
+#pragma unroll
+  for (int i = 0; i < LA; ++i) {
+    const int p = wave * LA + i;
+    offA[i] = (uint32_t)(min(p * 8 + (lane >> 3), a.M - 1 - m0) * a.lda + (ld_chunk ^ (4 * (p & 1))) * 8) * 2u;
+  }
+#pragma unroll
+  for (int i = 0; i < LW; ++i) {
+    const int p = wave * LW + i;
+    offW[i] = (uint32_t)((p * 8 + (lane >> 3)) * a.ldw + (ld_chunk ^ (4 * (p & 1))) * 8) * 2u;
+  }
+  const unsigned char* const baseA = (const unsigned char*)a.A + (size_t)m0 * a.lda * 2;
+  const unsigned char* const baseW = (const unsigned char*)a.W + (size_t)n0 * a.ldw * 2;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem;  // low 32 bits of a generic LDS pointer = LDS offset
+  auto dma16 = [&](const unsigned char* gbase, uint32_t goff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(goff), "s"(gbase) : "memory", "m0");
   };
-  auto issue_stage = [&](int slot, int kt) {
-    unsigned char* const st = smem + slot * STAGE;
-#pragma unroll
-    for (int i = 0; i < LA; ++i)
-      dma16(baseA + kt * D_ROW + i * a_step, i ? offA1 : offA0, st + (wave * LA + i) * 8 * D_ROW);
-#pragma unroll
-    for (int i = 0; i < LW; ++i)
-      dma16(baseW + kt * D_ROW + i * w_step, i ? offW1 : offW0, st + (BM + (wave * LW + i) * 8) * D_ROW);
+  auto issue = [&](int slot, int kt, int i) {  // instruction i of stage kt into the ring slot at byte `slot`
+    const uint32_t st = __builtin_amdgcn_readfirstlane(lds0 + slot);
+    if (i < LA) dma16(baseA + kt * D_ROW, offA[i], st + (wave * LA + i) * 8 * D_ROW);
+    else dma16(baseW + kt * D_ROW, offW[i - LA], st + (BM + (wave * LW + i - LA) * 8) * D_ROW);
   };
 
+  // ---- the first NS stages (of a shorter product: its last one again, so that the waits can count them), and behind
+  //      the first of them what the epilogue will need
+  const int KT = a.K / D_BK;
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) issue(0, 0, i);
+  WaveEpilogue<EPI, FM, FN, (NS > 2)> epilogue;
+  epilogue.prefetch(a, m0 + wm * TM, n0 + wn * TN, lane);
+  asm volatile("" ::: "memory");  // keep those loads here
+#pragma unroll
+  for (int s = 1; s < NS; ++s)
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) issue(s * STAGE, min(s, KT - 1), i);
+
+  // ---- fragments: group g of a stage is read into set g & 1
   const int sw = (lrow >> 1) & 7;
   const uint32_t fa_off = (uint32_t)((wm * TM + lrow) * D_ROW + ((lk ^ sw) << 4));
-  const uint32_t fb_off = (uint32_t)((BM + wn * 32 + lrow) * D_ROW + ((lk ^ sw) << 4));
-  f32x16 acc[FM][1];
+  const uint32_t fb_off = (uint32_t)((BM + wn * TN + lrow) * D_ROW + ((lk ^ sw) << 4));
+  f32x16 acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[i][0][v] = 0.f;
-
-  // ---- stages.  The tail re-reads the last one into slots nobody uses any more, so that every stage issues the same
-  //      loads and the wait can count them.
-  constexpr int AHEAD = LOADS * (NS - 2);  // loads that may be in flight at the wait: stages kt + 1 .. kt + NS - 2
-  static_assert(AHEAD < 16, "the low four bits of vmcnt");
-  const int KT = a.K / D_BK;
+    for (int j = 0; j < FN; ++j)
 #pragma unroll
-  for (int s = 0; s < NS - 1; ++s) issue_stage(s, min(s, KT - 1));
-  bf16x8 fa[4][FM], fb[4];  // all four sub-steps of a stage are read up front: registers are plentiful here
-  int slot = 0, fill = NS - 1;  // of the stage being multiplied, of the stage being loaded
-  for (int kt = 0; kt < KT; ++kt) {
-    // this wave's loads of stage kt have landed (those of later stages may be in flight) and its LDS reads of stage
-    // kt - 1 are complete; then meet the other waves
-    __builtin_amdgcn_s_waitcnt(0x0070 | AHEAD);
-    __builtin_amdgcn_s_barrier();
-    issue_stage(fill, min(kt + NS - 1, KT - 1));
-    const unsigned char* const st = smem + slot * STAGE;
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  constexpr int NG = 4 / G, NMG = G * FM * FN, SLOTS = 4 * FM * FN;  // groups, MFMAs of a group and of a stage
+  static_assert(NG % 2 == 0, "a stage's first group is read into the same set every time");
+  bf16x8 fa[2][G][FM], fb[2][G][FN];
+  auto read = [&](int set, int slot, int g) {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
+    for (int ks = 0; ks < G; ++ks) {
 #pragma unroll
-      for (int i = 0; i < FM; ++i) fa[ks][i] = *(const bf16x8*)(st + (fa_off ^ (uint32_t)(ks << 5)) + i * 32 * D_ROW);
-      fb[ks] = *(const bf16x8*)(st + (fb_off ^ (uint32_t)(ks << 5)));
+      for (int j = 0; j < FN; ++j) fb[set][ks][j] = *(const bf16x8*)(smem + slot + (fb_off ^ (uint32_t)((g * G + ks) << 5)) + j * 32 * D_ROW);
+#pragma unroll
+      for (int i = 0; i < FM; ++i) fa[set][ks][i] = *(const bf16x8*)(smem + slot + (fa_off ^ (uint32_t)((g * G + ks) << 5)) + i * 32 * D_ROW);
     }
     __builtin_amdgcn_sched_barrier(0);
+  };
+  // the MFMAs of a set; with LOAD, instruction l of stage kt follows the MFMA l * SLOTS / LOADS places behind the barrier
+  // (the set's first one is `first` places behind it)
+  auto mul = [&](auto load_tag, int set, int slot, int kt, int first) {
+    constexpr bool LOAD = decltype(load_tag)::value;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+    for (int m = 0; m < NMG; ++m) {
+      const int ks = m / (FM * FN), i = m / FN % FM, j = m % FN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][ks][j], fa[set][ks][i], acc[i][j], 0, 0, 0);
+      if constexpr (LOAD) {
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
-        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks], fa[ks][i], acc[i][0], 0, 0, 0);
+        for (int l = 0; l < LOADS; ++l)
+          if (l * SLOTS / LOADS == first + m) issue(slot, kt, l);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     __builtin_amdgcn_sched_barrier(0);
-    fill = slot;
-    slot = slot + 1 == NS ? 0 : slot + 1;
-  }
-  // the trailing loads still write LDS, which the epilogue reuses
-  __builtin_amdgcn_s_waitcnt(0x0070);
+  };
+  const std::true_type T{};
+  const std::false_type F{};
+  wait_loads<(NS - 1) * LOADS>();  // (the epilogue's loads are older than those that may be in flight here)
   __builtin_amdgcn_s_barrier();
-  wave_epilogue<EPI, FM, 1>(a, acc, smem, m0 + wm * TM, n0 + wn * 32, wave, lane);
+  __builtin_amdgcn_sched_barrier(0);
+  int cur = 0;  // byte offset of the slot being multiplied
+  read(0, 0, 0);
+#pragma unroll
+  for (int g = 0; g + 1 < NG; ++g) {
+    read((g + 1) & 1, cur, g + 1);
+    mul(F, g & 1, 0, 0, 0);
+  }
+  // From barrier to barrier: the last group of stage kt, then all but the last of stage kt + 1.  (The loads are behind a
+  // compile-time flag: a branch around them made the compiler copy all accumulators twice a stage.)
+  auto step = [&](auto load_tag, int kt) {
+    const int nxt = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    read(0, nxt, 0);
+    mul(load_tag, 1, cur, kt + NS, 0);
+#pragma unroll
+    for (int g = 0; g + 1 < NG; ++g) {
+      read((g + 1) & 1, nxt, g + 1);
+      mul(load_tag, g & 1, cur, kt + NS, (g + 1) * NMG);
+    }
+    cur = nxt;
+  };
+  int kt = 0;
+  for (; kt < KT - NS; ++kt) {
+    wait_loads<(NS - 2) * LOADS>();  // stage kt + 1 has landed; stages kt + 2 .. kt + NS - 1 may be in flight
+    step(T, kt);
+  }
+  for (; kt < KT - 1; ++kt) {
+    const int newer = KT - 2 - kt;  // stages behind kt + 1, at most NS - 2
+    if (NS >= 4 && newer >= 2) wait_loads<NS >= 4 ? 2 * LOADS : 0>();
+    else if (NS >= 3 && newer >= 1) wait_loads<NS >= 3 ? LOADS : 0>();
+    else wait_loads<0>();
+    step(F, kt);
+  }
+  mul(F, 1, 0, 0, 0);
+  wait_loads<0>();  // (a product of fewer than NS stages may still be loading)
+  __builtin_amdgcn_s_barrier();
+  epilogue.finish(a, acc, smem, m0 + wm * TM, n0 + wn * TN, wave, lane);
 }
 
-template <int NS, int BM, int BN>
-hipError_t launch_ring_as(const GemmArgs& a, hipStream_t s) {
+template <int NS, int BM, int BN, int WM, int WN, int G>
+hipError_t launch_pipe_as(const GemmArgs& a, hipStream_t s) {
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
-  // The cut over the XCDs, rows x columns: 2 x 4 unless another one deals the tiles out more than a tenth more evenly,
-  // then the most even one, then the one whose XCDs read the fewest operand rows.  Measured at 1731 to 5103 rows with
-  // N = 3072 to 4352: 2 x 4 is fastest or within 2 % of it everywhere, 8 x 1 (each XCD reads all of W) up to 20 % slower
-  // (5103 x 3456: 53 against 64 us), 4 x 2 up to 18 %, 1 x 8 up to 20 %.  At N = 1152 (9 tile columns, 60 tiles to an
-  // XCD against 45 of 8 x 1) it is 6 % slower.
-  auto tiles_of = [&](int sn) { return (long)((tiles_m + 8 / sn - 1) / (8 / sn)) * ((tiles_n + sn - 1) / sn); };
-  int split_n = 1;
-  long best = -1;
-  for (int sn = 1; sn <= 8; sn *= 2) {
-    const int sm = 8 / sn;
-    const long cost = tiles_of(sn) * 65536 + ((tiles_m + sm - 1) / sm * BM + (tiles_n + sn - 1) / sn * BN) / 64;
-    if (best < 0 || cost < best) { best = cost; split_n = sn; }
-  }
-  if (tiles_of(4) * 10 <= tiles_of(split_n) * 11) split_n = 4;
-  const int sm = 8 / split_n, mt = (tiles_m + sm - 1) / sm, nt = (tiles_n + split_n - 1) / split_n;
-  const long grid = 8L * mt * nt;
+  const long n_tiles = (long)tiles_m * tiles_n, grid = (n_tiles + 7) / 8 * 8;
   if (grid > 0x7fffffffL) return hipErrorInvalidValue;
   constexpr int lds = NS * (BM + BN) * D_ROW;
-#define VIT_LAUNCH(EPI)                                                                                               \
-  do {                                                                                                                \
-    auto kfn = gemm_bf16_ring_kernel<EPI, NS, BM, BN>;                                                           \
-    static LdsLimitOnce lds_limit;                                                                                    \
-    if (hipError_t e = lds_limit.ensure((const void*)kfn, lds); e != hipSuccess) return e;                            \
-    hipLaunchKernelGGL(kfn, dim3((unsigned)grid), dim3(BN * 4), lds, s, a, tiles_m, tiles_n, split_n, mt, nt);           \
+  static_assert(NS >= 2 && NS <= 4 && lds <= 160 * 1024, "the waits of the last stages; a unit's LDS");
+  static_assert(WM * WN * 32 * (BN / WN * 4 + 16) <= lds, "epilogue staging must fit in the ring");
+#define VIT_LAUNCH(EPI)                                                                                            \
+  do {                                                                                                             \
+    auto kfn = gemm_bf16_pipe_kernel<EPI, NS, BM, BN, WM, WN, G>;                                                  \
+    static LdsLimitOnce lds_limit;                                                                                 \
+    if (hipError_t e = lds_limit.ensure((const void*)kfn, lds); e != hipSuccess) return e;                         \
+    hipLaunchKernelGGL(kfn, dim3((unsigned)grid), dim3(WM * WN * 64), lds, s, a, tiles_m, tiles_n, (int)n_tiles);  \
   } while (0)
   switch (a.epilogue) {
     case EPI_BIAS: VIT_LAUNCH(EPI_BIAS); break;
@@ -781,57 +859,117 @@ hipError_t launch_ring_as(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_ring(const GemmArgs& a, hipStream_t s) {
-  // A product with few tiles of 128 x 128 leaves units idle, so the smallest products take smaller tiles: 64 x 64 (four stages,
-  // two workgroups to a unit) up to 384 of them, 64 x 128 (four stages) up to one per unit; 128 x 128 tiles with four
-  // stages up to one per unit, beyond that with two stages, two workgroups to a unit covering each other's waits.
-  // Measured, in us a launch: 577 rows, out-proj / fc2 / QKV / fc1 on 64 x 64 11.0 / 23.2 / 13.9 / 18.2, on 64 x 128
-  // 13.3 / 31.0 / 12.6 / 20.4, on 128 x 128 17.4 / 42.2 / 15.1 / 16.3; 1154 rows, out-proj / fc2 on 64 x 64 13.7 / 30.0,
-  // on 64 x 128 14.2 / 33.5; 1731 rows 15.4 / 35.5 and 14.2 / 32.8.  1154 rows, fc1 (320 tiles) on four stages 29.5, on
-  // two 21.8; 2885 rows, fc1 (736 tiles) 39.8 and 35.8, QKV (552) 36.8 and 31.8.  Between 513 and 768 tiles the four-stage
-  // ring needs three rounds to the other's two, and a stage takes 0.58 us alone on its unit and 0.95 shared: with many
-  // stages that decides (11540 rows, fc2, 728 tiles of 64 stages: 129 against 136), with 16 the epilogues do, which two
-  // workgroups on a unit cover for each other (out-proj 51 against 49).
-  const auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-  const long t128 = tiles(128, 128);
-  if (t128 > 512 && t128 <= 768 && a.K >= 2048) return launch_ring_as<4, 128, 128>(a, s);
-  if (t128 > 256) return launch_ring_as<2, 128, 128>(a, s);
-  if (tiles(64, 128) > 256) return launch_ring_as<4, 128, 128>(a, s);
-  if (tiles(64, 64) > 384) return launch_ring_as<4, 64, 128>(a, s);
-  return launch_ring_as<4, 64, 64>(a, s);
+// The time that a product is expected to take, in us.  A round is one tile (or, where two workgroups share a unit, two) on
+// each of 256 units; a stage takes `alone` with few units at work and `full` with all of them (the clock falls), and a
+// round has a fixed time of its own and an epilogue by its kind: bias, bias + GELU, residual or patch rows.  Fitted to
+// the times of 20 encoder products (out-proj, QKV, fc1 and fc2 at widths of 768, 1024, 1152, 1280 and 3200, so 768 to
+// 12 800 columns and stages of 12 to 200) at 16 sizes each of 197 to 160 000 rows, weighted towards the tiles that are near
+// the best one: the tile chosen is on average 1 % slower than the best of the ten, and 12 % faster than the predecessor.
+struct TileTime { int bm, bn, per_unit; float alone, full, fixed, epilogue[3]; };
+constexpr float LAUNCH_US = 1.8f;
+constexpr TileTime PIPE_TILES[] = {
+    {64, 64, 2, 0.187f, 0.401f, 1.2f, {0.0f, 0.1f, 0.3f}},
+    {64, 128, 1, 0.195f, 0.339f, 1.1f, {1.2f, 1.3f, 1.8f}},
+    {96, 128, 1, 0.270f, 0.442f, 0.9f, {0.7f, 2.3f, 3.3f}},
+    {128, 128, 1, 0.303f, 0.508f, 0.0f, {2.7f, 3.5f, 6.2f}},
+    {160, 128, 1, 0.279f, 0.605f, 3.3f, {0.0f, 1.7f, 5.3f}},
+    {192, 128, 1, 0.335f, 0.702f, 2.0f, {0.8f, 2.2f, 6.9f}},
+    {256, 128, 1, 0.393f, 0.868f, 2.8f, {1.2f, 2.7f, 8.8f}},
+    {160, 128, 2, 0.731f, 1.160f, 2.1f, {0.4f, 1.3f, 4.6f}},
+    {192, 128, 2, 0.782f, 1.319f, 1.2f, {1.0f, 1.9f, 6.0f}},
+};
+constexpr int PIPE_TILE_COUNT = sizeof(PIPE_TILES) / sizeof(PIPE_TILES[0]);
+
+int epilogue_kind(int epilogue) { return epilogue == EPI_BIAS_GELU ? 1 : epilogue == EPI_BIAS_RESIDUAL || epilogue == EPI_PATCH ? 2 : 0; }
+
+float pipe_time(const TileTime& t, int kind, long M, long N, int stages) {
+  const long n = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), cap = 256L * t.per_unit;
+  auto round = [&](long c) {
+    if (t.per_unit == 1) {
+      const float u = c / 256.0f;
+      return t.fixed + stages * (t.alone + (t.full - t.alone) * u) + t.epilogue[kind] * (0.3f + 0.7f * u);
+    }
+    if (c <= 256) return t.fixed + stages * t.alone + t.epilogue[kind] * (0.3f + 0.7f * c / 256.0f);
+    const float u = (c - 256) / 256.0f;
+    return t.fixed + stages * (t.alone + (t.full - t.alone) * (0.5f + 0.5f * u)) + t.epilogue[kind] * (1.0f + u);
+  };
+  return LAUNCH_US + (n / cap) * round(cap) + (n % cap ? round(n % cap) : 0.0f);
 }
 
-hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
-  const int tiles_m = (a.M + D_BM - 1) / D_BM, tiles_n = (a.N + D_BN - 1) / D_BN;
-  // column bands of four tiles; a remainder of one or two tile columns gets its own group shape
-  // (a remainder of three is a band with one idle column)
-  const int rem = tiles_n % D_GROUP_N;
-  const int narrow_w = rem == 3 ? 0 : rem;
-  const int n_bands = tiles_n / D_GROUP_N + (rem == 3 ? 1 : 0);
-  const int groups_full = ((tiles_m + D_GROUP_M - 1) / D_GROUP_M) * n_bands;
-  const int groups_narrow = narrow_w ? (tiles_m + 32 / narrow_w - 1) / (32 / narrow_w) : 0;
-  const int n_groups = groups_full + groups_narrow;
-  // compute units of the current device, looked up once per device
-  static std::atomic<int> cu_of_device[64];
+struct PipeChoice { int tile; float us; };
+PipeChoice best_pipe(int kind, long M, long N, int stages) {
+  PipeChoice best{0, pipe_time(PIPE_TILES[0], kind, M, N, stages)};
+  for (int i = 1; i < PIPE_TILE_COUNT; ++i) {
+    const float us = pipe_time(PIPE_TILES[i], kind, M, N, stages);
+    if (us < best.us) best = {i, us};
+  }
+  return best;
+}
+
+hipError_t launch_pipe(const GemmArgs& a, int tile, hipStream_t s) {
+  switch (tile) {
+    case 0: return launch_pipe_as<4, 64, 64, 2, 2, 2>(a, s);
+    case 1: return launch_pipe_as<4, 64, 128, 2, 4, 2>(a, s);
+    case 2: return launch_pipe_as<4, 96, 128, 1, 4, 1>(a, s);
+    case 3: return launch_pipe_as<4, 128, 128, 2, 4, 1>(a, s);
+    case 4: return launch_pipe_as<4, 160, 128, 1, 4, 1>(a, s);
+    case 5: return launch_pipe_as<3, 192, 128, 2, 4, 1>(a, s);
+    case 6: return launch_pipe_as<3, 256, 128, 4, 2, 1>(a, s);
+    case 7: return launch_pipe_as<2, 160, 128, 1, 4, 1>(a, s);
+    case 8: return launch_pipe_as<2, 192, 128, 2, 2, 1>(a, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+// The persistent kernel's walk: column bands of four tiles; a remainder of one or two tile columns gets its own group shape (a
+// remainder of three is a band with one idle column).  An XCD takes every eighth group, so a round is eight groups.
+struct Walk { int tiles_m, tiles_n, narrow_w, n_bands, groups_full, n_groups; };
+Walk persistent_walk(long M, long N) {
+  Walk w;
+  w.tiles_m = (int)((M + D_BM - 1) / D_BM);
+  w.tiles_n = (int)((N + D_BN - 1) / D_BN);
+  const int rem = w.tiles_n % D_GROUP_N;
+  w.narrow_w = rem == 3 ? 0 : rem;
+  w.n_bands = w.tiles_n / D_GROUP_N + (rem == 3 ? 1 : 0);
+  w.groups_full = ((w.tiles_m + D_GROUP_M - 1) / D_GROUP_M) * w.n_bands;
+  w.n_groups = w.groups_full + (w.narrow_w ? (w.tiles_m + 32 / w.narrow_w - 1) / (32 / w.narrow_w) : 0);
+  return w;
+}
+
+constexpr TileTime PERSISTENT_TILE = {256, 256, 1, 0.930f, 1.612f, 5.7f, {3.1f, 5.4f, 17.5f}};
+float persistent_time(int kind, long M, long N, int stages) {
+  const Walk w = persistent_walk(M, N);
+  const int rounds = (w.n_groups + 7) / 8;
+  const float u = (float)w.tiles_m * w.tiles_n / (256.0f * rounds);
+  const TileTime& t = PERSISTENT_TILE;
+  return LAUNCH_US + t.fixed + rounds * (stages * (t.alone + (t.full - t.alone) * u) + t.epilogue[kind]);
+}
+
+constexpr int PERSISTENT_GRID = 8 * D_GROUP_M * D_GROUP_N;  // one workgroup per compute unit: 8 XCDs x 32 slots
+
+// compute units of the current device, looked up once per device
+hipError_t compute_units(int* units) {
+  static std::atomic<int> of_device[64];
   int dev = 0;
   if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  int n_cu = cu_of_device[dev].load(std::memory_order_relaxed);
-  if (n_cu == 0) {
-    if (hipError_t e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev); e != hipSuccess) return e;
-    cu_of_device[dev].store(n_cu, std::memory_order_relaxed);
+  *units = of_device[dev].load(std::memory_order_relaxed);
+  if (*units == 0) {
+    if (hipError_t e = hipDeviceGetAttribute(units, hipDeviceAttributeMultiprocessorCount, dev); e != hipSuccess) return e;
+    of_device[dev].store(*units, std::memory_order_relaxed);
   }
-  // one workgroup per compute unit: 8 XCDs x 32 slots.  The unit count is a performance assumption only (the
-  // workgroups never wait for each other); a device with fewer units takes the small-tile kernel instead.
-  const int grid = 8 * D_GROUP_M * D_GROUP_N;
-  if (n_cu < grid) return launch_ring(a, s);
+  return hipSuccess;
+}
+
+hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
+  const Walk w = persistent_walk(a.M, a.N);
 #define VIT_LAUNCH(EPI, STREAM)                                                                                      \
   do {                                                                                                               \
     auto kfn = gemm_bf16_dma_kernel<EPI, STREAM>;                                                                    \
     static LdsLimitOnce lds_limit;                                                                                   \
     if (hipError_t e = lds_limit.ensure((const void*)kfn, D_LDS_BYTES); e != hipSuccess) return e;                   \
-    hipLaunchKernelGGL(kfn, dim3(grid), dim3(512), D_LDS_BYTES, s, a, tiles_m, tiles_n, n_bands, groups_full,        \
-                       narrow_w, n_groups);                                                                          \
+    hipLaunchKernelGGL(kfn, dim3(PERSISTENT_GRID), dim3(512), D_LDS_BYTES, s, a, w.tiles_m, w.tiles_n, w.n_bands,    \
+                       w.groups_full, w.narrow_w, w.n_groups);                                                       \
   } while (0)
   switch (a.epilogue) {
     case EPI_BIAS:
@@ -865,39 +1003,43 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
   // head-by-head output: heads of 64 or 128 columns (a wave's column block never straddles two)
   if (a.epilogue == EPI_BIAS_HEADS && (a.hm_dh <= 0 || a.hm_dh % 64 != 0 || a.hm_rows < (size_t)a.M)) return hipErrorInvalidValue;
-  const int tiles_m = (a.M + 255) / 256, tiles_n = (a.N + 255) / 256;
-  const long big_tiles = (long)tiles_m * tiles_n;
-  // A product one column band wide (1, 2 or 4 tile columns) is walked in rounds of 256 / tiles_n row blocks, one
-  // tile per compute unit.  When the last round holds at most 128 tiles, half or more of the units would sit out a
-  // whole tile time: those row blocks go to the small-tile kernel in a second launch instead (at most 512 tiles of
-  // 128 x 128: one round of two workgroups per unit), also when that leaves the persistent kernel a single round
-  // (a product of 257 to 383 tiles, which as a whole would be too small for it).  Measured on the N = 1024
-  // products at 24 to 64 images: a limit of 64 tiles leaves 3 % on the table at 36 to 40 and at 64 images, a
-  // limit of 192 loses 5 % at 48.  Both kernels give a row the same bits, so where the cut falls does not show
-  // in the result.  The cut is made at the end the walk reaches last.
+  const int kind = epilogue_kind(a.epilogue), stages = a.K / BK;
+  int units = 0;
+  if (hipError_t e = compute_units(&units); e != hipSuccess) return e;
+  const PipeChoice pipe = best_pipe(kind, a.M, a.N, stages);
+  // The unit count is a performance assumption only (no workgroup waits for another): a device with fewer of them takes
+  // one workgroup per tile.
+  if (units < PERSISTENT_GRID) return launch_pipe(a, pipe.tile, s);
+  const float whole = persistent_time(kind, a.M, a.N, stages);
+  // A product one column band wide (1, 2 or 4 tile columns) is walked in rounds of 256 / tiles_n row blocks, one tile per
+  // unit.  Where the last round leaves most units idle for a whole tile time, its rows go to the other kernel in a second
+  // launch (fc2 of 20195 x 1024 x 4096: 174 us so, 216 without).  All kernels give a row the same bits, so where the cut
+  // falls does not show in the result.  It is made at the end that the walk reaches last.
+  const int tiles_m = (a.M + D_BM - 1) / D_BM, tiles_n = (a.N + D_BN - 1) / D_BN;
   if (a.epilogue != EPI_PATCH && (tiles_n == 1 || tiles_n == 2 || tiles_n == 4)) {
-    const int per_round = 256 / tiles_n;
-    const int tail_blocks = tiles_m % per_round;
-    if (tail_blocks > 0 && tiles_m > per_round && tail_blocks * tiles_n <= 128) {
-      const int cut = a.reverse ? tail_blocks * 256 : (tiles_m - tail_blocks) * 256;  // first row of the upper part
-      auto rows_from = [&](int row0, int rows) {
-        GemmArgs b = a;
-        b.M = rows;
-        b.A = (const unsigned char*)a.A + (size_t)row0 * a.lda * 2;
-        if (a.out) b.out = (unsigned char*)a.out + (size_t)row0 * (a.epilogue == EPI_BIAS_HEADS ? a.hm_dh : a.ldo) * 2;  // a row's stride
-        if (a.resid) b.resid = a.resid + (size_t)row0 * a.ldo;
-        return b;
-      };
-      const GemmArgs lower = rows_from(0, cut), upper = rows_from(cut, a.M - cut);
-      if (hipError_t e = launch_dma(a.reverse ? upper : lower, s); e != hipSuccess) return e;
-      return launch_ring(a.reverse ? lower : upper, s);
+    const int per_round = 256 / tiles_n, tail_blocks = tiles_m % per_round;
+    if (tail_blocks > 0 && tiles_m > per_round) {
+      const int main_rows = (tiles_m - tail_blocks) * D_BM, tail_rows = a.M - main_rows;
+      const PipeChoice tail = best_pipe(kind, tail_rows, a.N, stages);
+      if (persistent_time(kind, main_rows, a.N, stages) + tail.us < std::min(whole, pipe.us)) {
+        auto rows_from = [&](int row0, int rows) {
+          GemmArgs b = a;
+          b.M = rows;
+          b.A = (const unsigned char*)a.A + (size_t)row0 * a.lda * 2;
+          if (a.out) b.out = (unsigned char*)a.out + (size_t)row0 * (a.epilogue == EPI_BIAS_HEADS ? a.hm_dh : a.ldo) * 2;  // a row's stride
+          if (a.resid) b.resid = a.resid + (size_t)row0 * a.ldo;
+          return b;
+        };
+        // (walked in reverse, the persistent kernel takes the last rows of the matrix, ragged row block included)
+        const int cut = a.reverse ? tail_blocks * D_BM : main_rows;
+        const GemmArgs lower = rows_from(0, cut), upper = rows_from(cut, a.M - cut);
+        if (hipError_t e = launch_dma(a.reverse ? upper : lower, s); e != hipSuccess) return e;
+        const GemmArgs& rest = a.reverse ? lower : upper;
+        return launch_pipe(rest, best_pipe(kind, rest.M, a.N, stages).tile, s);
+      }
     }
   }
-  // The persistent 256 x 256 kernel pays off from about one and a half tiles per compute unit
-  // (measured crossover between 300 and 440 tiles on the encoder's shapes); below that its last,
-  // partly filled round costs more than the smaller tiles' extra operand traffic.
-  if (big_tiles < 384) return launch_ring(a, s);
-  return launch_dma(a, s);
+  return whole < pipe.us ? launch_dma(a, s) : launch_pipe(a, pipe.tile, s);
 }
 
 }  // namespace vitenc

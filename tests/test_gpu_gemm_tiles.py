@@ -45,3 +45,21 @@ def test_rows_alone_cut_over_the_xcds(n):
         assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
     want, _ = O.vit_oracle_encode(cfg, w, px[-1:], [1], one)
     assert_parity(whole[-T:], want, "bf16", f"row cut n={n}")
+
+
+@pytest.mark.parametrize("n,hidden,mlp", [(14, 512, 2056), (28, 512, 2056), (44, 512, 2056), (50, 512, 2056), (60, 512, 2056),
+                                          (40, 64, 4104), (40, 128, 4104), (40, 192, 4104)])
+def test_tile_heights_and_short_products(n, hidden, mlp):
+    """Tiles of 96 to 256 rows (none of which divides n * 226), with one and with two workgroups to a unit, under every epilogue;
+    and products of one, two and three k-stages, fewer than the tiles' rings hold."""
+    cfg = dict(CFG, hidden=hidden, heads=hidden // 64, mlp=mlp, layers_local=1)
+    say(f"case matrix-product tiles, {n} images of 226 tokens, width {hidden}")
+    w, px = gen.make_weights(cfg, seed=5), gen.make_pixels(cfg, n, seed=n)
+    whole, _ = gpu_encode(cfg, w, px, [n], np.arange(n + 1, dtype=np.int32))
+    T = gen.tokens_per_tile(cfg)
+    one = np.array([0, 1], dtype=np.int32)
+    for i in sorted({0, n // 3, n // 2, n - 1}):
+        alone, _ = gpu_encode(cfg, w, px[i:i + 1], [1], one)
+        assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
+    want, _ = O.vit_oracle_encode(cfg, w, px[-1:], [1], one)
+    assert_parity(whole[-T:], want, "bf16", f"tile heights n={n} width={hidden}")

@@ -18,7 +18,8 @@
 // back to back and is slowed by about 12 %), so the kernel is shaped around the number of waves per SIMD and the
 // vector instruction count per 32 x 32 block of logits: a wave owns 32 queries, which keeps it at 128-168 VGPRs
 // so that four (head dim 64) or three waves from different workgroups share a SIMD and interleave their
-// dependency chains (a fourth wave is worth 7 % at head dim 64); the queries arrive multiplied by
+// dependency chains (a fourth wave is worth 7 % at head dim 64; launches of few workgroups take a deeper pipelined
+// form of one wave less, see `attend_deep`); the queries arrive multiplied by
 // log2(e) / sqrt(head dim), so the logits are exp2 arguments as they leave the first product; full key tiles
 // carry no mask code at all (a segment's last tile is a separate instantiation that also skips an empty key
 // half, and waves with no valid query row skip the arithmetic); and the normal pass uses no reference maximum:
@@ -38,20 +39,18 @@ namespace vitenc {
 namespace {
 
 constexpr int AKV = 64;  // keys per LDS tile
-enum { SUM_VALU = 0, SUM_ROWS = 1 };
+enum { SUM_ONES = 0, SUM_ROWS = 1 };
 constexpr float REFERENCE_LIMIT = 18446744073709551616.0f;  // 2^64: a row sum this large moves the reference maximum
 
-// QB = 32-query blocks per wave, NW = waves per workgroup: a work item is 32 * QB * NW query rows.
-// All head dims run QB = 1, NW = 4 (128 rows); QB = 2 (each K / V^T fragment feeding two MFMAs, two
-// waves per SIMD) was measured 15 % slower.
+// A workgroup is four waves with 32 query rows each, the 128 of a work item (blocks of 64 queries per wave, each K / V^T
+// fragment feeding two MFMAs, were measured 15 % slower).
 // DHP = head dim as stored (a multiple of 8: 64, 72, 80, 96, 128).  The S^T product runs over DHL = DHP rounded up
 // to whole 16-wide k-steps: for 72 the K tile's LDS rows carry 8 zero columns (written once, never by the loader)
 // and the Q fragment of the last half k-step is zero, so nothing is padded in HBM.
-template <int DHP, int QB, int NW>
+template <int DHP>
 struct AttnShape {
   static constexpr int DHL = (DHP + 15) / 16 * 16;  // head dim of the K rows in LDS
-  static constexpr int ANT = 64 * NW;            // threads per workgroup
-  static constexpr int AQ = 32 * QB * NW;        // query rows per work item
+  static constexpr int ANT = 256;                   // threads per workgroup
   static constexpr int KS = DHL / 16;            // k-steps of the S^T product
   static constexpr int DB = (DHP + 31) / 32;     // 32-row blocks of O^T
   static constexpr int NCH = DHP / 8;            // 16-byte chunks per K/V row
@@ -70,17 +69,16 @@ struct AttnShape {
   static constexpr int STAGE = K_BYTES + V_BYTES;
   static constexpr int K_ITEMS = AKV * NCH;  // 16-byte chunks of the K tile, and of the V tile
   static constexpr int K_PER = (K_ITEMS + ANT - 1) / ANT;
-  // where the row sums of P come from in the fast pass: spare rows of the last O^T block if the head dim leaves
-  // any (72, 80: two columns of ones in the V rows' padding), vector instructions otherwise (v_dot2c_f32_bf16 of a packed pair with a pair of ones: 8 per
-  // block of logits).  (One more accumulator fed by a fragment of ones held in registers costs 20 registers: at
-  // head dim 64 that is the fourth wave of a SIMD, and the kernel came out 5 % slower with it, 13 % when forced
-  // into 128 registers.)
-  static constexpr int SUM = DB * 32 - DHP >= 8 ? SUM_ROWS : SUM_VALU;
+  // where the row sums of P come from in the normal pass: spare rows of the last O^T block if the head dim leaves any
+  // (72, 80: two columns of ones in the V rows' padding), else two small products with ones (see `ones`).  (A 32 x 32 x 16
+  // product with ones costs 16 more accumulators: at head dim 64 that is the fourth wave of a SIMD, and the kernel came
+  // out 5 % slower with it, 13 % when forced into 128 registers.)
+  static constexpr int SUM = DB * 32 - DHP >= 8 ? SUM_ROWS : SUM_ONES;
 };
 
-template <int DHP, int QB, int NW>
-__global__ __launch_bounds__(64 * NW, QB == 1 ? (DHP == 64 ? 4 : DHP <= 96 ? 3 : 2) : 2) void attention_bf16_kernel(const AttnArgs a) {
-  using Sh = AttnShape<DHP, QB, NW>;
+template <int DHP, bool DEEP>
+__global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : DHP <= 96 ? 3 : 2) void attention_bf16_kernel(const AttnArgs a) {
+  using Sh = AttnShape<DHP>;
   constexpr int ANT = Sh::ANT;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];  // 2 stages of (K tile, V tile)
 
@@ -118,20 +116,19 @@ __global__ __launch_bounds__(64 * NW, QB == 1 ? (DHP == 64 ? 4 : DHP <= 96 ? 3 :
   const bf16_t* v_base = (const bf16_t*)a.qkv + (size_t)(2 * a.heads + head) * blk;
   const int seg_end = w.seg_start + w.seg_len;
 
-  // Q^T fragments of the wave's two query blocks: lane holds d = 16*ks + 8*g .. +8 of its query row;
+  // Q^T fragments of the wave's query block: lane holds d = 16*ks + 8*g .. +8 of its query row;
   // rows past the segment end compute on a copy of its last row and are never stored.
-  bf16x8 qf[QB][Sh::KS];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int qload = min(w.q0 + (wave * QB + qb) * 32 + lq, seg_end - 1);
+  bf16x8 qf[Sh::KS];
+  {
+    const int qload = min(w.q0 + wave * 32 + lq, seg_end - 1);
 #pragma unroll
     for (int ks = 0; ks < Sh::KS; ++ks) {
       if (ks * 16 + 8 < DHP) {  // both 8-wide halves of the k-step lie inside the head
-        qf[qb][ks] = *(const bf16x8*)(q_base + (size_t)qload * row_elems + ks * 16 + g * 8);
+        qf[ks] = *(const bf16x8*)(q_base + (size_t)qload * row_elems + ks * 16 + g * 8);
       } else {  // head dim 72: the upper half of the last k-step does not exist; its lanes feed zeros
         const bf16x8 lo = *(const bf16x8*)(q_base + (size_t)qload * row_elems + ks * 16);
         const u32x4 z = {0u, 0u, 0u, 0u};
-        qf[qb][ks] = g == 0 ? lo : __builtin_bit_cast(bf16x8, z);
+        qf[ks] = g == 0 ? lo : __builtin_bit_cast(bf16x8, z);
       }
     }
   }
@@ -186,8 +183,8 @@ __global__ __launch_bounds__(64 * NW, QB == 1 ? (DHP == 64 ? 4 : DHP <= 96 ? 3 :
   };
 
   const int n_tiles = (w.seg_len + AKV - 1) / AKV;
-  // a wave whose 32 * QB query rows all lie past the segment end (last block of a segment) skips the arithmetic
-  const bool wave_active = w.q0 + wave * QB * 32 < seg_end;
+  // a wave whose 32 query rows all lie past the segment end (last block of a segment) skips the arithmetic
+  const bool wave_active = w.q0 + wave * 32 < seg_end;
 
   // What the loader never writes must still be finite (a product with garbage could be NaN): the K rows' columns
   // DHP .. DHL - 1 take part in S^T and are zero.  The V rows' columns DHP .. 32 DB - 1 only produce O^T rows that are
@@ -212,41 +209,73 @@ __global__ __launch_bounds__(64 * NW, QB == 1 ? (DHP == 64 ? 4 : DHP <= 96 ? 3 :
     }
   }
 
-  f32x16 o[QB][Sh::DB];
-  float l[QB];  // row sums of P (FAST with SUM_VALU, and the general pass)
-  float m[QB];  // reference maximum in log2 units (general pass)
+  f32x16 o[Sh::DB];
+  float l = 0.f;  // row sum of P
+  // SUM_ONES: P^T's fragment is an operand of the 16 x 16 x 32 product as well, whose column n sums the eight values of the
+  // lanes n, n + 16, n + 32 and n + 48, of the queries n and n + 16 that is; a first operand with ones for the lanes of one
+  // in its even rows and for those of the other in its odd rows tells them apart.  Two of them take 32 clocks, the eight
+  // v_dot2c_f32_bf16 with a pair of ones that they replaced 128: those do not run beside MFMAs (a probe: 16 exp2, 8 packed
+  // conversions and 8 MFMAs of 32 clocks take 266 clocks with four waves on a SIMD, 395 with the eight dot products).
+  // Attention of 260 x 577 tokens, 16 heads of 64: 481 us with the dot products, 470 now.
+  f32x4 lsum = {0.f, 0.f, 0.f, 0.f};
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)(((lane ^ (lane >> 4)) & 1) ? 0.0f : 1.0f);
+  auto sum_ones = [&](const bf16x8 (&p)[2]) {
+    if constexpr (Sh::SUM == SUM_ONES) {
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, p[s2], lsum, 0, 0, 0);
+    }
+  };
+  auto read_vt = [&](const unsigned char* sV, int kb, int b, int s2) {
+    // V^T[32 b + lq][keys 32 kb + 16 s2 + 4 g .. + 3] and the same eight keys on: two transposing reads
+    const unsigned char* p = sV + (kb * 32 + s2 * 16) * Sh::V_STRIDE + ((uint32_t)(b * 64) ^ vt_swap) + vt_off;
+    const u32x2 lo = read_tr(p), hi = read_tr(p + 8 * Sh::V_STRIDE);
+    return __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+  };
+  auto mask = [&](f32x16& st, int kb, int remaining) {  // keys past the segment end
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (kb * 32 + 8 * (v >> 2) + 4 * g + (v & 3) >= remaining) st[v] = -INFINITY;
+  };
+  const std::true_type T{};
+  const std::false_type F{};
+  auto fetch = [&](int t) {  // tile t into registers
+    if (t < n_tiles) {
+      if ((t + 1) * AKV <= w.seg_len) load_tile(t * AKV, F);
+      else load_tile(t * AKV, T);
+    }
+  };
+  auto store = [&](int t) { store_tile(lds + (t & 1) * Sh::STAGE, lds + (t & 1) * Sh::STAGE + Sh::K_BYTES); };
 
-  // One pass over the segment's K/V tiles.
+  // One pass over the segment's K/V tiles, block by block of 32 keys.
   //
   // FAST (the pass that normally is the only one): P^T = exp2(S^T) with no reference maximum at all.  The logits
   // arrive in log2 units (the QKV product has multiplied the queries by log2(e) / sqrt(head dim)), P is a bf16
   // value and the sums are fp32, eight exponent bits both, so nothing is lost while the row sum stays between
   // 2^-100 and 2^100, i.e. while the largest logit of a row lies within about +-69 (natural units) of zero.  That
-  // is checked once, after the last tile; a workgroup with a row outside runs the general pass instead.  Per
+  // is checked once, after the last tile; a wave with a row outside runs the general pass instead.  Per
   // 32 x 32 block of logits this pass issues 16 exp2, 8 packed conversions and its MFMAs; the row sums come from
-  // the matrix cores where the head dim leaves spare rows in the last O^T block (SUM_ROWS: two columns of ones in the
-  // V tile's padding), else from 8 two-element dot products with ones (SUM_VALU).  Either way the sum is taken
+  // the matrix cores: from spare rows of the last O^T block where the head dim leaves any (SUM_ROWS: two columns of ones
+  // in the V tile's padding), else from two 16 x 16 x 32 products (SUM_ONES).  Either way the sum is taken
   // over the rounded weights, the ones the second product multiplies with.
   //
   // General pass: the online softmax with a lazily moving reference maximum m.  m only has to keep exp2 in range,
   // not to be the exact running maximum, so the row maximum is not computed on its common path either: a row sum
   // that reaches 2^64 (or is not a number: m = -inf before the first tile) says that m has to move; only then is
   // the maximum of the half tile taken, m moved and the accumulators rescaled.
-  auto attend = [&](auto fast_tag) {
+  auto attend = [&](auto fast_tag, const bool active) {
     constexpr bool FAST = decltype(fast_tag)::value;
-    constexpr int SUM = FAST ? Sh::SUM : SUM_VALU;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
+    float m = -INFINITY;  // reference maximum in log2 units (general pass)
+    if (active) {
 #pragma unroll
       for (int b = 0; b < Sh::DB; ++b)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[qb][b][v] = 0.f;
-      m[qb] = -INFINITY;
-      l[qb] = 0.f;
+        for (int v = 0; v < 16; ++v) o[b][v] = 0.f;
+      l = 0.f;
     }
-    if (w.seg_len >= AKV) load_tile(0, std::false_type{});
-    else load_tile(0, std::true_type{});
-    store_tile(lds, lds + Sh::K_BYTES);
+    fetch(0);
+    store(0);
     __syncthreads();
 
     // One K/V tile.  MASK is set only for a segment's last, partial tile: full tiles carry no
@@ -255,112 +284,74 @@ __global__ __launch_bounds__(64 * NW, QB == 1 ? (DHP == 64 ? 4 : DHP <= 96 ? 3 :
       constexpr bool MASK = decltype(mask_tag)::value;
       const unsigned char* sK = lds + (t & 1) * Sh::STAGE;
       const unsigned char* sV = sK + Sh::K_BYTES;
-      if (t + 1 < n_tiles) {  // the next tile is full unless it is the segment's last, partial one
-        if ((t + 2) * AKV <= w.seg_len) load_tile((t + 1) * AKV, std::false_type{});
-        else load_tile((t + 1) * AKV, std::true_type{});
-      }
-
+      fetch(t + 1);
       const int remaining = w.seg_len - t * AKV;  // valid keys in this tile (may exceed AKV)
       // the tile is processed in two 32-key halves to keep S^T and P^T small in registers
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
-        if (!wave_active) break;  // (the wave still stages K / V and meets the barriers)
+        if (!active) break;  // (the wave still stages K / V and meets the barriers)
         if (MASK && kb * 32 >= remaining) break;  // the second half of the last tile may hold no key at all
-        // ---- S^T = K . Q^T: each K fragment feeds all query blocks of the wave; keys past the segment end are
-        //      masked (only a segment's last tile has any)
-        f32x16 st[QB];
+        f32x16 st;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) st[qb][v] = 0.f;
+        for (int v = 0; v < 16; ++v) st[v] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < Sh::KS; ++ks) {
-          const bf16x8 kf = *(const bf16x8*)(sK + (kb * 32 + lq) * Sh::K_STRIDE + (ks * 2 + g) * 16);
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb)
-            st[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qb][ks], st[qb], 0, 0, 0);
+          const bf16x8 k = *(const bf16x8*)(sK + (kb * 32 + lq) * Sh::K_STRIDE + (ks * 2 + g) * 16);
+          st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, qf[ks], st, 0, 0, 0);
         }
-        if (MASK) {
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int key = kb * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-              if (key >= remaining) st[qb][v] = -INFINITY;
-            }
-        }
+        if (MASK) mask(st, kb, remaining);
         // ---- P^T replaces S^T as bf16 fragments
-        bf16x8 pf[QB][2];
+        bf16x8 p[2];
+        float psum;
+        auto exponentials = [&](float neg_m) {
+          uint32_t pw[8];
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          float psum;
-          auto exponentials = [&](const f32x16& sq, float neg_m) {
+          for (int e = 0; e < 8; ++e)
+            pw[e] = pack_bf16x2(__builtin_amdgcn_exp2f(FAST ? st[2 * e] : st[2 * e] + neg_m),
+                                __builtin_amdgcn_exp2f(FAST ? st[2 * e + 1] : st[2 * e + 1] + neg_m));
+          if constexpr (!FAST) {
+            // two weights per instruction.  (The packed words are taken from the scalar array: cast from the elements of a
+            // vector, this compiler gave all four instructions the vector's first register.)
+            const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
             psum = 0.f;
 #pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2) {
-              float p[8];
-#pragma unroll
-              for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(FAST ? sq[s2 * 8 + e] : sq[s2 * 8 + e] + neg_m);
-              const uint32_t pw[4] = {pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]), pack_bf16x2(p[4], p[5]),
-                                      pack_bf16x2(p[6], p[7])};
-              const u32x4 pk = {pw[0], pw[1], pw[2], pw[3]};
-              if (SUM == SUM_VALU) {
-                // the row sum is taken over the rounded weights, the ones the second product multiplies with, two
-                // per instruction: v_dot2c_f32_bf16 with a pair of ones (fp32 accumulation).  (The packed words are
-                // taken from the scalar array: cast from the elements of the vector `pk`, this compiler gave all
-                // four instructions the vector's first register.)
-                const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                  psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[e]), ones, psum, false);
-              }
-              pf[qb][s2] = __builtin_bit_cast(bf16x8, pk);
-            }
-          };
-          exponentials(st[qb], -m[qb]);
-          if constexpr (!FAST) {
-            if (__builtin_amdgcn_ballot_w64(!(psum < REFERENCE_LIMIT)) != 0) {
-              // Rare: move m to the maximum seen so far (the same for the two lanes that share a query), rescale
-              // the accumulators and redo the exponentials.  (Forming the logits again here instead of keeping
-              // them alive costs head dims 80 and 96 seven per cent: measured.)
-              const f32x16& sr = st[qb];
-              float mx = sr[0];
-#pragma unroll
-              for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sr[v]);
-              mx = fmaxf(mx, __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(partner_addr, __builtin_bit_cast(int, mx))));
-              const float m_up = fmaxf(m[qb], mx);
-              const float corr = __builtin_amdgcn_exp2f(m[qb] - m_up);
-              l[qb] *= corr;
-#pragma unroll
-              for (int b = 0; b < Sh::DB; ++b)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[qb][b][v] *= corr;
-              m[qb] = m_up;
-              exponentials(sr, -m[qb]);
-            }
+            for (int e = 0; e < 8; ++e) psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[e]), one2, psum, false);
           }
-          if (SUM == SUM_VALU) l[qb] += psum;
+          p[0] = __builtin_bit_cast(bf16x8, u32x4{pw[0], pw[1], pw[2], pw[3]});
+          p[1] = __builtin_bit_cast(bf16x8, u32x4{pw[4], pw[5], pw[6], pw[7]});
+        };
+        exponentials(-m);
+        if constexpr (!FAST) {
+          if (__builtin_amdgcn_ballot_w64(!(psum < REFERENCE_LIMIT)) != 0) {
+            // Rare: move m to the maximum seen so far (the same for the two lanes that share a query), rescale
+            // the accumulators and redo the exponentials.  (Forming the logits again here instead of keeping
+            // them alive costs head dims 80 and 96 seven per cent: measured.)
+            float mx = st[0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, st[v]);
+            mx = fmaxf(mx, __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(partner_addr, __builtin_bit_cast(int, mx))));
+            const float m_up = fmaxf(m, mx);
+            const float corr = __builtin_amdgcn_exp2f(m - m_up);
+            l *= corr;
+#pragma unroll
+            for (int b = 0; b < Sh::DB; ++b)
+#pragma unroll
+              for (int v = 0; v < 16; ++v) o[b][v] *= corr;
+            m = m_up;
+            exponentials(-m);
+          }
+          l += psum;
+        } else {
+          sum_ones(p);
         }
-        // ---- O^T += V^T . P^T: each V^T fragment feeds all query blocks of the wave
+        // ---- O^T += V^T . P^T
 #pragma unroll
         for (int b = 0; b < Sh::DB; ++b)
 #pragma unroll
-          for (int s2 = 0; s2 < 2; ++s2) {
-            // V^T[32 b + lq][keys 32 kb + 16 s2 + 4 g .. + 3] and the same eight keys on: two transposing reads
-            const unsigned char* p = sV + (kb * 32 + s2 * 16) * Sh::V_STRIDE + ((uint32_t)(b * 64) ^ vt_swap) + vt_off;
-            const u32x2 lo = read_tr(p), hi = read_tr(p + 8 * Sh::V_STRIDE);
-            const u32x4 packed = {lo[0], lo[1], hi[0], hi[1]};
-            const bf16x8 vf = __builtin_bit_cast(bf16x8, packed);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-              o[qb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[qb][s2], o[qb][b], 0, 0, 0);
-          }
+          for (int s2 = 0; s2 < 2; ++s2)
+            o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_vt(sV, kb, b, s2), p[s2], o[b], 0, 0, 0);
       }
-
-      if (t + 1 < n_tiles) {
-        unsigned char* nK = lds + ((t + 1) & 1) * Sh::STAGE;
-        store_tile(nK, nK + Sh::K_BYTES);
-      }
+      if (t + 1 < n_tiles) store(t + 1);
       __syncthreads();
     };
     // Every load issued so far (the Q fragments among them) has landed before the loop starts: the
@@ -368,25 +359,132 @@ __global__ __launch_bounds__(64 * NW, QB == 1 ? (DHP == 64 ? 4 : DHP <= 96 ? 3 :
     // each tile's first MFMAs wait for the global loads of the NEXT tile issued just before them.
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     const int n_full = w.seg_len / AKV;  // tiles with all 64 keys valid
-    for (int t = 0; t < n_full; ++t) process_tile(t, std::false_type{});
-    if (n_full < n_tiles) process_tile(n_full, std::true_type{});
+    for (int t = 0; t < n_full; ++t) process_tile(t, F);
+    if (n_full < n_tiles) process_tile(n_full, T);
+    if (!FAST && active) l += __shfl_xor(l, 32, 64);  // the row sum of every query, in both lanes that share it
+  };
 
-    // the row sum of every query, in both lanes that share it
+  // DEEP: the same pass, FAST, with the blocks of 32 keys pipelined.  A wave's chain for a block, LDS read -> MFMAs -> exp2 ->
+  // conversion -> MFMAs, is several times as long as its MFMAs.  Here the matrix cores form the next block's logits while
+  // the exponentials of this one are formed, one or a few behind each MFMA, and every fragment is read a whole product
+  // ahead of its use (K's during the second product of the block before, V's during the next block's first product).
+  // Two barriers a tile: behind the first, tile t + 1 (stored before it) is complete; behind the second nobody reads tile
+  // t any more.
+  auto attend_deep = [&]() {
+    bf16x8 kf[Sh::KS];        // K fragments of the next first product
+    bf16x8 vf[Sh::DB][2];     // V^T fragments of the next second product
+    bf16x8 pf[2];             // P^T of a block
+    auto read_k = [&](int buf, int kb) {
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      if constexpr (SUM == SUM_VALU) l[qb] += __shfl_xor(l[qb], 32, 64);
-      else l[qb] = o[qb][Sh::DB - 1][((DHP % 32) / 8) * 4];
+      for (int ks = 0; ks < Sh::KS; ++ks)
+        kf[ks] = *(const bf16x8*)(lds + buf * Sh::STAGE + (kb * 32 + lq) * Sh::K_STRIDE + (ks * 2 + g) * 16);
+    };
+    auto read_v = [&](int buf, int kb) {
+#pragma unroll
+      for (int b = 0; b < Sh::DB; ++b)
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) vf[b][s2] = read_vt(lds + buf * Sh::STAGE + Sh::K_BYTES, kb, b, s2);
+    };
+    // S^T of the block in kf into `sn`, and P^T of the block in `so` into pf: the exponentials between the MFMAs
+    auto logits_and_weights = [&](auto next_tag, auto exp_tag, f32x16& sn, const f32x16& so) {
+      constexpr bool NEXT = decltype(next_tag)::value, EXP = decltype(exp_tag)::value;
+      uint32_t pw[8];
+#pragma unroll
+      for (int ks = 0; ks < Sh::KS; ++ks) {
+        if constexpr (NEXT) {
+          if (ks == 0) {
+            const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], zero, 0, 0, 0);
+          } else {
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sn, 0, 0, 0);
+          }
+        }
+        if constexpr (EXP) {
+#pragma unroll
+          for (int e = 8 * ks / Sh::KS; e < 8 * (ks + 1) / Sh::KS; ++e)
+            pw[e] = pack_bf16x2(__builtin_amdgcn_exp2f(so[2 * e]), __builtin_amdgcn_exp2f(so[2 * e + 1]));
+        }
+        if constexpr (NEXT) __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (EXP) {
+        pf[0] = __builtin_bit_cast(bf16x8, u32x4{pw[0], pw[1], pw[2], pw[3]});
+        pf[1] = __builtin_bit_cast(bf16x8, u32x4{pw[4], pw[5], pw[6], pw[7]});
+      }
+    };
+    auto accumulate = [&]() {  // O^T += V^T . P^T, and the row sums
+      sum_ones(pf);
+#pragma unroll
+      for (int b = 0; b < Sh::DB; ++b)
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[b][s2], pf[s2], o[b], 0, 0, 0);
+    };
+    fetch(0);
+    store(0);
+    fetch(1);
+    __syncthreads();
+    // waves without queries only move tiles
+    if (wave_active) {
+      f32x16 s0, s1;
+#pragma unroll
+      for (int b = 0; b < Sh::DB; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[b][v] = 0.f;
+      read_k(0, 0);
+      logits_and_weights(T, F, s0, s0);
+      read_k(0, 1);  // (of a tile of 32 keys or less: rows that repeat the last one, and no use)
+      for (int t = 0; t < n_tiles - 1; ++t) {  // full tiles, each with another behind it
+        const int buf = t & 1;
+        store(t + 1);
+        fetch(t + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        read_v(buf, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        logits_and_weights(T, T, s1, s0);
+        __syncthreads();
+        read_k(buf ^ 1, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        accumulate();
+        __builtin_amdgcn_sched_barrier(0);
+        read_v(buf, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        logits_and_weights(T, T, s0, s1);
+        __builtin_amdgcn_sched_barrier(0);
+        read_k(buf ^ 1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        accumulate();
+        __syncthreads();
+      }
+      const int buf = (n_tiles - 1) & 1, remaining = w.seg_len - (n_tiles - 1) * AKV;  // 1 to 64 keys
+      read_v(buf, 0);
+      if (remaining > 32) {
+        logits_and_weights(T, T, s1, s0);
+        accumulate();
+        read_v(buf, 1);
+        mask(s1, 1, remaining);
+        logits_and_weights(F, T, s1, s1);
+      } else {
+        mask(s0, 0, remaining);
+        logits_and_weights(F, T, s0, s0);
+      }
+      accumulate();
+    } else {
+      for (int t = 0; t < n_tiles - 1; ++t) {
+        store(t + 1);
+        fetch(t + 2);
+        __syncthreads();
+        __syncthreads();
+      }
     }
   };
 
-  attend(std::true_type{});
-  {
-    bool ok = true;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) ok = ok && l[qb] >= 0x1p-100f && l[qb] <= 0x1p100f;  // false for NaN
-    // (the barrier also separates the last tile's LDS reads from the general pass's first stores)
-    if (__syncthreads_or(wave_active && !ok)) attend(std::false_type{});
-  }
+  if constexpr (DEEP) attend_deep();
+  else attend(T, wave_active);
+  if constexpr (Sh::SUM == SUM_ONES) l = lane & 16 ? lsum[1] : lsum[0];
+  else l = o[Sh::DB - 1][((DHP % 32) / 8) * 4];
+  // which waves run the general pass depends on their own rows alone, not on what shares their workgroup
+  const bool again = wave_active && __builtin_amdgcn_ballot_w64(!(l >= 0x1p-100f && l <= 0x1p100f)) != 0;  // (NaN, too)
+  // (the barrier also separates the last tile's LDS reads from the general pass's first stores)
+  if (__syncthreads_or(again)) attend(F, again);
 
   // ---- normalise and store: lane owns a query; registers 4j..4j+3 of block b are
   //      d = 32b + 8j + 4g .. +3, four consecutive columns -> one 8-byte piece.
@@ -394,79 +492,70 @@ __global__ __launch_bounds__(64 * NW, QB == 1 ? (DHP == 64 ? 4 : DHP <= 96 ? 3 :
   // so the 8-byte writes of 16 rows and the read-back fall on different banks) and stores them 16 bytes per lane,
   // DHP / 8 lanes per row: a store instruction then touches 4 to 8 rows where direct 8-byte stores touch 32, a
   // quarter of the cache requests for the same bytes.
-  if constexpr (QB == 1) {
-    if (wave_active) {
-      constexpr int ROWB = DHP * 2 + 8, NCH = DHP / 8;
-      unsigned char* so = lds + wave * 32 * ROWB;
-      const float inv = 1.0f / l[0];  // (rows past the segment end: never stored)
+  if (!wave_active) return;
+  constexpr int ROWB = DHP * 2 + 8, NCH = DHP / 8;
+  unsigned char* so = lds + wave * 32 * ROWB;
+  const float inv = 1.0f / l;  // (rows past the segment end: never stored)
 #pragma unroll
-      for (int b = 0; b < Sh::DB; ++b)
+  for (int b = 0; b < Sh::DB; ++b)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (b * 32 + 8 * j >= DHP) continue;  // the spare rows of the last O^T block
-          const u32x2 pk = {pack_bf16x2(o[0][b][4 * j] * inv, o[0][b][4 * j + 1] * inv),
-                            pack_bf16x2(o[0][b][4 * j + 2] * inv, o[0][b][4 * j + 3] * inv)};
-          *(u32x2*)(so + lq * ROWB + (b * 32 + 8 * j + 4 * g) * 2) = pk;
-        }
-      __builtin_amdgcn_wave_barrier();
-      bf16_t* obase = (bf16_t*)a.out + (size_t)(w.q0 + wave * 32) * a.ld_o + head * DHP;
-#pragma unroll
-      for (int p = 0; p < (32 * NCH + 63) / 64; ++p) {
-        const int item = min(p * 64 + lane, 32 * NCH - 1), row = item / NCH, ch = item % NCH;
-        const u32x2 lo = *(const u32x2*)(so + row * ROWB + ch * 16), hi = *(const u32x2*)(so + row * ROWB + ch * 16 + 8);
-        if (p * 64 + lane < 32 * NCH && w.q0 + wave * 32 + row < seg_end)
-          *(u32x4*)(obase + (size_t)row * a.ld_o + ch * 8) = u32x4{lo[0], lo[1], hi[0], hi[1]};
-      }
+    for (int j = 0; j < 4; ++j) {
+      if (b * 32 + 8 * j >= DHP) continue;  // the spare rows of the last O^T block
+      const u32x2 pk = {pack_bf16x2(o[b][4 * j] * inv, o[b][4 * j + 1] * inv),
+                        pack_bf16x2(o[b][4 * j + 2] * inv, o[b][4 * j + 3] * inv)};
+      *(u32x2*)(so + lq * ROWB + (b * 32 + 8 * j + 4 * g) * 2) = pk;
     }
-    return;
-  }
+  __builtin_amdgcn_wave_barrier();
+  bf16_t* obase = (bf16_t*)a.out + (size_t)(w.q0 + wave * 32) * a.ld_o + head * DHP;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int qrow = w.q0 + (wave * QB + qb) * 32 + lq;
-    if (qrow < seg_end) {
-      const float inv = 1.0f / l[qb];
-      bf16_t* orow = (bf16_t*)a.out + (size_t)qrow * a.ld_o + head * DHP;
-#pragma unroll
-      for (int b = 0; b < Sh::DB; ++b)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int d = b * 32 + 8 * j + 4 * g;
-          if (d < DHP) {
-            const u32x2 pk = {pack_bf16x2(o[qb][b][4 * j] * inv, o[qb][b][4 * j + 1] * inv),
-                              pack_bf16x2(o[qb][b][4 * j + 2] * inv, o[qb][b][4 * j + 3] * inv)};
-            *(u32x2*)(orow + d) = pk;
-          }
-        }
-    }
+  for (int p = 0; p < (32 * NCH + 63) / 64; ++p) {
+    const int item = min(p * 64 + lane, 32 * NCH - 1), row = item / NCH, ch = item % NCH;
+    const u32x2 lo = *(const u32x2*)(so + row * ROWB + ch * 16), hi = *(const u32x2*)(so + row * ROWB + ch * 16 + 8);
+    if (p * 64 + lane < 32 * NCH && w.q0 + wave * 32 + row < seg_end)
+      *(u32x4*)(obase + (size_t)row * a.ld_o + ch * 8) = u32x4{lo[0], lo[1], hi[0], hi[1]};
   }
 }
 
 }  // namespace
 
-int attention_q_block(int dtype_bf16, int dh_pad) { return !dtype_bf16 ? 64 : 128; }  // 32 * QB * NW
+int attention_q_block(int dtype_bf16, int dh_pad) { return !dtype_bf16 ? 64 : 128; }
+
+template <int DHP, bool DEEP>
+static hipError_t launch_attention_as(const AttnArgs& a, hipStream_t s) {
+  constexpr int smem = 2 * AttnShape<DHP>::STAGE;
+  auto kfn = attention_bf16_kernel<DHP, DEEP>;
+  static LdsLimitOnce lds_limit;  // raised once per kernel and device
+  if (hipError_t e = lds_limit.ensure((const void*)kfn, smem); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kfn, dim3(((a.n_work + 7) / 8) * 8, a.heads), dim3(256), smem, s, a);
+  return hipGetLastError();
+}
+
+template <int DHP>
+static hipError_t launch_attention_dh(const AttnArgs& a, hipStream_t s) {
+  // DEEP needs a third more registers, so a unit holds a workgroup less: three for four at head dim 64, two for three at 72 to
+  // 96.  It is the better one where workgroups are too few to hide a wave's chain behind other waves, in us against the
+  // other one: 577 tokens, 16 heads of 64: 1 image 9.6 and 11.8, 8 images 20.9 and 22.1, 35 (2800 workgroups) 65.7 and 66.7, 260
+  // 492 and 482; at the other head dims as long as it takes no more rounds of the units: 16 heads of 80, 6404 tokens (816)
+  // 266 and 280; 1601 tokens, 2 tiles (416) 40.1 and 41.9, 3 (624) 60.6 and 56.9, 4 (832) 74.9 and 77.0, 5 (1040) 92.3
+  // and 90.3.  At 128 both hold two and DEEP, a few registers short, is no faster.
+  if constexpr (DHP <= 96) {
+    const long n = (long)a.n_work * a.heads;
+    if (DHP == 64 ? n <= 3072 : (n + 511) / 512 <= (n + 767) / 768) return launch_attention_as<DHP, true>(a, s);
+  }
+  return launch_attention_as<DHP, false>(a, s);
+}
 
 hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s) {
   if (a.n_work <= 0) return hipSuccess;
   if ((a.qkv_rows == 0 && a.ld_qkv % 8 != 0) || a.ld_o % 8 != 0) return hipErrorInvalidValue;
-  const dim3 grid(((a.n_work + 7) / 8) * 8, a.heads);
-#define VIT_ATTN(DHP, QB, NW)                                                                            \
-  do {                                                                                                 \
-    constexpr int smem = 2 * AttnShape<DHP, QB, NW>::STAGE;                                            \
-    auto kfn = attention_bf16_kernel<DHP, QB, NW>;                                                     \
-    static LdsLimitOnce lds_limit; /* raised once per kernel and device */                             \
-    if (hipError_t e = lds_limit.ensure((const void*)kfn, smem); e != hipSuccess) return e;            \
-    hipLaunchKernelGGL(kfn, grid, dim3(AttnShape<DHP, QB, NW>::ANT), smem, s, a);                      \
-  } while (0)
   switch (a.dh_pad) {
-    case 64: VIT_ATTN(64, 1, 4); break;
-    case 72: VIT_ATTN(72, 1, 4); break;
-    case 80: VIT_ATTN(80, 1, 4); break;
-    case 96: VIT_ATTN(96, 1, 4); break;
-    case 128: VIT_ATTN(128, 1, 4); break;
+    case 64: return launch_attention_dh<64>(a, s);
+    case 72: return launch_attention_dh<72>(a, s);
+    case 80: return launch_attention_dh<80>(a, s);
+    case 96: return launch_attention_dh<96>(a, s);
+    case 128: return launch_attention_dh<128>(a, s);
     default: return hipErrorInvalidValue;
   }
-#undef VIT_ATTN
-  return hipGetLastError();
 }
 
 }  // namespace vitenc

@@ -63,3 +63,20 @@ def test_tile_heights_and_short_products(n, hidden, mlp):
         assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
     want, _ = O.vit_oracle_encode(cfg, w, px[-1:], [1], one)
     assert_parity(whole[-T:], want, "bf16", f"tile heights n={n} width={hidden}")
+
+
+@pytest.mark.parametrize("dh,heads,n", [(64, 16, 100), (72, 4, 70), (80, 4, 70), (96, 4, 70), (128, 4, 70)])
+def test_tokens_do_not_depend_on_the_attention_kernel(dh, heads, n):
+    """Two query blocks per image and head: the whole batch has more workgroups than the pipelined form of the attention kernel
+    takes, an image alone has 8 to 32.  170 keys: two full tiles, then one of more than 32 keys."""
+    cfg = dict(CFG, image_size=52, hidden=dh * heads, heads=heads, mlp=64, layers_local=1, proj_layers=0, proj_dims=())
+    say(f"case attention forms, head dim {dh}, {n} images of 170 tokens")
+    w, px = gen.make_weights(cfg, seed=6), gen.make_pixels(cfg, n, seed=dh)
+    whole, _ = gpu_encode(cfg, w, px, [n], np.arange(n + 1, dtype=np.int32))
+    T = gen.tokens_per_tile(cfg)
+    one = np.array([0, 1], dtype=np.int32)
+    for i in (0, n // 2, n - 1):
+        alone, _ = gpu_encode(cfg, w, px[i:i + 1], [1], one)
+        assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
+    want, _ = O.vit_oracle_encode(cfg, w, px[-1:], [1], one)
+    assert_parity(whole[-T:], want, "bf16", f"attention forms dh={dh}")

@@ -7,8 +7,7 @@
 // directly (global_load_lds_dwordx4) and are described where they are defined:
 // * gemm_bf16_pipe_kernel (most products, and the last rows of the other one's): one tile of 64 to 256 rows by 64 or
 //   128 columns per workgroup, a ring of two to four 64-wide k-stages;
-// * gemm_bf16_dma_kernel (products of many whole rounds of tiles): persistent, 256 x 256 tiles, eight waves of 128 x 64,
-//   two 64-wide k-stages.
+// * gemm_bf16_dma_kernel (products of many whole rounds of tiles): persistent, 256 x 256 tiles, eight waves of 128 x 64.
 // Which of them, and which tile, a product takes is decided by the time that each is expected to need (launch_gemm_bf16).
 // * LDS tiles are [row][64 bf16] with the 16-byte chunks XOR-swizzled by (row >> 1) & 7:
 //   LDS serves a 16-byte-per-lane read 16 lanes at a time over 64 banks, and this
@@ -175,15 +174,17 @@ struct WaveEpilogue {
 //
 // * One workgroup per compute unit walks a list of tiles.  Operand tiles go global -> LDS directly
 //   (global_load_lds_dwordx4: each lane supplies its own global offset, the wave writes 1 KiB of
-//   consecutive LDS = 8 rows) through two 64-wide k-stages of 64 KiB.  The stream of stages does
-//   not stop at tile boundaries, so the next tile's first stages land while the current tile
-//   finishes and its epilogue runs; no launch gap, no cold prologue per tile.
-// * A stage is multiplied in four 16-wide sub-steps, each reading the next sub-step's fragments
-//   while its own MFMAs run.  Before the last sub-step one wait + barrier establishes both that
-//   the other stage has landed and that nobody reads this stage's LDS any more; the last sub-step
-//   then reads the other stage's first fragments and issues the loads that refill this stage, one
-//   after each MFMA (a wave that issued them back to back would sit in the memory pipeline's
-//   back-pressure while the matrix core runs dry).
+//   consecutive LDS = 8 rows).  The stream of stages does not stop at tile boundaries, so the next
+//   tile's first stages land while the current tile finishes and its epilogue runs; no launch gap, no
+//   cold prologue per tile.
+// * LDS is five units of 32 KiB: three stages of A, two of W.  A stage is multiplied in four 16-wide sub-steps, each
+//   reading the next one's A fragments; the W fragments of all four are read in the first, so that W's unit is free
+//   after a quarter of the stage (a barrier says so) and A's after three (the stage's sync, which also says that the next
+//   stage has landed).  A unit's loads, two to a sub-step, thus have one and a half to two stages to land.  With two stages
+//   of both operands, in which a load had half a stage, a wait on the slowest of them set the pace wherever the L2 missed:
+//   51232 x 1280 x 5120 took 742 us and takes 668, 93312 x 4352 x 1152 917 and 878, 150020 x 1024 x 4096 1178 and 1115.
+// * All of that only without branches: with run-time tests around the loads the same stages took 5 % longer than the two
+//   of before, without them 2 to 10 % less (37 branches a stage).  Hence the STEADY form.
 // * LDS rows are 128 bytes; the 16-byte chunk index is XORed with (row >> 1) & 7, which the lane
 //   achieves by choosing which global chunk it loads, so any 16 consecutive rows of one logical
 //   chunk fall on 16 distinct 16-byte bank groups of the 64 banks.
@@ -192,19 +193,19 @@ struct WaveEpilogue {
 //   groups); consecutive groups along N go to consecutive XCDs, so the XCDs working at the same
 //   time share A rows (first fetch fills the memory-side cache for the others) and the 32 units of
 //   one XCD share both operands in its L2.
-// * Epilogue staging has its own 18 KiB of LDS (16 rows x 144 bytes per wave).
-constexpr int D_BM = 256, D_BN = 256, D_BK = 64, D_ST = 2;
-constexpr int D_ROW = D_BK * 2;                       // bytes per LDS row
-constexpr int D_STAGE_BYTES = (D_BM + D_BN) * D_ROW;  // 64 KiB
-constexpr int D_STAGING_ROW = 144, D_STAGING_BYTES = 8 * 16 * D_STAGING_ROW;
-constexpr int D_LDS_BYTES = D_ST * D_STAGE_BYTES + D_STAGING_BYTES;  // 146 KiB of the 160 KiB
+// * A wave's epilogue is staged (16 rows x 144 bytes) in the rows of A's dead unit that the wave itself refills next.
+constexpr int D_BM = 256, D_BN = 256, D_BK = 64;
+constexpr int D_ROW = D_BK * 2;                   // bytes per LDS row
+constexpr int D_UNIT_BYTES = 256 * D_ROW;         // one operand's rows of a stage: 32 KiB
+constexpr int D_LDS_BYTES = 5 * D_UNIT_BYTES;     // three units for A, two for W: all of the 160 KiB
+constexpr int D_STAGING_ROW = 144;
+static_assert(16 * D_STAGING_ROW <= 32 * D_ROW, "a wave stages its epilogue in the rows that it loads");
 constexpr int D_GROUP_M = 8, D_GROUP_N = 4;
-constexpr int D_LOADS = 8;  // direct-to-LDS instructions per wave and stage (4 for A, 4 for W), 8 rows each
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-// Epilogue of one wave of the persistent kernel: same register layout as wave_epilogue, but staged
+// Epilogue of one wave of the persistent kernel: same register layout as WaveEpilogue, but staged
 // 16 rows at a time through the wave's private 16 x 144-byte LDS rows (`st`).
 template <int EPI, bool STREAM_OUT, bool FULL>
 __device__ __forceinline__ void wave_epilogue_p(const GemmArgs& a, f32x16 (&acc)[4][2], unsigned char* st, int row0,
@@ -400,7 +401,6 @@ __global__ __launch_bounds__(512) void gemm_bf16_dma_kernel(const GemmArgs a, in
                                                             int groups_full, int narrow_w, int n_groups) {
   constexpr int FM = 4, FN = 2, TM = 128, TN = 64;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  unsigned char* staging = smem + D_ST * D_STAGE_BYTES;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps addresses in scalar registers
@@ -441,41 +441,38 @@ __global__ __launch_bounds__(512) void gemm_bf16_dma_kernel(const GemmArgs a, in
   const uint32_t offW0 = (uint32_t)(ld_row * a.ldw + ld_chunk * 8) * 2u;
   const uint32_t offW1 = (uint32_t)(ld_row * a.ldw + (ld_chunk ^ 4) * 8) * 2u;
   const size_t a_step = (size_t)16 * a.lda, w_step = (size_t)16 * a.ldw;  // bytes per 8 rows
-  const unsigned char *baseA = nullptr, *baseW = nullptr;  // load cursor: uniform tile bases at k = 0
-  int g_l = next_group(xcd), kt_l = 0;
-  auto set_load_tile = [&]() {
-    int tm, tn;
-    if (g_l < n_groups && tile_of(g_l, tm, tn)) {
-      baseA = (const unsigned char*)a.A + (size_t)tm * D_BM * a.lda * 2;
-      baseW = (const unsigned char*)a.W + (size_t)tn * D_BN * a.ldw * 2;
-    }
-  };
-  set_load_tile();
   // One direct-to-LDS instruction.  It is written as inline assembly so that the compiler's
-  // wait-count insertion, which cannot know that the stage written here is never one being read,
+  // wait-count insertion, which cannot know that the unit written here is never one being read,
   // does not fence every surrounding LDS read; completion is tracked by hand (sync_stage).  M0 holds
   // the LDS destination of lane 0.
-  auto dma16 = [&](const unsigned char* gbase, uint32_t goff, unsigned char* lptr) {
-    // low 32 bits of a generic LDS pointer = LDS offset; wave-uniform by construction
-    const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lptr);
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(goff), "s"(gbase)
-                 : "memory", "m0");
+  auto dma16 = [&](const unsigned char* gbase, uint32_t goff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(goff), "s"(gbase) : "memory", "m0");
   };
-  // instruction i of stage slot `st` at the load cursor: i in [0,4) -> A rows 8i.., [4,8) -> W rows 8(i-4)..
-  auto issue_load = [&](int st, int i) {
-    unsigned char* base = smem + st * D_STAGE_BYTES;
-    if (i < 4)
-      dma16(baseA + i * a_step + kt_l * D_ROW, (i & 1) ? offA1 : offA0, base + (wave * 32 + i * 8) * D_ROW);
-    else
-      dma16(baseW + (i - 4) * w_step + kt_l * D_ROW, (i & 1) ? offW1 : offW0,
-            base + D_BM * D_ROW + (wave * 32 + (i - 4) * 8) * D_ROW);
-  };
+  // load cursors, one per operand: the tile list position, the stage inside the tile, the tile's address at k = 0, the LDS
+  // unit that is filled next
   const int KT = a.K / D_BK;
-  auto advance_load_cursor = [&]() {
-    if (++kt_l == KT) {
-      kt_l = 0;
-      g_l = next_group(g_l + 8);
-      set_load_tile();
+  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + wave * 32 * D_ROW);  // (low 32 bits = LDS offset)
+  struct Cursor { int g, kt; const unsigned char* base; uint32_t unit; };
+  Cursor ca{next_group(xcd), 0, nullptr, 0}, cw = ca;
+  auto set_tile = [&](Cursor& c, bool is_a) {
+    int tm, tn;
+    if (c.g < n_groups && tile_of(c.g, tm, tn))
+      c.base = is_a ? (const unsigned char*)a.A + (size_t)tm * D_BM * a.lda * 2 : (const unsigned char*)a.W + (size_t)tn * D_BN * a.ldw * 2;
+  };
+  set_tile(ca, true);
+  set_tile(cw, false);
+  // instruction i of 4 (rows 32 wave + 8 i ..) of the operand's next stage
+  auto load_a = [&](int i) { dma16(ca.base + i * a_step, (i & 1) ? offA1 : offA0, lds_wave + ca.unit + i * 8 * D_ROW); };
+  auto load_w = [&](int i) {
+    dma16(cw.base + i * w_step, (i & 1) ? offW1 : offW0, lds_wave + 3 * D_UNIT_BYTES + cw.unit + i * 8 * D_ROW);
+  };
+  auto advance = [&](Cursor& c, bool is_a) {
+    c.unit = c.unit + D_UNIT_BYTES == (is_a ? 3u : 2u) * D_UNIT_BYTES ? 0 : c.unit + D_UNIT_BYTES;
+    c.base += D_ROW;
+    if (++c.kt == KT) {
+      c.kt = 0;
+      c.g = next_group(c.g + 8);
+      set_tile(c, is_a);
     }
   };
 
@@ -483,104 +480,116 @@ __global__ __launch_bounds__(512) void gemm_bf16_dma_kernel(const GemmArgs a, in
   //      with pos0 = lk ^ sw the chunk of sub-step ks is pos0 ^ 2ks, i.e. the byte offset XOR (ks << 5)
   const int sw = (lrow >> 1) & 7;
   const uint32_t fa_off = (uint32_t)((wm * TM + lrow) * D_ROW + ((lk ^ sw) << 4));
-  const uint32_t fb_off = (uint32_t)(D_BM * D_ROW + (wn * TN + lrow) * D_ROW + ((lk ^ sw) << 4));
+  const uint32_t fb_off = (uint32_t)(3 * D_UNIT_BYTES + (wn * TN + lrow) * D_ROW + ((lk ^ sw) << 4));
 
   f32x16 acc[FM][FN];
-  bf16x8 fa0[FM], fb0[FN], fa1[FM], fb1[FN];  // fragments of even / odd sub-steps
-
-  auto rd_a = [&](int st, int ks, int i) {
-    return *(const bf16x8*)(smem + st * D_STAGE_BYTES + (fa_off ^ (uint32_t)(ks << 5)) + i * 32 * D_ROW);
+  bf16x8 fa0[FM], fa1[FM], fb[4][FN];  // A fragments of even / odd sub-steps, W fragments of all four
+  uint32_t ua = 0, uw = 0;             // byte offsets of the stage being multiplied in A's and in W's units
+  auto rd_a = [&](uint32_t unit, int ks, int i) {
+    return *(const bf16x8*)(smem + unit + (fa_off ^ (uint32_t)(ks << 5)) + i * 32 * D_ROW);
   };
-  auto rd_b = [&](int st, int ks, int j) {
-    return *(const bf16x8*)(smem + st * D_STAGE_BYTES + (fb_off ^ (uint32_t)(ks << 5)) + j * 32 * D_ROW);
+  auto rd_b = [&](uint32_t unit, int ks, int j) {
+    return *(const bf16x8*)(smem + unit + (fb_off ^ (uint32_t)(ks << 5)) + j * 32 * D_ROW);
   };
   auto mm = [&](int i, const bf16x8& x, const bf16x8 (&w)[FN]) {
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[j], x, acc[i][j], 0, 0, 0);
   };
 
-  // ---- how many k-stages this workgroup will load in total
+  // ---- how many k-stages this workgroup multiplies in total
   int n_my_tiles = 0;
   for (int g = next_group(xcd); g < n_groups; g = next_group(g + 8)) ++n_my_tiles;
   const int total_stages = n_my_tiles * KT;
-  int issued = 0, consumed = 0;  // k-stages issued to the ring / multiplied so far
-  int st_c = 0;                  // ring slot of the stage being multiplied
+  int stage = 0;  // the one being multiplied
 
-  // Every load this wave has issued has landed and every LDS read it has issued is complete; then
-  // meet the other waves.  (The vector-memory counter also counts the epilogue's stores.)
-  auto sync_stage = [&]() {
-    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  // One 64-wide k-stage.  On entry fa0 / fb[0] hold the fragments of its sub-step 0.
+  //   sub-step 0: the W fragments of the other three sub-steps are read, and A's of the next;
+  //   barrier:    every wave has its W fragments, W's unit is dead: it takes W of stage + 2 (one load per MFMA pair);
+  //   sub-step 2: reads the last A fragments;
+  //   sync:       stage + 1 has landed for every wave (A and W of stage + 2 may be in flight), A's unit is dead: it takes A
+  //               of stage + 3, in sub-step 3, which reads the next stage's first fragments.
+  // last = a tile's last stage: the loads of A wait until the epilogue has used the unit; in the residual kernel the next
+  // tile's first fragments are read behind the epilogue, too, which needs their registers for residual values.
+  bool pend_a = false;  // the second half of A's loads is still to be issued
+  // STEADY: no tile end, and the stages whose loads go out exist: no branch but the cursors'
+  auto k_stage = [&](auto steady_tag, const bool last) {
+    constexpr bool STEADY = decltype(steady_tag)::value;
+    const uint32_t una = ua + D_UNIT_BYTES == 3u * D_UNIT_BYTES ? 0 : ua + D_UNIT_BYTES, unw = uw ^ D_UNIT_BYTES;
+    const bool more_w = STEADY || stage + 2 < total_stages, more_a = STEADY || (stage + 3 < total_stages && !last);
+    const bool ahead = STEADY || (stage + 1 < total_stages && !(last && EPI == EPI_BIAS_RESIDUAL)), pend = STEADY || pend_a;
+    fa1[0] = rd_a(ua, 1, 0); fb[1][0] = rd_b(uw, 1, 0); fb[1][1] = rd_b(uw, 1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      mm(i, fa0[i], fb[0]);
+      if (i + 1 < FM) fa1[i + 1] = rd_a(ua, 1, i + 1);
+      if (i < 2) { fb[2 + i][0] = rd_b(uw, 2 + i, 0); fb[2 + i][1] = rd_b(uw, 2 + i, 1); }
+      if ((i & 1) && pend) load_a(2 + (i >> 1));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (pend) advance(ca, true);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      mm(i, fa1[i], fb[1]);
+      fa0[i] = rd_a(ua, 2, i);
+      if (i == 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC27F);  // lgkmcnt(2): the last reads of fa1 and of fa0 so far came behind those of fb
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if ((i & 1) && more_w) load_w(i >> 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i) fa1[i] = rd_a(ua, 3, i);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      mm(i, fa0[i], fb[2]);
+      if (!(i & 1) && more_w) load_w(2 + (i >> 1));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (more_w) advance(cw, false);
+    if (more_w) __builtin_amdgcn_s_waitcnt(0x0078);  // vmcnt(8) lgkmcnt(0)
+    else __builtin_amdgcn_s_waitcnt(0x0070);         // vmcnt(0) lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
-  };
-
-  // One sub-step that multiplies fragment set (x, w) while reading sub-step `ks` of stage `st`
-  // into (nx, nw); with `late` set, load instructions late0 .. late0 + 3 of the stage being
-  // prefetched follow the four MFMA pairs.  sched_barrier(0) fences keep each group's instructions
-  // together in this order.
-  auto sub_step = [&](int st, int ks, const bf16x8 (&x)[FM], const bf16x8 (&w)[FN], bf16x8 (&nx)[FM],
-                      bf16x8 (&nw)[FN], bool late, int late0) {
-    nw[0] = rd_b(st, ks, 0); nw[1] = rd_b(st, ks, 1);
-    nx[0] = rd_a(st, ks, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (ahead) { fb[0][0] = rd_b(unw, 0, 0); fb[0][1] = rd_b(unw, 0, 1); fa0[0] = rd_a(una, 0, 0); }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      mm(i, x[i], w);
-      if (i + 1 < FM) nx[i + 1] = rd_a(st, ks, i + 1);
-      if (late) issue_load(st ^ 1, late0 + i);
+      mm(i, fa1[i], fb[3]);
+      if (ahead && i + 1 < FM) fa0[i + 1] = rd_a(una, 0, i + 1);
+      if ((i & 1) && more_a) load_a(i >> 1);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (!STEADY) pend_a = more_a;
+    ua = una;
+    uw = unw;
+    ++stage;
   };
 
-  // One 64-wide k-stage.  On entry fa0 / fb0 hold the fragments of its sub-step 0.
-  //   sub-steps 0..2: MFMAs of sub-step j while the fragments of sub-step j + 1 are read;
-  //   sync:           the other stage has landed for every wave and this stage's LDS is dead;
-  //   sub-step 3:     its MFMAs while sub-step 0 of the other stage is read and the first four loads
-  //                   of the stage after that go into the slot this stage just freed, one per MFMA
-  //                   pair; the other four follow in sub-step 0 of the next stage (eight in a row
-  //                   would queue up in the memory pipeline and hold back the MFMAs behind them).
-  bool pend = false;  // the second half of a stage's loads is still to be issued
-  // AHEAD = false (a tile's last stage in the residual kernel): the next tile's first fragments are not read
-  // here but after the epilogue, which needs their registers for residual values in flight.
-  auto k_stage = [&](auto load_tag, auto next_tag, const bool AHEAD) {
-    constexpr bool LOAD = decltype(load_tag)::value, NEXT = decltype(next_tag)::value;
-    const int sn = st_c ^ 1;
-    sub_step(st_c, 1, fa0, fb0, fa1, fb1, pend, 4);
-    if (pend) { advance_load_cursor(); pend = false; }
-    sub_step(st_c, 2, fa1, fb1, fa0, fb0, false, 0);
-    // the last fragments of this stage are read up front so that they are complete at the barrier
-    fb1[0] = rd_b(st_c, 3, 0); fb1[1] = rd_b(st_c, 3, 1);
+  // ---- prologue: A of three stages, W of two, in the order in which the stages above would have asked for them
 #pragma unroll
-    for (int i = 0; i < FM; ++i) fa1[i] = rd_a(st_c, 3, i);
-    __builtin_amdgcn_sched_barrier(0);
+  for (int st = 0; st < 3; ++st) {
+    if (st < total_stages) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i) mm(i, fa0[i], fb0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (NEXT) sync_stage();
-    __builtin_amdgcn_sched_barrier(0);
-    if (NEXT && AHEAD) { fb0[0] = rd_b(sn, 0, 0); fb0[1] = rd_b(sn, 0, 1); fa0[0] = rd_a(sn, 0, 0); }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      mm(i, fa1[i], fb1);
-      if (NEXT && AHEAD && i < FM - 1) fa0[i + 1] = rd_a(sn, 0, i + 1);
-      if (LOAD) issue_load(st_c, i);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < (st < 2 ? 4 : 2); ++i) load_a(i);
+      if (st < 2) advance(ca, true);
+      else pend_a = true;
     }
-    if (LOAD) { pend = true; ++issued; }
-    ++consumed;
-    st_c = sn;
-  };
-
-  // ---- prologue: fill both stages, wait for them, read the first fragments
-  for (int i = 0; i < D_ST && issued < total_stages; ++i) {
+    if (st < 2 && st < total_stages) {
 #pragma unroll
-    for (int j = 0; j < D_LOADS; ++j) issue_load(i, j);
-    advance_load_cursor();
-    ++issued;
+      for (int i = 0; i < 4; ++i) load_w(i);
+      advance(cw, false);
+    }
   }
   if (total_stages > 0) {
-    sync_stage();
-    fb0[0] = rd_b(0, 0, 0); fb0[1] = rd_b(0, 0, 1);
+    if (total_stages >= 3) __builtin_amdgcn_s_waitcnt(0x007A);  // vmcnt(10): stage 0 has landed
+    else __builtin_amdgcn_s_waitcnt(0x0070);
+    __builtin_amdgcn_s_barrier();
+    fb[0][0] = rd_b(0, 0, 0); fb[0][1] = rd_b(0, 0, 1);
 #pragma unroll
     for (int i = 0; i < FM; ++i) fa0[i] = rd_a(0, 0, i);
   }
@@ -600,35 +609,38 @@ __global__ __launch_bounds__(512) void gemm_bf16_dma_kernel(const GemmArgs a, in
       for (int j = 0; j < FN; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    // stages that still prefetch one; then (only at the end of the list) a stage that only reads
-    // ahead; then the very last stage of the list, which has nothing after it
-    const int n_ld = min(KT, total_stages - issued);
-    const int n_nx = min(KT, total_stages - 1 - consumed);
     constexpr bool RESID = EPI == EPI_BIAS_RESIDUAL;
-    const std::true_type T{};
-    const std::false_type F{};
-    // (wave-uniform run-time flag: a compile-time variant of the last stage would merge three copies of the
-    //  accumulators' live ranges and spill)
-    for (int kt = 0; kt < n_ld; ++kt) k_stage(T, T, !RESID || kt != KT - 1);
-    for (int kt = n_ld; kt < n_nx; ++kt) k_stage(F, T, !RESID || kt != KT - 1);
-    for (int kt = max(n_ld, n_nx); kt < KT; ++kt) k_stage(F, F, true);
+    unsigned char* staging = smem;
+    const int steady = pend_a ? min(KT - 1, total_stages - 3 - stage) : 0;
+    int kt = 0;
+    for (; kt < steady; ++kt) k_stage(std::true_type{}, false);
+    for (; kt < KT; ++kt) {
+      if (kt == KT - 1) staging = smem + ua + wave * 32 * D_ROW;  // A's unit of the last stage: dead behind its sync, refilled below
+      k_stage(std::false_type{}, kt == KT - 1);
+    }
     if constexpr (RESID) {  // the fragment registers are dead across the epilogue: say so
 #pragma unroll
       for (int i = 0; i < FM; ++i) fa0[i] = bf16x8{};
-      fb0[0] = bf16x8{}; fb0[1] = bf16x8{};
+      fb[0][0] = bf16x8{}; fb[0][1] = bf16x8{};
     }
     asm volatile("" ::: "memory");  // keep the epilogue's loads below the k-loop
     if (a.tile_stamps) stamp_t1 = wall_clock64();
     // a wave's 128 x 64 block lies wholly inside the matrix for all but the last row block / a ragged last column
     if (row0 + TM <= a.M && ncol0 + TN <= a.N)
-      wave_epilogue_p<EPI, STREAM_OUT, true>(a, acc, staging + wave * 16 * D_STAGING_ROW, row0, ncol0, lane);
+      wave_epilogue_p<EPI, STREAM_OUT, true>(a, acc, staging, row0, ncol0, lane);
     else
-      wave_epilogue_p<EPI, STREAM_OUT, false>(a, acc, staging + wave * 16 * D_STAGING_ROW, row0, ncol0, lane);
+      wave_epilogue_p<EPI, STREAM_OUT, false>(a, acc, staging, row0, ncol0, lane);
+    if (stage + 2 < total_stages) {  // the loads of A that the last stage held back: into the rows that only this wave has staged in
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      load_a(0);
+      load_a(1);
+      pend_a = true;
+    }
     if constexpr (RESID) {  // the next tile's first fragments (its first stage landed before the last sync)
-      if (consumed < total_stages) {
-        fb0[0] = rd_b(st_c, 0, 0); fb0[1] = rd_b(st_c, 0, 1);
+      if (stage < total_stages) {
+        fb[0][0] = rd_b(uw, 0, 0); fb[0][1] = rd_b(uw, 0, 1);
 #pragma unroll
-        for (int i = 0; i < FM; ++i) fa0[i] = rd_a(st_c, 0, i);
+        for (int i = 0; i < FM; ++i) fa0[i] = rd_a(ua, 0, i);
       }
     }
     if (a.tile_stamps) {
@@ -863,20 +875,21 @@ hipError_t launch_pipe_as(const GemmArgs& a, hipStream_t s) {
 // each of 256 units; a stage takes `alone` with few units at work and `full` with all of them (the clock falls), and a
 // round has a fixed time of its own and an epilogue by its kind: bias, bias + GELU, residual or patch rows.  Fitted to
 // the times of 20 encoder products (out-proj, QKV, fc1 and fc2 at widths of 768, 1024, 1152, 1280 and 3200, so 768 to
-// 12 800 columns and stages of 12 to 200) at 16 sizes each of 197 to 160 000 rows, weighted towards the tiles that are near
-// the best one: the tile chosen is on average 1 % slower than the best of the ten, and 12 % faster than the predecessor.
+// 12 800 columns and stages of 12 to 200) at 18 sizes each of 197 to 160 000 rows, weighted towards the tiles that are near
+// the best one: the tile chosen is on average 1 % slower than the best of the ten.  (Two launches of the choice that this one
+// replaced, by numbers of tiles alone and with 256 x 256, 128 x 128, 64 x 128 and 64 x 64 to choose from, took 13 % longer.)
 struct TileTime { int bm, bn, per_unit; float alone, full, fixed, epilogue[3]; };
 constexpr float LAUNCH_US = 1.8f;
 constexpr TileTime PIPE_TILES[] = {
-    {64, 64, 2, 0.187f, 0.401f, 1.2f, {0.0f, 0.1f, 0.3f}},
-    {64, 128, 1, 0.195f, 0.339f, 1.1f, {1.2f, 1.3f, 1.8f}},
-    {96, 128, 1, 0.270f, 0.442f, 0.9f, {0.7f, 2.3f, 3.3f}},
-    {128, 128, 1, 0.303f, 0.508f, 0.0f, {2.7f, 3.5f, 6.2f}},
-    {160, 128, 1, 0.279f, 0.605f, 3.3f, {0.0f, 1.7f, 5.3f}},
-    {192, 128, 1, 0.335f, 0.702f, 2.0f, {0.8f, 2.2f, 6.9f}},
-    {256, 128, 1, 0.393f, 0.868f, 2.8f, {1.2f, 2.7f, 8.8f}},
-    {160, 128, 2, 0.731f, 1.160f, 2.1f, {0.4f, 1.3f, 4.6f}},
-    {192, 128, 2, 0.782f, 1.319f, 1.2f, {1.0f, 1.9f, 6.0f}},
+    {64, 64, 2, 0.191f, 0.374f, 1.3f, {0.0f, 0.0f, 0.1f}},
+    {64, 128, 1, 0.204f, 0.331f, 2.1f, {0.0f, 0.0f, 0.2f}},
+    {96, 128, 1, 0.319f, 0.415f, 1.4f, {0.0f, 1.1f, 2.0f}},
+    {128, 128, 1, 0.310f, 0.500f, 1.7f, {0.0f, 0.6f, 2.7f}},
+    {160, 128, 1, 0.284f, 0.605f, 2.5f, {0.0f, 1.3f, 4.4f}},
+    {192, 128, 1, 0.315f, 0.707f, 1.8f, {0.0f, 1.1f, 5.1f}},
+    {256, 128, 1, 0.312f, 0.880f, 2.7f, {0.0f, 1.2f, 6.9f}},
+    {160, 128, 2, 0.759f, 1.142f, 0.0f, {1.1f, 2.0f, 5.0f}},
+    {192, 128, 2, 0.768f, 1.278f, 0.0f, {1.6f, 2.5f, 6.2f}},
 };
 constexpr int PIPE_TILE_COUNT = sizeof(PIPE_TILES) / sizeof(PIPE_TILES[0]);
 
@@ -891,7 +904,7 @@ float pipe_time(const TileTime& t, int kind, long M, long N, int stages) {
     }
     if (c <= 256) return t.fixed + stages * t.alone + t.epilogue[kind] * (0.3f + 0.7f * c / 256.0f);
     const float u = (c - 256) / 256.0f;
-    return t.fixed + stages * (t.alone + (t.full - t.alone) * (0.5f + 0.5f * u)) + t.epilogue[kind] * (1.0f + u);
+    return t.fixed + stages * (t.alone + (t.full - t.alone) * (0.85f + 0.15f * u)) + t.epilogue[kind] * (1.0f + u);
   };
   return LAUNCH_US + (n / cap) * round(cap) + (n % cap ? round(n % cap) : 0.0f);
 }
@@ -936,13 +949,14 @@ Walk persistent_walk(long M, long N) {
   return w;
 }
 
-constexpr TileTime PERSISTENT_TILE = {256, 256, 1, 0.930f, 1.612f, 5.7f, {3.1f, 5.4f, 17.5f}};
+constexpr TileTime PERSISTENT_TILE = {256, 256, 1, 0.675f, 1.513f, 4.5f, {4.3f, 7.2f, 17.2f}};
+constexpr float NARROW_GROUP = 0.11f;  // what the groups of a remainder's columns take longer than those of a band
 float persistent_time(int kind, long M, long N, int stages) {
   const Walk w = persistent_walk(M, N);
   const int rounds = (w.n_groups + 7) / 8;
-  const float u = (float)w.tiles_m * w.tiles_n / (256.0f * rounds);
+  const float u = (float)w.tiles_m * w.tiles_n / (256.0f * rounds), narrow = (float)(w.n_groups - w.groups_full) / w.n_groups;
   const TileTime& t = PERSISTENT_TILE;
-  return LAUNCH_US + t.fixed + rounds * (stages * (t.alone + (t.full - t.alone) * u) + t.epilogue[kind]);
+  return LAUNCH_US + t.fixed + rounds * (stages * (t.alone + (t.full - t.alone) * u) + t.epilogue[kind]) * (1.0f + NARROW_GROUP * narrow);
 }
 
 constexpr int PERSISTENT_GRID = 8 * D_GROUP_M * D_GROUP_N;  // one workgroup per compute unit: 8 XCDs x 32 slots

@@ -881,7 +881,7 @@ hipError_t launch_pipe_as(const GemmArgs& a, hipStream_t s) {
 struct TileTime { int bm, bn, per_unit; float alone, full, fixed, epilogue[3]; };
 constexpr float LAUNCH_US = 1.8f;
 constexpr TileTime PIPE_TILES[] = {
-    {64, 64, 2, 0.191f, 0.374f, 1.3f, {0.0f, 0.0f, 0.1f}},
+    {64, 64, 2, 0.191f, 0.389f, 1.6f, {0.0f, 0.0f, 0.1f}},
     {64, 128, 1, 0.204f, 0.331f, 2.1f, {0.0f, 0.0f, 0.2f}},
     {96, 128, 1, 0.319f, 0.415f, 1.4f, {0.0f, 1.1f, 2.0f}},
     {128, 128, 1, 0.310f, 0.500f, 1.7f, {0.0f, 0.6f, 2.7f}},

@@ -1,15 +1,36 @@
 // Memory-bound row kernels: LayerNorm (fp32 residual stream -> matrix operand), patch
 // gather, CLS rows, padding fill.  All are HBM-bound; each element is read once and
 // written once with 16-byte accesses where the layout allows.
+#include <type_traits>
+
 #include "common.h"
 
 namespace vitenc {
 
 namespace {
 
+// The sum over a wave, in every lane: the butterfly over lanes 32, 16, 8, 4, 2 and 1 apart, moved by the vector unit itself
+// (halves of a wave and of a half exchanged; then rotations within rows of 16, which reach the same partner's value because
+// it repeats every 8, 4 and 2 lanes by then).  Each of the six steps through the LDS unit instead is a latency of its own
+// in the chain that a launch of a few hundred rows consists of, twice a row: 577 rows of 1024 columns 3.33 us a launch so and
+// 3.07 now, 4616 rows 7.29 and 6.55 (with the loads below, which no longer wait for each other).
 __device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  // (the two words are taken out of the vector before the cast: cast in place, both became its first element)
+  auto add_words = [](auto pair) {
+    const uint32_t lo = pair[0], hi = pair[1];
+    return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+  };
+  uint32_t u = __builtin_bit_cast(uint32_t, v);
+  v = add_words(__builtin_amdgcn_permlane32_swap(u, u, false, false));
+  u = __builtin_bit_cast(uint32_t, v);
+  v = add_words(__builtin_amdgcn_permlane16_swap(u, u, false, false));
+  auto rotated = [](float x, auto n) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + decltype(n)::value, 0xF, 0xF, false));
+  };
+  v += rotated(v, std::integral_constant<int, 8>{});
+  v += rotated(v, std::integral_constant<int, 4>{});
+  v += rotated(v, std::integral_constant<int, 2>{});
+  v += rotated(v, std::integral_constant<int, 1>{});
   return v;
 }
 
@@ -28,36 +49,40 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float* __restrict_
   if (reverse) row = rows - 1 - row;
   const float* xr = x + (size_t)row * ldx;
   f32x4 v[MAXV];
+  // Up to 1280 columns (SHORT) those past the row are read at its last ones and set to zero: with a branch around each load
+  // the compiler waited for one before it issued the next.  Wider rows are bound by HBM, and there the loads count (3200
+  // columns: 20.5 us a launch of 5125 rows with them, 19.6 without).
+  constexpr bool SHORT = MAXV <= 5;
+  auto column = [&](int i) { return SHORT ? min((i * 64 + lane) * 4, D - 4) : (i * 64 + lane) * 4; };
 #pragma unroll
   for (int i = 0; i < MAXV; ++i) {
-    const int c = (i * 64 + lane) * 4;
-    if (c < D) {
-      // STREAM_IN: x is larger than the memory-side cache; it is read once here and non-temporally, so that
-      // it does not displace operands (-1 % on the large encode step).  A small x sits in L2, where the hint
-      // costs 2-5 %.  (Compile-time: a run-time choice between the two loads gets merged into one plain load.)
-      if constexpr (STREAM_IN) v[i] = __builtin_nontemporal_load((const f32x4*)(xr + c));
-      else v[i] = *(const f32x4*)(xr + c);
-    } else {
+    if (!SHORT && column(i) >= D) {
       v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      continue;
     }
+    // STREAM_IN: x is larger than the memory-side cache; it is read once here and non-temporally, so that
+    // it does not displace operands (-1 % on the large encode step).  A small x sits in L2, where the hint
+    // costs 2-5 %.  (Compile-time: a run-time choice between the two loads gets merged into one plain load.)
+    if constexpr (STREAM_IN) v[i] = __builtin_nontemporal_load((const f32x4*)(xr + column(i)));
+    else v[i] = *(const f32x4*)(xr + column(i));
   }
-  // Up to 1280 columns the gains and shifts are asked for before the row's sums are formed: a launch of a few hundred rows
+  // The gains and shifts of such rows are asked for before the row's sums are formed: a launch of a few hundred rows
   // is one chain of memory latencies, and behind the sums they would be another link of it (one image, 49 launches: the encode
   // 1919 -> 1846 us; 35 images 15453 -> 15265).  Wider rows would
-  // hold them in as many registers as the row itself, and are bound by HBM.
-  constexpr bool EARLY = NORMALIZE && MAXV <= 5;
+  // hold them in as many registers as the row itself.
+  constexpr bool EARLY = NORMALIZE && SHORT;
   f32x4 ge[EARLY ? MAXV : 1], be[EARLY ? MAXV : 1];
   if constexpr (EARLY) {
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
-      const int c = (i * 64 + lane) * 4;
-      if (c < D) {
-        ge[i] = *(const f32x4*)(gamma + c);
-        be[i] = *(const f32x4*)(beta + c);
-      }
+      ge[i] = *(const f32x4*)(gamma + column(i));
+      be[i] = *(const f32x4*)(beta + column(i));
     }
     __builtin_amdgcn_sched_barrier(0);
   }
+#pragma unroll
+  for (int i = 0; i < MAXV; ++i)
+    if (SHORT && (i * 64 + lane) * 4 >= D) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   float mean = 0.f, rstd = 1.f;
   if (NORMALIZE) {
     float s = 0.f;

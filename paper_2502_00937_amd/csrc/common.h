@@ -131,26 +131,42 @@ struct GemmArgs {
                       //   attention kernel reads); ldo is not used
 };
 
-// Applies one epilogue of the fp32 path to four neighbouring accumulators of one row; the caller guarantees
-// row < M, col < N, and that col, N and the leading dimensions are multiples of 4.
+// One epilogue of the fp32 path for four neighbouring accumulators of one row: what it reads (bias, residual or position
+// values) is asked for by fetch, ahead of the product whose result it needs no sooner.  Rows and columns past the matrix
+// are read at its last ones; only the caller of store guarantees row < M, col < N.  col, N and the leading dimensions
+// are multiples of 4.
 template <int EPI>
-__device__ __forceinline__ void epilogue_store4_f32(const GemmArgs& a, int row, int col, const f32x4 acc) {
-  f32x4 v = acc + *(const f32x4*)(a.bias + col);
-  if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) {
+struct Epilogue4F32 {
+  f32x4 bias, add;
+  float* dst;
+  __device__ __forceinline__ void fetch(const GemmArgs& a, int row, int col) {
+    row = row < a.M ? row : a.M - 1;
+    col = col < a.N ? col : a.N - 4;
+    bias = *(const f32x4*)(a.bias + col);
+    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) {
+      dst = (float*)a.out + (size_t)row * a.ldo + col;
+    } else if constexpr (EPI == EPI_BIAS_RESIDUAL) {
+      dst = a.resid + (size_t)row * a.ldo + col;
+      add = *(const f32x4*)dst;
+    } else {  // EPI_PATCH
+      const int tile = row / a.patches, tok = a.cls + (row - tile * a.patches);
+      dst = a.resid + ((size_t)tile * a.tokens + tok) * a.ldo + col;
+      add = *(const f32x4*)(a.pos + (size_t)tok * a.ldo + col);
+    }
+  }
+  __device__ __forceinline__ void store(const f32x4 acc) const {
+    f32x4 v = acc + bias;
     if constexpr (EPI == EPI_BIAS_GELU) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
+    } else if constexpr (EPI == EPI_BIAS_RESIDUAL) {
+      v = add + v;
+    } else if constexpr (EPI == EPI_PATCH) {
+      v = v + add;
     }
-    *(f32x4*)((float*)a.out + (size_t)row * a.ldo + col) = v;
-  } else if constexpr (EPI == EPI_BIAS_RESIDUAL) {
-    f32x4* p = (f32x4*)(a.resid + (size_t)row * a.ldo + col);
-    *p += v;
-  } else {  // EPI_PATCH
-    const int tile = row / a.patches;
-    const int tok = a.cls + (row - tile * a.patches);
-    *(f32x4*)(a.resid + ((size_t)tile * a.tokens + tok) * a.ldo + col) = v + *(const f32x4*)(a.pos + (size_t)tok * a.ldo + col);
+    *(f32x4*)dst = v;
   }
-}
+};
 
 constexpr int kTileStampSlots = 64;  // tiles per workgroup whose phases are recorded
 

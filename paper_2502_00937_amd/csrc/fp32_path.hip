@@ -17,7 +17,7 @@ namespace {
 // transposed, so a lane holds four consecutive columns of one row per register quad.  A row's sums are formed in the
 // same order whatever F is, so a token does not depend on the tile size its launch took.
 // Operand rows are padded by the host so tile loads never leave the buffers.
-// Measured on four 197-token images, width 192 (M = 788): out-proj and fc2 7.4 us on average, QKV 7.4, fc1 12.6; the
+// Measured on four 197-token images, width 192 (M = 788): out-proj and fc2 7.4 us on average, QKV 7.4, fc1 12.5; the
 // predecessor (64 x 64 tile, VALU multiply-adds, one 16-wide k-step in flight) took 34, 16.6 and 18.5.  The error of
 // the encoder against 64 bits is 3.5e-7 (6.5e-7 before: four shorter chains instead of one).
 template <int EPI, int F>
@@ -55,6 +55,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs a) {
   const int KB = a.K / 64;
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) load(d, min(d, KB - 1));
+  // eight lanes finish a row of each 32 x 32 block; on 32 x 32 tiles, what they need for it (bias, residual or position rows)
+  // is asked for here and not behind the sums (encode of four images 618 -> 600 us); 64 x 64 ones have no registers for it
+  const int er = tid >> 3, ec = (tid & 7) * 4;
+  Epilogue4F32<EPI> epilogue;
+  if constexpr (F == 1) {
+    epilogue.fetch(a, m0 + er, n0 + ec);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   for (int k0 = 0; k0 < KB; k0 += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
@@ -85,11 +93,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs a) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < F; ++i) {
-      const int r = i * 32 + (tid >> 3), c = (tid & 7) * 4;
-      const int row = m0 + r, col = n0 + j * 32 + c;
-      const f32x4 v = (*(const f32x4*)&red[0][r][c] + *(const f32x4*)&red[1][r][c]) +
-                      (*(const f32x4*)&red[2][r][c] + *(const f32x4*)&red[3][r][c]);
-      if (row < a.M && col < a.N) epilogue_store4_f32<EPI>(a, row, col, v);
+      const int r = i * 32 + er;
+      const int row = m0 + r, col = n0 + j * 32 + ec;
+      const f32x4 v = (*(const f32x4*)&red[0][r][ec] + *(const f32x4*)&red[1][r][ec]) +
+                      (*(const f32x4*)&red[2][r][ec] + *(const f32x4*)&red[3][r][ec]);
+      if (row < a.M && col < a.N) {
+        if constexpr (F > 1) epilogue.fetch(a, row, col);
+        epilogue.store(v);
+      }
     }
   }
 }

@@ -19,6 +19,7 @@ struct PrepArgs {
   const unsigned char* img;
   float* out;
   int H, W, C, S, rows, cols, thumb;
+  float tile_y, tile_x, thumb_y, thumb_x;  // source pixels per canvas pixel: of the tiles' canvas, of the thumbnail's
   float scale[4], shift[4];  // out = tap * scale[c] + shift[c]: 1/(255 std) and -mean/std
 };
 
@@ -32,15 +33,15 @@ __device__ __forceinline__ void taps(int o, float ratio, int n_in, int& i0, int&
   w = src - (float)i0;
 }
 
-// Canvas coordinates of the first pixel of a thread's run, and the size its canvas is resized to; the thumbnail (if any) is
+// Canvas coordinates of the first pixel of a thread's run, and the source pixels per canvas pixel; the thumbnail (if any) is
 // the last tile.
-struct Place { int oy, ox, out_h, out_w; };
+struct Place { int oy, ox; float ratio_y, ratio_x; };
 __device__ __forceinline__ Place place(const PrepArgs& a, int tile, int y, int x) {
   if (tile < a.rows * a.cols) {  // a tile of the (rows*S) x (cols*S) canvas
     const int ty = tile / a.cols, tx = tile - ty * a.cols;
-    return {ty * a.S + y, tx * a.S + x, a.rows * a.S, a.cols * a.S};
+    return {ty * a.S + y, tx * a.S + x, a.tile_y, a.tile_x};
   }
-  return {y, x, a.S, a.S};  // the whole image at S x S
+  return {y, x, a.thumb_y, a.thumb_x};  // the whole image at S x S
 }
 
 __device__ __forceinline__ float blend(float p00, float p01, float p10, float p11, float wx, float wy, float scale, float shift) {
@@ -58,8 +59,8 @@ __global__ __launch_bounds__(256) void preprocess_kernel(const PrepArgs a) {
   const Place pl = place(a, tile, y, x);
   int y0, y1, x0, x1;
   float wy, wx;
-  taps(pl.oy, (float)a.H / (float)pl.out_h, a.H, y0, y1, wy);
-  taps(pl.ox, (float)a.W / (float)pl.out_w, a.W, x0, x1, wx);
+  taps(pl.oy, pl.ratio_y, a.H, y0, y1, wy);
+  taps(pl.ox, pl.ratio_x, a.W, x0, x1, wx);
   const unsigned char* r0 = a.img + (size_t)y0 * a.W * a.C;
   const unsigned char* r1 = a.img + (size_t)y1 * a.W * a.C;
   float* o = a.out + ((size_t)tile * a.C * a.S + y) * a.S + x;
@@ -69,36 +70,50 @@ __global__ __launch_bounds__(256) void preprocess_kernel(const PrepArgs a) {
 
 // Four neighbouring output pixels per thread.  A pixel's two horizontal taps are neighbours in the interleaved image, at
 // most 8 bytes together: one 8-byte load (any alignment) per pixel and row in place of 4 C single bytes, and 16-byte
-// stores.  The single-byte form was bound by its 12 loads and 3 stores a pixel: an 896 x 896 image to 4 tiles of 448
-// and a thumbnail (14.5 MB moved) takes 6.6 us, launch included, against 10.3.
-// A window that would reach past the image's last byte starts earlier and is shifted down.
+// stores.  What bounds it then are vector instructions, so the taps' places in their window are constants: at the right edge,
+// where the second tap is the first one again, it is the next bytes (whatever they are) with weight 0; and only a window
+// that would reach past the image's last byte starts earlier and is shifted down.  An 896 x 896 image to 4 tiles of 448 and
+// a thumbnail (14.5 MB moved) takes 5.6 us, launch included, on shifted taps 5.8.
 template <int C>
 __global__ __launch_bounds__(256) void preprocess_quad_kernel(const PrepArgs a) {
   const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (idx >= a.S * a.S) return;
-  const int y = idx / a.S, x = idx - y * a.S;
+  // idx / S: the quotient of a float reciprocal is off by at most one below 2^22 rows
+  int y = (int)((float)idx * __builtin_amdgcn_rcpf((float)a.S)), x = idx - y * a.S;
+  if (x < 0) { --y; x += a.S; }
+  if (x >= a.S) { ++y; x -= a.S; }
   const int tile = blockIdx.y;
   const Place pl = place(a, tile, y, x);
   int y0, y1;
   float wy;
-  taps(pl.oy, (float)a.H / (float)pl.out_h, a.H, y0, y1, wy);
-  const float ratio_x = (float)a.W / (float)pl.out_w;
+  taps(pl.oy, pl.ratio_y, a.H, y0, y1, wy);
   const size_t last = (size_t)a.H * a.W * C - 8;  // the last place an 8-byte window may start
   const size_t row0 = (size_t)y0 * a.W * C, row1 = (size_t)y1 * a.W * C;
   uint64_t q[2][4];
   float wx[4];
-  bool same[4];  // the second tap is the first one again (right edge)
+  uint32_t at[4];  // byte of the first tap in its row
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     int x0, x1;
-    taps(pl.ox + i, ratio_x, a.W, x0, x1, wx[i]);
-    same[i] = x1 == x0;
+    taps(pl.ox + i, pl.ratio_x, a.W, x0, x1, wx[i]);
+    if (x1 == x0) wx[i] = 0.f;
+    at[i] = (uint32_t)x0 * C;
+  }
+  const unsigned char* const rows[2] = {a.img + row0, a.img + row1};
+  if (row1 + at[3] <= last) {  // (neither the rows nor the taps of a run ever go back)
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const size_t at = (r ? row1 : row0) + (size_t)(x0 * C), from = at < last ? at : last;
-      __builtin_memcpy(&q[r][i], a.img + from, 8);
-      q[r][i] >>= (at - from) * 8;
-    }
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) __builtin_memcpy(&q[r][i], rows[r] + at[i], 8);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const size_t want = (r ? row1 : row0) + at[i], from = want < last ? want : last;
+        __builtin_memcpy(&q[r][i], a.img + from, 8);
+        q[r][i] >>= (want - from) * 8;
+      }
   }
   float* const o = a.out + ((size_t)tile * C * a.S + y) * a.S + x;
 #pragma unroll
@@ -106,9 +121,8 @@ __global__ __launch_bounds__(256) void preprocess_quad_kernel(const PrepArgs a) 
     float4 v;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int s1 = same[i] ? 8 * c : 8 * (C + c);
-      (&v.x)[i] = blend((float)(uint8_t)(q[0][i] >> (8 * c)), (float)(uint8_t)(q[0][i] >> s1), (float)(uint8_t)(q[1][i] >> (8 * c)),
-                        (float)(uint8_t)(q[1][i] >> s1), wx[i], wy, a.scale[c], a.shift[c]);
+      auto byte = [](uint64_t w, int n) { return (float)(uint8_t)((uint32_t)(n < 4 ? w : w >> 32) >> (8 * (n & 3))); };
+      (&v.x)[i] = blend(byte(q[0][i], c), byte(q[0][i], C + c), byte(q[1][i], c), byte(q[1][i], C + c), wx[i], wy, a.scale[c], a.shift[c]);
     }
     *(float4*)(o + (size_t)c * a.S * a.S) = v;
   }
@@ -140,6 +154,9 @@ extern "C" vit_status_t vit_preprocess_tiles(const uint8_t* image, int32_t heigh
   a.img = image; a.out = out_pixels;
   a.H = height; a.W = width; a.C = channels; a.S = tile_size; a.rows = grid_rows; a.cols = grid_cols;
   a.thumb = thumbnail ? 1 : 0;
+  a.tile_y = (float)height / (float)((int64_t)grid_rows * tile_size);
+  a.tile_x = (float)width / (float)((int64_t)grid_cols * tile_size);
+  a.thumb_y = (float)height / (float)tile_size; a.thumb_x = (float)width / (float)tile_size;
   // Rows of 4 pixels need a side that is a multiple of 4 (a run then lies in one row, 16-byte aligned in every plane if the
   // buffer is); everything else takes the general kernel.
   const bool quad = tile_size % 4 == 0 && ((uintptr_t)out_pixels & 15) == 0 && (int64_t)height * width * channels >= 8;

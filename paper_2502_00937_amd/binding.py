@@ -180,12 +180,15 @@ def vit_encode_packed_static(handle: int, pixels_ptr: int, images_per_request, t
     return rto
 
 
+_PACK = [struct.Struct("%df" % n) for n in range(5)]
+
+
 def _floats(values, n: int):
     """n host floats for the C side.  Two ctypes arrays cost a preprocessing call 3.5 us of its 10, packed bytes less
     than 1; the array still takes what packing refuses (another count, values that are not numbers yet)."""
     values = tuple(values)  # an iterator can be read once only
     try:
-        return struct.pack("%df" % n, *values)
+        return (_PACK[n] if 0 < n < len(_PACK) else struct.Struct("%df" % n)).pack(*values)
     except (struct.error, OverflowError, TypeError):
         return (C.c_float * n)(*[float(v) for v in values])
 
@@ -213,9 +216,12 @@ def preprocess_tiles(image, tile_size: int, grid_rows: int, grid_cols: int, thum
     if out is None:
         out = torch.empty((n_tiles, Cn, tile_size, tile_size), dtype=torch.float32, device=image.device)
     assert out.is_cuda and out.dtype == torch.float32 and out.is_contiguous()
-    if image.device.index == torch.cuda.current_device():  # the usual case needs no switch there and back
-        vit_preprocess_tiles(image.data_ptr(), H, W, Cn, tile_size, grid_rows, grid_cols, thumbnail, mean, std,
-                             out.data_ptr(), out.numel() * 4, torch.cuda.current_stream().cuda_stream)
+    index = image.get_device()
+    if index == torch.cuda.current_device():  # the usual case needs no switch there and back
+        # the stream's handle without a Stream object around it, where this torch has that: 1.5 us of the call
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        vit_preprocess_tiles(image.data_ptr(), H, W, Cn, tile_size, grid_rows, grid_cols, thumbnail, mean, std, out.data_ptr(),
+                             out.numel() * 4, raw(index) if raw else torch.cuda.current_stream().cuda_stream)
     else:
         with torch.cuda.device(image.device):
             vit_preprocess_tiles(image.data_ptr(), H, W, Cn, tile_size, grid_rows, grid_cols, thumbnail, mean, std,

@@ -65,6 +65,24 @@ def test_tile_heights_and_short_products(n, hidden, mlp):
     assert_parity(whole[-T:], want, "bf16", f"tile heights n={n} width={hidden}")
 
 
+@pytest.mark.parametrize("hidden,mlp,n", [(320, 2056, 273), (576, 3016, 182), (832, 3016, 127), (832, 3016, 182), (1088, 2056, 100)])
+def test_tokens_do_not_depend_on_the_persistent_kernel(hidden, mlp, n):
+    """Products that the persistent kernel takes, several tiles to a workgroup, at odd numbers of k-stages: QKV of 5, 13 and 17
+    (four tile columns, the last of them ragged, and 8 + 2 and 12 + 1 of them), fc1 of 9 and 13; and fc2 of 832 columns at 127
+    images, whose last round of rows is a launch of its own.  An image alone takes one tile per workgroup."""
+    cfg = dict(CFG, hidden=hidden, heads=hidden // 64, mlp=mlp, layers_local=1, proj_layers=0, proj_dims=())
+    say(f"case persistent matrix product, {n} images of 226 tokens, width {hidden}")
+    w, px = gen.make_weights(cfg, seed=7), gen.make_pixels(cfg, n, seed=n)
+    whole, _ = gpu_encode(cfg, w, px, [n], np.arange(n + 1, dtype=np.int32))
+    T = gen.tokens_per_tile(cfg)
+    one = np.array([0, 1], dtype=np.int32)
+    for i in sorted({0, n // 3, n // 2, n - 1}):
+        alone, _ = gpu_encode(cfg, w, px[i:i + 1], [1], one)
+        assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
+    want, _ = O.vit_oracle_encode(cfg, w, px[-1:], [1], one)
+    assert_parity(whole[-T:], want, "bf16", f"persistent n={n} width={hidden}")
+
+
 @pytest.mark.parametrize("dh,heads,n", [(64, 16, 100), (72, 4, 70), (80, 4, 70), (96, 4, 70), (128, 4, 70)])
 def test_tokens_do_not_depend_on_the_attention_kernel(dh, heads, n):
     """Two query blocks per image and head: the whole batch has more workgroups than the pipelined form of the attention kernel

@@ -17,12 +17,14 @@ namespace {
 // transposed, so a lane holds four consecutive columns of one row per register quad.  A row's sums are formed in the
 // same order whatever F is, so a token does not depend on the tile size its launch took.
 // Operand rows are padded by the host so tile loads never leave the buffers.
-// Measured on four 197-token images, width 192 (M = 788): out-proj and fc2 7.4 us on average, QKV 7.4, fc1 12.5; the
-// predecessor (64 x 64 tile, VALU multiply-adds, one 16-wide k-step in flight) took 34, 16.6 and 18.5.  The error of
-// the encoder against 64 bits is 3.5e-7 (6.5e-7 before: four shorter chains instead of one).
+// How many k-blocks are in flight decides how many workgroups a unit holds: 32 x 32 tiles three with three blocks (two with
+// four, and fc1 of four 197-token images is 600 tiles on 256 units), 64 x 64 tiles four with one (one with two: nothing then
+// covers a wave's loads and its sums).  Encodes of the 12-block encoder of width 192 by 4, 12 and 64 images: 599, 975 and
+// 3295 us with four and two blocks, 565, 871 and 2984 with three and one; with two (four workgroups) on 32 x 32, 585 and
+// 901.  The error of the encoder against 64 bits is 3.5e-7 (four short chains; one long one gave 6.5e-7).
 template <int EPI, int F>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs a) {
-  constexpr int DEPTH = F == 1 ? 4 : 2;  // k-blocks in flight per wave
+__global__ __launch_bounds__(256, F == 1 ? 3 : 2) void gemm_f32_kernel(const GemmArgs a) {
+  constexpr int DEPTH = F == 1 ? 3 : 1;  // k-blocks in flight per wave
   constexpr int LD = 36;                 // LDS row: 32 columns and a pad that spreads the rows over the banks
   __shared__ __attribute__((aligned(16))) float red[4][32 * F][LD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -56,7 +58,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs a) {
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) load(d, min(d, KB - 1));
   // eight lanes finish a row of each 32 x 32 block; on 32 x 32 tiles, what they need for it (bias, residual or position rows)
-  // is asked for here and not behind the sums (encode of four images 618 -> 600 us); 64 x 64 ones have no registers for it
+  // is asked for here and not behind the sums (encode of four images 618 -> 600 us); 64 x 64 ones are many to a unit and cover it
   const int er = tid >> 3, ec = (tid & 7) * 4;
   Epilogue4F32<EPI> epilogue;
   if constexpr (F == 1) {
@@ -216,12 +218,13 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const AttnArgs a) {
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.K <= 0 || a.K % 64 != 0 || a.lda % 4 != 0 || a.ldw % 4 != 0 || a.ldo % 4 != 0 || a.N % 4 != 0) return hipErrorInvalidValue;
-  // 64 x 64 tiles read half the operand bytes of 32 x 32 ones and pay from two to a compute unit on.  Whole encodes of
-  // the 12-block encoder of width 192, in us: 1 image 523 on 32 x 32 and 807 on 64 x 64 everywhere, 8 images 846 and 965,
-  // 64 images 3 650 and 3 330; the line at 256 tiles instead of 512: 8 images 870, 16 1 200 against 1 235, 32 2 010
-  // against 1 850.
+  // 64 x 64 tiles read half the operand bytes of 32 x 32 ones, which pays once there are enough of them to fill the units
+  // evenly.  Whole encodes, in us, with the line at 512, 1024, 1536, 3072 tiles and on 32 x 32 everywhere: 12 blocks of
+  // width 192, 16 images 1073, 1042, 1043, -, -; 32: 1682, 1646, 1585, -, -; 64: 2994, 2915, 2910, 2835, 2836; 300: -, -, 11490,
+  // 11762, 11897; 3 blocks of width 768, 24 images: -, -, 3002, 3024, 3084; 64: -, -, 7609, 7740, 7994.  The products that
+  // these differ in have 1773 and 2364 tiles (width 192, 64 images), 2772 (300 images), 2664 and 2364 (width 768).
   const long tiles64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64);
-  const int t = tiles64 >= 512 ? 64 : 32;
+  const int t = tiles64 >= 2560 ? 64 : 32;
   const dim3 grid((a.N + t - 1) / t, (a.M + t - 1) / t), block(256);
 #define VIT_LAUNCH(EPI)                                                                        \
   do {                                                                                         \

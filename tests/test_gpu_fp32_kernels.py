@@ -43,8 +43,7 @@ def test_segment_lengths_and_head_dims(dh, heads, grid, has_cls, tiles):
 
 
 def test_tile_sizes_give_the_same_bits():
-    """An image alone takes the 32 x 32 tiles in every product; 86 of them (5590 rows, 5504 of patches) take 64 x 64 in all but
-    the projector (352 tiles; the line is at 512)."""
+    """86 images (5590 rows): more workgroups than the units hold at once, an image alone far fewer."""
     cfg = _cfg(image_size=32, hidden=384, heads=6, mlp=520, proj_layers=1, proj_dims=(200,))
     say("case fp32 tile sizes")
     n = 86
@@ -52,6 +51,22 @@ def test_tile_sizes_give_the_same_bits():
     whole, _ = gpu_encode(cfg, w, px, [n], np.arange(n + 1, dtype=np.int32))
     T = gen.tokens_per_tile(cfg)
     for i in (0, 43, n - 1):
+        alone, _ = gpu_encode(cfg, w, px[i:i + 1], [1], np.array([0, 1], dtype=np.int32))
+        assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
+    want, _ = O.vit_oracle_encode(cfg, w, px[-2:], [2], np.arange(3, dtype=np.int32))
+    assert assert_parity(whole[-2 * T:], want, "fp32", "fp32 large tiles")[0] <= REL
+
+
+def test_large_tiles_give_the_same_bits():
+    """560 images (36 400 rows, 35 840 of patches) take 64 x 64 tiles in all but the projector (2276 tiles; the line is at 2560),
+    an image alone 32 x 32 in every product."""
+    cfg = _cfg(image_size=32, hidden=384, heads=6, mlp=520, proj_layers=1, proj_dims=(200,))
+    say("case fp32 large tiles")
+    n = 560
+    w, px = gen.make_weights(cfg, seed=1), gen.make_pixels(cfg, n, seed=2)
+    whole, _ = gpu_encode(cfg, w, px, [n], np.arange(n + 1, dtype=np.int32))
+    T = gen.tokens_per_tile(cfg)
+    for i in (0, 281, n - 1):
         alone, _ = gpu_encode(cfg, w, px[i:i + 1], [1], np.array([0, 1], dtype=np.int32))
         assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
     want, _ = O.vit_oracle_encode(cfg, w, px[-2:], [2], np.arange(3, dtype=np.int32))

@@ -833,7 +833,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_pipe_kernel(const Gemm
   }
   for (; kt < KT - 1; ++kt) {
     const int newer = KT - 2 - kt;  // stages behind kt + 1, at most NS - 2
-    if (NS >= 4 && newer >= 2) wait_loads<NS >= 4 ? 2 * LOADS : 0>();
+    if (NS >= 5 && newer >= 3) wait_loads<NS >= 5 ? 3 * LOADS : 0>();
+    else if (NS >= 4 && newer >= 2) wait_loads<NS >= 4 ? 2 * LOADS : 0>();
     else if (NS >= 3 && newer >= 1) wait_loads<NS >= 3 ? LOADS : 0>();
     else wait_loads<0>();
     step(F, kt);
@@ -850,7 +851,7 @@ hipError_t launch_pipe_as(const GemmArgs& a, hipStream_t s) {
   const long n_tiles = (long)tiles_m * tiles_n, grid = (n_tiles + 7) / 8 * 8;
   if (grid > 0x7fffffffL) return hipErrorInvalidValue;
   constexpr int lds = NS * (BM + BN) * D_ROW;
-  static_assert(NS >= 2 && NS <= 4 && lds <= 160 * 1024, "the waits of the last stages; a unit's LDS");
+  static_assert(NS >= 2 && NS <= 5 && lds <= 160 * 1024, "the waits of the last stages; a unit's LDS");
   static_assert(WM * WN * 32 * (BN / WN * 4 + 16) <= lds, "epilogue staging must fit in the ring");
 #define VIT_LAUNCH(EPI)                                                                                            \
   do {                                                                                                             \
@@ -920,8 +921,13 @@ PipeChoice best_pipe(int kind, long M, long N, int stages) {
 }
 
 hipError_t launch_pipe(const GemmArgs& a, int tile, hipStream_t s) {
+  // The longer a product of few 64 x 64 tiles, the more of its stages wait for weights that no unit has read yet: a fifth
+  // stage is worth 5 to 9 % from K = 4096 on (fc2 of 577 rows, 1024 x 4096, 15.0 us and 13.9; of 729 rows, 1152 x 4352, 19.9
+  // and 18.3; 577 rows, 1280 x 5120, 23.3 and 20.5), nothing at K = 3072 and below, and it costs products of two workgroups to
+  // a unit 2 to 4 % (QKV of 577 rows 9.4 and 9.7).
+  const bool long_alone = a.K >= 4096 && (long)((a.M + 63) / 64) * ((a.N + 63) / 64) <= 256;
   switch (tile) {
-    case 0: return launch_pipe_as<4, 64, 64, 2, 2, 2>(a, s);
+    case 0: return long_alone ? launch_pipe_as<5, 64, 64, 2, 2, 2>(a, s) : launch_pipe_as<4, 64, 64, 2, 2, 2>(a, s);
     case 1: return launch_pipe_as<4, 64, 128, 2, 4, 2>(a, s);
     case 2: return launch_pipe_as<4, 96, 128, 1, 4, 1>(a, s);
     case 3: return launch_pipe_as<4, 128, 128, 2, 4, 1>(a, s);

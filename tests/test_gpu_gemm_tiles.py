@@ -65,6 +65,23 @@ def test_tile_heights_and_short_products(n, hidden, mlp):
     assert_parity(whole[-T:], want, "bf16", f"tile heights n={n} width={hidden}")
 
 
+@pytest.mark.parametrize("mlp", [4096, 4104, 4424])
+def test_five_stage_ring(mlp):
+    """fc2 of 64 to 70 k-stages: on 64 x 64 tiles with a ring of five stages for one and three images, on larger tiles for 40."""
+    cfg = dict(CFG, mlp=mlp, layers_local=1, proj_layers=0, proj_dims=())
+    say(f"case ring of five stages, mlp {mlp}")
+    n = 40
+    w, px = gen.make_weights(cfg, seed=8), gen.make_pixels(cfg, n, seed=mlp)
+    whole, _ = gpu_encode(cfg, w, px, [n], np.arange(n + 1, dtype=np.int32))
+    T = gen.tokens_per_tile(cfg)
+    for i, k in ((0, 1), (17, 3), (n - 1, 1)):
+        some, _ = gpu_encode(cfg, w, px[i:i + k], [k], np.arange(k + 1, dtype=np.int32))
+        assert np.array_equal(some, whole[i * T:(i + k) * T]), i
+    one = np.array([0, 1], dtype=np.int32)
+    want, _ = O.vit_oracle_encode(cfg, w, px[-1:], [1], one)
+    assert_parity(whole[-T:], want, "bf16", f"five stages mlp={mlp}")
+
+
 @pytest.mark.parametrize("hidden,mlp,n", [(320, 2056, 273), (576, 3016, 182), (832, 3016, 127), (832, 3016, 182), (1088, 2056, 100)])
 def test_tokens_do_not_depend_on_the_persistent_kernel(hidden, mlp, n):
     """Products that the persistent kernel takes, several tiles to a workgroup, at odd numbers of k-stages: QKV of 5, 13 and 17

@@ -6,7 +6,7 @@
 // Two kernels share the fragment layout and the epilogues; both move their operands global -> LDS
 // directly (global_load_lds_dwordx4) and are described where they are defined:
 // * gemm_bf16_pipe_kernel (most products, and the last rows of the other one's): one tile of 64 to 256 rows by 64 or
-//   128 columns per workgroup, a ring of two to four 64-wide k-stages;
+//   128 columns per workgroup, a ring of two to five 64-wide k-stages;
 // * gemm_bf16_dma_kernel (products of many whole rounds of tiles): persistent, 256 x 256 tiles, eight waves of 128 x 64.
 // Which of them, and which tile, a product takes is decided by the time that each is expected to need (launch_gemm_bf16).
 // * LDS tiles are [row][64 bf16] with the 16-byte chunks XOR-swizzled by (row >> 1) & 7:

@@ -1,5 +1,5 @@
-"""Every tile of the small-problem matrix product: batch sizes at which the products of one encoder take 64 x 64, 64 x 128
-and 128 x 128 tiles with two and four stages, with ragged last row and column blocks.  An image's tokens must not depend on
+"""Every tile of the small-problem matrix product: batch sizes at which the products of one encoder take tiles of 64 to 256 rows
+by 64 or 128 columns, with ragged last row and column blocks, and the persistent kernel.  An image's tokens must not depend on
 the tile (bit for bit against the image alone), and the image alone is held to the oracle at the bar of the parity tests."""
 import numpy as np
 import pytest

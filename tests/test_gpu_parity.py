@@ -83,9 +83,8 @@ def test_ragged_many_tiles_bf16():
 
 
 def test_wide_batch_mixes_both_gemm_kernels():
-    """160 tiles x 226 = 36 160 token rows (142 row blocks of 256, ragged last one): the QKV product (three tile
-    columns, 426 tiles) takes the persistent 256 x 256 kernel, the others (one or two tile columns) the
-    128 x 128 ring kernel with two-stage rings; K of 4 and 8 k-stages.  The oracle encodes sampled images
+    """160 tiles x 226 = 36 160 token rows (142 row blocks of 256, ragged last one): several rounds of every kind of tile,
+    K of 4 and 8 k-stages (the persistent kernel's own sizes are in test_gpu_gemm_tiles.py).  The oracle encodes sampled images
     (first, a multi-tile one, last)."""
     cfg = gen.get_config("test_medium_bf16")
     tpi = [1, 4, 1, 1, 2, 7, 1, 3] * 8           # 64 images, 160 tiles

@@ -879,22 +879,28 @@ hipError_t launch_pipe_as(const GemmArgs& a, hipStream_t s) {
 // 12 800 columns and stages of 12 to 200) at 18 sizes each of 197 to 160 000 rows, weighted towards the tiles that are near
 // the best one: the tile chosen is on average 1 % slower than the best of the ten.  (Two launches of the choice that this one
 // replaced, by numbers of tiles alone and with 256 x 256, 128 x 128, 64 x 128 and 64 x 64 to choose from, took 13 % longer.)
-struct TileTime { int bm, bn, per_unit; float alone, full, fixed, epilogue[3]; };
+// Patch rows have epilogues of their own, fitted to the patch embeddings of four encoders (1024 to 3200 columns) at 1 to 260 tiles
+// of pixels: on the one-tile kernel they take 1.5 to 2.5 times a residual's, on the persistent one less than that.  Priced as
+// residual rows, products of many rounds stayed on the one-tile kernel (149760 x 1024 x 640: 477 us, 294 on the persistent
+// one); with these the tile chosen is on average 1 % slower than the best of the ten.
+struct TileTime { int bm, bn, per_unit; float alone, full, fixed, epilogue[4]; };
 constexpr float LAUNCH_US = 1.8f;
 constexpr TileTime PIPE_TILES[] = {
-    {64, 64, 2, 0.191f, 0.389f, 1.6f, {0.0f, 0.0f, 0.1f}},
-    {64, 128, 1, 0.204f, 0.331f, 2.1f, {0.0f, 0.0f, 0.2f}},
-    {96, 128, 1, 0.319f, 0.415f, 1.4f, {0.0f, 1.1f, 2.0f}},
-    {128, 128, 1, 0.310f, 0.500f, 1.7f, {0.0f, 0.6f, 2.7f}},
-    {160, 128, 1, 0.284f, 0.605f, 2.5f, {0.0f, 1.3f, 4.4f}},
-    {192, 128, 1, 0.315f, 0.707f, 1.8f, {0.0f, 1.1f, 5.1f}},
-    {256, 128, 1, 0.312f, 0.880f, 2.7f, {0.0f, 1.2f, 6.9f}},
-    {160, 128, 2, 0.759f, 1.142f, 0.0f, {1.1f, 2.0f, 5.0f}},
-    {192, 128, 2, 0.768f, 1.278f, 0.0f, {1.6f, 2.5f, 6.2f}},
+    {64, 64, 2, 0.191f, 0.389f, 1.6f, {0.0f, 0.0f, 0.1f, 1.0f}},
+    {64, 128, 1, 0.204f, 0.331f, 2.1f, {0.0f, 0.0f, 0.2f, 2.4f}},
+    {96, 128, 1, 0.319f, 0.415f, 1.4f, {0.0f, 1.1f, 2.0f, 5.0f}},
+    {128, 128, 1, 0.310f, 0.500f, 1.7f, {0.0f, 0.6f, 2.7f, 7.1f}},
+    {160, 128, 1, 0.284f, 0.605f, 2.5f, {0.0f, 1.3f, 4.4f, 7.5f}},
+    {192, 128, 1, 0.315f, 0.707f, 1.8f, {0.0f, 1.1f, 5.1f, 10.2f}},
+    {256, 128, 1, 0.312f, 0.880f, 2.7f, {0.0f, 1.2f, 6.9f, 13.3f}},
+    {160, 128, 2, 0.759f, 1.142f, 0.0f, {1.1f, 2.0f, 5.0f, 8.2f}},
+    {192, 128, 2, 0.768f, 1.278f, 0.0f, {1.6f, 2.5f, 6.2f, 10.1f}},
 };
 constexpr int PIPE_TILE_COUNT = sizeof(PIPE_TILES) / sizeof(PIPE_TILES[0]);
 
-int epilogue_kind(int epilogue) { return epilogue == EPI_BIAS_GELU ? 1 : epilogue == EPI_BIAS_RESIDUAL || epilogue == EPI_PATCH ? 2 : 0; }
+int epilogue_kind(int epilogue) {
+  return epilogue == EPI_BIAS_GELU ? 1 : epilogue == EPI_BIAS_RESIDUAL ? 2 : epilogue == EPI_PATCH ? 3 : 0;
+}
 
 float pipe_time(const TileTime& t, int kind, long M, long N, int stages) {
   const long n = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), cap = 256L * t.per_unit;
@@ -955,7 +961,7 @@ Walk persistent_walk(long M, long N) {
   return w;
 }
 
-constexpr TileTime PERSISTENT_TILE = {256, 256, 1, 0.675f, 1.513f, 4.5f, {4.3f, 7.2f, 17.2f}};
+constexpr TileTime PERSISTENT_TILE = {256, 256, 1, 0.675f, 1.513f, 4.5f, {4.3f, 7.2f, 17.2f, 14.2f}};
 constexpr float NARROW_GROUP = 0.11f;  // what the groups of a remainder's columns take longer than those of a band
 float persistent_time(int kind, long M, long N, int stages) {
   const Walk w = persistent_walk(M, N);

@@ -443,10 +443,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_dma_kernel(const GemmArgs a, in
   const size_t a_step = (size_t)16 * a.lda, w_step = (size_t)16 * a.ldw;  // bytes per 8 rows
   // One direct-to-LDS instruction.  It is written as inline assembly so that the compiler's
   // wait-count insertion, which cannot know that the unit written here is never one being read,
-  // does not fence every surrounding LDS read; completion is tracked by hand (sync_stage).  M0 holds
-  // the LDS destination of lane 0.
+  // does not fence every surrounding LDS read; completion is tracked by hand (the waits ahead of the
+  // barriers).  M0 holds the LDS destination of lane 0; a scalar write of it needs one wait state ahead of
+  // the load that reads it, which the compiler puts there for its own code but not inside an asm text.
   auto dma16 = [&](const unsigned char* gbase, uint32_t goff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(goff), "s"(gbase) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(goff), "s"(gbase) : "memory", "m0");
   };
   // load cursors, one per operand: the tile list position, the stage inside the tile, the tile's address at k = 0, the LDS
   // unit that is filled next
@@ -737,7 +738,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_pipe_kernel(const Gemm
   const unsigned char* const baseW = (const unsigned char*)a.W + (size_t)n0 * a.ldw * 2;
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;  // low 32 bits of a generic LDS pointer = LDS offset
   auto dma16 = [&](const unsigned char* gbase, uint32_t goff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(goff), "s"(gbase) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(goff), "s"(gbase) : "memory", "m0");
   };
   auto issue = [&](int slot, int kt, int i) {  // instruction i of stage kt into the ring slot at byte `slot`
     const uint32_t st = __builtin_amdgcn_readfirstlane(lds0 + slot);

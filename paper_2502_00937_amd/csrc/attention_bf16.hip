@@ -90,7 +90,9 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
   if (wi >= a.n_work) return;
   const AttnWork w = a.work[a.reverse ? a.n_work - 1 - wi : wi];
   const int head = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  // wave-uniform to the compiler, too: whether a wave has queries decides which of two paths with barriers it takes
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, g = lane >> 5;
   const int partner_addr = (lane ^ 32) << 2;  // ds_bpermute byte address of the lane that holds the other 16 keys of a query
   // The transposing LDS read (ds_read_b64_tr_b16) works on groups of 16 lanes: lane j of a group points at 8 bytes

@@ -172,10 +172,10 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
     }
   };
   // registers -> LDS, K and V rows alike (the second product reads V through the transposing LDS read)
-  auto store_tile = [&](unsigned char* sK, unsigned char* sV) {
+  auto store_tile = [&](unsigned char* sK, unsigned char* sV, int thread) {
 #pragma unroll
     for (int i = 0; i < Sh::K_PER; ++i) {
-      const int it = tid + i * ANT;
+      const int it = thread + i * ANT;
       if (Sh::K_ITEMS % ANT == 0 || it < Sh::K_ITEMS) {
         const int key = it / Sh::NCH, ch = it - key * Sh::NCH;
         *(u32x4*)(sK + key * Sh::K_STRIDE + ch * 16) = rk[i];
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
       else load_tile(t * AKV, T);
     }
   };
-  auto store = [&](int t) { store_tile(lds + (t & 1) * Sh::STAGE, lds + (t & 1) * Sh::STAGE + Sh::K_BYTES); };
+  auto store = [&](int t, int thread) { store_tile(lds + (t & 1) * Sh::STAGE, lds + (t & 1) * Sh::STAGE + Sh::K_BYTES, thread); };
 
   // One pass over the segment's K/V tiles, block by block of 32 keys.
   //
@@ -269,6 +269,10 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
   auto attend = [&](auto fast_tag, const bool active) {
     constexpr bool FAST = decltype(fast_tag)::value;
     float m = -INFINITY;  // reference maximum in log2 units (general pass)
+    // A second pass works its places in LDS out again: kept across the pipelined pass, they were the register that it has not got
+    // (168 of 168 at head dim 64 and one more in scratch memory).
+    int thread = tid;
+    if constexpr (DEEP) asm("" : "+v"(thread));
     if (active) {
 #pragma unroll
       for (int b = 0; b < Sh::DB; ++b)
@@ -277,7 +281,7 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
       l = 0.f;
     }
     fetch(0);
-    store(0);
+    store(0, thread);
     __syncthreads();
 
     // One K/V tile.  MASK is set only for a segment's last, partial tile: full tiles carry no
@@ -353,7 +357,7 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
           for (int s2 = 0; s2 < 2; ++s2)
             o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_vt(sV, kb, b, s2), p[s2], o[b], 0, 0, 0);
       }
-      if (t + 1 < n_tiles) store(t + 1);
+      if (t + 1 < n_tiles) store(t + 1, thread);
       __syncthreads();
     };
     // Every load issued so far (the Q fragments among them) has landed before the loop starts: the
@@ -421,7 +425,7 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
         for (int s2 = 0; s2 < 2; ++s2) o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[b][s2], pf[s2], o[b], 0, 0, 0);
     };
     fetch(0);
-    store(0);
+    store(0, tid);
     fetch(1);
     __syncthreads();
     // waves without queries only move tiles
@@ -436,7 +440,7 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
       read_k(0, 1);  // (of a tile of 32 keys or less: rows that repeat the last one, and no use)
       for (int t = 0; t < n_tiles - 1; ++t) {  // full tiles, each with another behind it
         const int buf = t & 1;
-        store(t + 1);
+        store(t + 1, tid);
         fetch(t + 2);
         __builtin_amdgcn_sched_barrier(0);
         read_v(buf, 0);
@@ -471,7 +475,7 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
       accumulate();
     } else {
       for (int t = 0; t < n_tiles - 1; ++t) {
-        store(t + 1);
+        store(t + 1, tid);
         fetch(t + 2);
         __syncthreads();
         __syncthreads();

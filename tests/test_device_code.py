@@ -117,3 +117,7 @@ def test_attention_barriers_are_under_no_mask(kernels):
         assert sum(ins.startswith("s_barrier") for _, ins, _ in code) >= 4, name
         assert not _barriers_under_a_mask(code), name
     assert looked_at >= 9
+
+
+def test_no_kernel_keeps_registers_in_scratch_memory(kernels):
+    assert not [(name, ins) for name, code in kernels.items() for _, ins, _ in code if ins.startswith("scratch_")]

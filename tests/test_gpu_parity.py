@@ -471,6 +471,18 @@ def test_every_accepted_head_dim_matches_oracle(dh, heads, dtype):
     check_case(cfg, [2, 1, 3], [1, 0, 2], wseed=dh, pseed=dh + 1, label=f"dh{dh}")
 
 
+@pytest.mark.parametrize("hidden,heads", [(8, 1), (248, 31), (256, 4), (264, 3), (512, 4), (520, 5), (640, 10), (768, 6), (776, 97), (1024, 8),
+                                          (1032, 129), (1280, 10), (1288, 23)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_row_lengths_around_whole_slots_of_a_wave(hidden, heads, dtype):
+    """LayerNorm holds a row in 1 to 5, 8 or 16 slots of 256 columns: lengths that fill them, and those around."""
+    cfg = {"image_size": 8, "patch_size": 4, "channels": 3, "hidden": hidden, "heads": heads, "mlp": 64, "layers_local": 1,
+           "layers_global": 0, "has_cls": 1, "final_ln": 1, "ln_eps": 1e-6, "proj_layers": 0, "proj_dims": (), "dtype": dtype,
+           "token_merge": 1}
+    say(f"case rows of {hidden} columns, {dtype}")
+    check_case(cfg, [3, 1], [2], label=f"rows of {hidden}")
+
+
 @pytest.mark.parametrize("channels,dtype", [(1, "bf16"), (4, "bf16"), (1, "fp32"), (4, "fp32"), (16, "bf16")])
 def test_channel_counts_other_than_three(channels, dtype):
     """Patch vectors of C p^2 values for C = 1, 4 and the maximum, 16 (the patch product's contraction length

@@ -254,6 +254,37 @@ def vendor_gemm(torch, gen):
         del a, w, c
 
 
+# (epilogue, columns, depth) of the products of encoders of widths from 384 to 3200, and the rows that they are timed at
+PRODUCT_ENCODERS = {384: (1152, 384, 1536, 768), 512: (1536, 512, 2048, 640), 768: (2304, 768, 3072, 768), 1024: (3072, 1024, 4096, 640),
+                    1152: (3456, 1152, 4304, 640), 1280: (3840, 1280, 5120, 640), 1408: (4608, 1536, 6144, 640),
+                    1664: (6144, 2048, 8192, 640), 3200: (9600, 3200, 12800, 640)}  # width: QKV columns, attention's, MLP's, patch depth
+PRODUCT_ROWS = (197, 257, 577, 729, 1154, 1731, 2308, 2885, 3645, 4616, 5193, 6404, 8078, 9232, 11540, 14425, 17310, 20195, 21870,
+                25675, 32020, 40390, 51232, 65778, 86550, 115400, 150020)
+
+
+def product_times(torch, V):
+    """Every form of the bf16 matrix product on the products of nine encoders, as CSV: what the library's expected times are
+    fitted to."""
+    u64 = lambda n: -(-n // 64) * 64
+    products = []
+    for d, (qkv, att, mlp, patch) in PRODUCT_ENCODERS.items():
+        products += [("bias", qkv, u64(d)), ("residual", d, u64(att)), ("gelu", mlp, u64(d)), ("residual", d, u64(mlp)), ("patch", d, patch)]
+    products += [("gelu", 4096, 1024), ("bias", 4096, 4096), ("gelu", 6144, 12800), ("bias", 6144, 6144)]
+    ws = torch.empty(5 << 30, dtype=torch.bfloat16, device="cuda").uniform_(-1.0, 1.0)
+    print("epilogue,columns,depth,rows,as planned," + ",".join(V.PRODUCT_FORMS), flush=True)
+    for epilogue, n, k in products:
+        for rows in PRODUCT_ROWS:
+            if 2.0 * rows * n * k > 6e12:  # some 6 ms
+                continue
+            if epilogue in ("residual", "patch"):
+                ws.uniform_(-1.0, 1.0)  # residual streams grow from launch to launch
+            # room for output and operand, and half a GiB of weights, which no cache holds from one turn to the next
+            room = min(ws.numel() * 2, (rows + 1000) * (n * 4 + k * 2) + 600 * n * 4 + max(512 << 20, (n + 256) * k * 2))
+            times = [None if form and form.startswith("64") and rows > 32000 else
+                     V.vit_product_time(epilogue, rows, n, k, ws.data_ptr(), room, form) for form in (None,) + V.PRODUCT_FORMS]
+            print(f"{epilogue},{n},{k},{rows}," + ",".join("" if t is None else f"{t:.1f}" for t in times), flush=True)
+
+
 def power_trace(args, torch, gen, V):
     """Socket power and per-XCD shader clocks (amd-smi, twice a second) while the workload's encode step runs back to
     back for about six seconds.  Context for every fraction of peak this script prints: the device holds its power
@@ -324,6 +355,9 @@ def main():
                          "and print measured encode latencies beside the event model's")
     ap.add_argument("--vendor-gemm", action="store_true",
                     help="time the vendor library's bf16 matrix product (torch.matmul) on the step's shapes: context only")
+    ap.add_argument("--product-times", action="store_true",
+                    help="time every form of the bf16 matrix product on the products of nine encoders at 27 sizes and print "
+                         "them as CSV (several minutes)")
     ap.add_argument("--power-trace", action="store_true",
                     help="run the workload's step back to back for six seconds while sampling socket power and shader "
                          "clocks with amd-smi; prints one JSON line (context for the fractions of peak)")
@@ -352,6 +386,9 @@ def main():
         return
     if args.vendor_gemm:
         vendor_gemm(torch, gen)
+        return
+    if args.product_times:
+        product_times(torch, V)
         return
     if args.power_trace:
         power_trace(args, torch, gen, V)

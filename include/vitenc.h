@@ -309,6 +309,29 @@ vit_status_t vit_preprocess_tiles(const uint8_t* image, int32_t height, int32_t 
  */
 vit_status_t vit_mfma_ceiling(int device, double seconds, int32_t random_operands, double* tflops);
 
+/*
+ * Measurement aids (no part of the encode path): how a bf16 matrix product [rows, depth] x
+ * [columns, depth]^T of the encoder is computed, and how long it takes.  epilogue: 0 bias, 1 bias
+ * and GELU, 2 added to the residual stream, 3 patch embedding.  form: 0 to 8 a tile per workgroup
+ * of 64 x 64, 64 x 128, 96, 128, 160, 192 and 256 x 128, and 160 x 128 and 192 x 128 with two
+ * workgroups to a compute unit; 9 the persistent kernel's 256 x 256 tiles.
+ *   vit_product_plan  the form that the encoder takes on a device of `units` compute units, the
+ *                     number of rows that go to another form in a second launch (0: none) and
+ *                     that form, and the time this is expected to take.  Host only.
+ *   vit_product_time  mean microseconds of a launch on the current device, on `stream`, in the form
+ *                     given (-1: as the encoder takes it), over some 10 ms of launches whose
+ *                     weights are taken in turn from what `workspace` holds of them, as layers'
+ *                     are.  workspace: DEVICE, 256-byte aligned, filled by the caller with finite
+ *                     bf16 values (the clock that the chip holds depends on the data); it is
+ *                     overwritten.  It holds the output, the operand, bias, 577 position rows
+ *                     and one to any number of copies of the weights.  Waits for the launches.
+ * Errors: VIT_EINVAL (NULL, range, alignment), VIT_ECAPACITY, VIT_EDEVICE.
+ */
+vit_status_t vit_product_plan(int32_t epilogue, int64_t rows, int32_t columns, int32_t depth, int32_t units,
+                              int32_t* form, int64_t* rest_rows, int32_t* rest_form, double* expected_us);
+vit_status_t vit_product_time(int32_t epilogue, int64_t rows, int32_t columns, int32_t depth, int32_t form,
+                              void* workspace, size_t workspace_bytes, void* stream, double* us);
+
 #pragma GCC visibility pop
 #ifdef __cplusplus
 }

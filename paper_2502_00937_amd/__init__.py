@@ -4,6 +4,8 @@ The binding marshals arguments only; every step of the encoder runs inside the H
 library.  PyTorch supplies device memory and the stream.
 """
 from .binding import (  # noqa: F401
+    PRODUCT_EPILOGUES,
+    PRODUCT_FORMS,
     TokenHandoff,
     VitEncoder,
     VitError,
@@ -18,5 +20,7 @@ from .binding import (  # noqa: F401
     vit_encoder_query,
     vit_mfma_ceiling,
     vit_preprocess_tiles,
+    vit_product_plan,
+    vit_product_time,
     vit_weight_count,
 )

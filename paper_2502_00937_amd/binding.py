@@ -93,6 +93,12 @@ def load_library():
                                          C.c_void_p]
     lib.vit_mfma_ceiling.restype = C.c_int
     lib.vit_mfma_ceiling.argtypes = [C.c_int, C.c_double, C.c_int32, C.POINTER(C.c_double)]
+    lib.vit_product_plan.restype = C.c_int
+    lib.vit_product_plan.argtypes = [C.c_int32, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32),
+                                     C.POINTER(C.c_int64), C.POINTER(C.c_int32), C.POINTER(C.c_double)]
+    lib.vit_product_time.restype = C.c_int
+    lib.vit_product_time.argtypes = [C.c_int32, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_size_t,
+                                     C.c_void_p, C.POINTER(C.c_double)]
     lib.vit_profile_read.restype = C.c_int
     lib.vit_profile_read.argtypes = [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
     _LIB = lib
@@ -227,6 +233,29 @@ def preprocess_tiles(image, tile_size: int, grid_rows: int, grid_cols: int, thum
             vit_preprocess_tiles(image.data_ptr(), H, W, Cn, tile_size, grid_rows, grid_cols, thumbnail, mean, std,
                                  out.data_ptr(), out.numel() * 4, torch.cuda.current_stream().cuda_stream)
     return out
+
+
+PRODUCT_EPILOGUES = ("bias", "gelu", "residual", "patch")
+PRODUCT_FORMS = ("64x64", "64x128", "96x128", "128x128", "160x128", "192x128", "256x128", "160x128 two a unit",
+                 "192x128 two a unit", "persistent 256x256")
+
+
+def vit_product_plan(epilogue: str, rows: int, columns: int, depth: int, units: int = 256):
+    """(form, rows of a second launch, its form or None, expected us) of a bf16 product on a device of that many units."""
+    form, rest, rest_form, us = C.c_int32(), C.c_int64(), C.c_int32(), C.c_double()
+    _check(load_library().vit_product_plan(PRODUCT_EPILOGUES.index(epilogue), rows, columns, depth, units, C.byref(form),
+                                           C.byref(rest), C.byref(rest_form), C.byref(us)))
+    return PRODUCT_FORMS[form.value], rest.value, PRODUCT_FORMS[rest_form.value] if rest.value else None, us.value
+
+
+def vit_product_time(epilogue: str, rows: int, columns: int, depth: int, workspace_ptr: int, workspace_bytes: int,
+                     form: str | None = None, stream: int = 0) -> float:
+    """Mean us of a launch of a bf16 product in that form (None: as the encoder takes it)."""
+    us = C.c_double()
+    _check(load_library().vit_product_time(PRODUCT_EPILOGUES.index(epilogue), rows, columns, depth,
+                                           -1 if form is None else PRODUCT_FORMS.index(form), workspace_ptr, workspace_bytes,
+                                           stream, C.byref(us)))
+    return us.value
 
 
 def vit_mfma_ceiling(device: int = 0, seconds: float = 0.1, random_operands: bool = True) -> float:

@@ -194,7 +194,13 @@ struct AttnArgs {
 
 // ---- launchers (defined in the .hip files) ----------------------------------------------
 // bf16 MFMA path
-hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
+// form: the kernel and tile to take whatever the plan says (measurement), or -1
+hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s, int form = -1);
+// How a bf16 product is computed: by the tiles of PIPE_TILES (0 ...) or by the persistent kernel, and, where rest_rows is not 0, that
+// many of its rows by the tile rest_form; us is the time that this is expected to take.
+constexpr int PRODUCT_PERSISTENT = 9;
+struct ProductPlan { int form, rest_rows, rest_form; float us; };
+ProductPlan plan_product(int epilogue, long M, long N, int K, int units, bool reverse);
 hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s);
 // fp32 path
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);

@@ -898,6 +898,7 @@ constexpr TileTime PIPE_TILES[] = {
     {192, 128, 2, 0.768f, 1.278f, 0.0f, {1.6f, 2.5f, 6.2f, 10.1f}},
 };
 constexpr int PIPE_TILE_COUNT = sizeof(PIPE_TILES) / sizeof(PIPE_TILES[0]);
+static_assert(PIPE_TILE_COUNT == PRODUCT_PERSISTENT, "forms are numbered tiles first");
 
 int epilogue_kind(int epilogue) {
   return epilogue == EPI_BIAS_GELU ? 1 : epilogue == EPI_BIAS_RESIDUAL ? 2 : epilogue == EPI_PATCH ? 3 : 0;
@@ -943,6 +944,7 @@ hipError_t launch_pipe(const GemmArgs& a, int tile, hipStream_t s) {
     case 6: return launch_pipe_as<3, 256, 128, 4, 2, 1>(a, s);
     case 7: return launch_pipe_as<2, 160, 128, 1, 4, 1>(a, s);
     case 8: return launch_pipe_as<2, 192, 128, 2, 2, 1>(a, s);
+    default: break;
   }
   return hipErrorInvalidValue;
 }
@@ -1023,50 +1025,62 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
 
 int gemm_row_pad() { return 256; }
 
-hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
+// Which kernels a product takes.  kind as in TileTime::epilogue.
+ProductPlan plan_product(int epilogue, long M, long N, int K, int units, bool reverse) {
+  const int kind = epilogue_kind(epilogue), stages = K / BK;
+  const PipeChoice pipe = best_pipe(kind, M, N, stages);
+  ProductPlan plan{pipe.tile, 0, 0, pipe.us};
+  // The unit count is a performance assumption only (no workgroup waits for another): a device with fewer of them takes
+  // one workgroup per tile.
+  if (units < PERSISTENT_GRID) return plan;
+  const float whole = persistent_time(kind, M, N, stages);
+  if (whole < plan.us) plan = {PRODUCT_PERSISTENT, 0, 0, whole};
+  // A product one column band wide (1, 2 or 4 tile columns) is walked in rounds of 256 / tiles_n row blocks, one tile per
+  // unit.  Where the last round leaves most units idle for a whole tile time, its rows go to the other kernel in a second
+  // launch (fc2 of 20195 x 1024 x 4096: 174 us so, 216 without).  All kernels give a row the same bits, so where the cut
+  // falls does not show in the result.  It is made at the end that the walk reaches last.
+  const int tiles_m = (int)((M + D_BM - 1) / D_BM), tiles_n = (int)((N + D_BN - 1) / D_BN);
+  if (epilogue != EPI_PATCH && (tiles_n == 1 || tiles_n == 2 || tiles_n == 4)) {
+    const int per_round = 256 / tiles_n, tail_blocks = tiles_m % per_round;
+    if (tail_blocks > 0 && tiles_m > per_round) {
+      const long main_rows = (long)(tiles_m - tail_blocks) * D_BM;
+      const float us = persistent_time(kind, main_rows, N, stages) + best_pipe(kind, M - main_rows, N, stages).us;
+      if (us < plan.us) {
+        const long rest = reverse ? (long)tail_blocks * D_BM : M - main_rows;  // (walked in reverse, the persistent kernel takes
+                                                                               //  the last rows, ragged row block included)
+        plan = {PRODUCT_PERSISTENT, (int)rest, best_pipe(kind, rest, N, stages).tile, us};
+      }
+    }
+  }
+  return plan;
+}
+
+hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s, int form) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   // 16-byte epilogue accesses need 8-element aligned columns and leading dimensions
   if (a.K <= 0 || a.K % BK != 0 || a.lda % 8 != 0 || a.ldw % 8 != 0 || a.ldo % 8 != 0 || a.N % 8 != 0)
     return hipErrorInvalidValue;
   // head-by-head output: heads of 64 or 128 columns (a wave's column block never straddles two)
   if (a.epilogue == EPI_BIAS_HEADS && (a.hm_dh <= 0 || a.hm_dh % 64 != 0 || a.hm_rows < (size_t)a.M)) return hipErrorInvalidValue;
-  const int kind = epilogue_kind(a.epilogue), stages = a.K / BK;
+  if (form >= 0) return form == PRODUCT_PERSISTENT ? launch_dma(a, s) : launch_pipe(a, form, s);
   int units = 0;
   if (hipError_t e = compute_units(&units); e != hipSuccess) return e;
-  const PipeChoice pipe = best_pipe(kind, a.M, a.N, stages);
-  // The unit count is a performance assumption only (no workgroup waits for another): a device with fewer of them takes
-  // one workgroup per tile.
-  if (units < PERSISTENT_GRID) return launch_pipe(a, pipe.tile, s);
-  const float whole = persistent_time(kind, a.M, a.N, stages);
-  // A product one column band wide (1, 2 or 4 tile columns) is walked in rounds of 256 / tiles_n row blocks, one tile per
-  // unit.  Where the last round leaves most units idle for a whole tile time, its rows go to the other kernel in a second
-  // launch (fc2 of 20195 x 1024 x 4096: 174 us so, 216 without).  All kernels give a row the same bits, so where the cut
-  // falls does not show in the result.  It is made at the end that the walk reaches last.
-  const int tiles_m = (a.M + D_BM - 1) / D_BM, tiles_n = (a.N + D_BN - 1) / D_BN;
-  if (a.epilogue != EPI_PATCH && (tiles_n == 1 || tiles_n == 2 || tiles_n == 4)) {
-    const int per_round = 256 / tiles_n, tail_blocks = tiles_m % per_round;
-    if (tail_blocks > 0 && tiles_m > per_round) {
-      const int main_rows = (tiles_m - tail_blocks) * D_BM, tail_rows = a.M - main_rows;
-      const PipeChoice tail = best_pipe(kind, tail_rows, a.N, stages);
-      if (persistent_time(kind, main_rows, a.N, stages) + tail.us < std::min(whole, pipe.us)) {
-        auto rows_from = [&](int row0, int rows) {
-          GemmArgs b = a;
-          b.M = rows;
-          b.A = (const unsigned char*)a.A + (size_t)row0 * a.lda * 2;
-          if (a.out) b.out = (unsigned char*)a.out + (size_t)row0 * (a.epilogue == EPI_BIAS_HEADS ? a.hm_dh : a.ldo) * 2;  // a row's stride
-          if (a.resid) b.resid = a.resid + (size_t)row0 * a.ldo;
-          return b;
-        };
-        // (walked in reverse, the persistent kernel takes the last rows of the matrix, ragged row block included)
-        const int cut = a.reverse ? tail_blocks * D_BM : main_rows;
-        const GemmArgs lower = rows_from(0, cut), upper = rows_from(cut, a.M - cut);
-        if (hipError_t e = launch_dma(a.reverse ? upper : lower, s); e != hipSuccess) return e;
-        const GemmArgs& rest = a.reverse ? lower : upper;
-        return launch_pipe(rest, best_pipe(kind, rest.M, a.N, stages).tile, s);
-      }
-    }
+  const ProductPlan plan = plan_product(a.epilogue, a.M, a.N, a.K, units, a.reverse != 0);
+  if (plan.rest_rows > 0) {
+    auto rows_from = [&](int row0, int rows) {
+      GemmArgs b = a;
+      b.M = rows;
+      b.A = (const unsigned char*)a.A + (size_t)row0 * a.lda * 2;
+      if (a.out) b.out = (unsigned char*)a.out + (size_t)row0 * (a.epilogue == EPI_BIAS_HEADS ? a.hm_dh : a.ldo) * 2;  // a row's stride
+      if (a.resid) b.resid = a.resid + (size_t)row0 * a.ldo;
+      return b;
+    };
+    const int cut = a.reverse ? plan.rest_rows : a.M - plan.rest_rows;
+    const GemmArgs lower = rows_from(0, cut), upper = rows_from(cut, a.M - cut);
+    if (hipError_t e = launch_dma(a.reverse ? upper : lower, s); e != hipSuccess) return e;
+    return launch_pipe(a.reverse ? lower : upper, plan.rest_form, s);
   }
-  return whole < pipe.us ? launch_dma(a, s) : launch_pipe(a, pipe.tile, s);
+  return plan.form == PRODUCT_PERSISTENT ? launch_dma(a, s) : launch_pipe(a, plan.form, s);
 }
 
 }  // namespace vitenc

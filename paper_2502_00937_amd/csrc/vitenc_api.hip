@@ -358,6 +358,15 @@ __global__ __launch_bounds__(256) void mfma_ceiling_kernel(const u32x4* __restri
   if (sum == 123.456f) out[threadIdx.x] = sum;  // keeps the loop alive; never true in practice
 }
 
+// what the bf16 matrix products cannot take (NULL: nothing)
+const char* product_refused(int32_t epilogue, int64_t rows, int32_t columns, int32_t depth, int32_t units) {
+  if (epilogue < EPI_BIAS || epilogue > EPI_PATCH) return "epilogue must be 0 to 3";
+  if (rows <= 0 || rows > ((int64_t)1 << 31) - 2048) return "rows must be positive and below 2^31 - 2048";
+  if (columns <= 0 || columns % 8 != 0 || columns > 1 << 20) return "columns must be a positive multiple of 8, at most 2^20";
+  if (depth <= 0 || depth % 64 != 0 || depth > 1 << 20) return "depth must be a positive multiple of 64, at most 2^20";
+  return units <= 0 ? "units must be positive" : nullptr;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1008,6 +1017,66 @@ vit_status_t vit_mfma_ceiling(int device, double seconds, int32_t random_operand
   (void)hipFree(dev);
   if (err != hipSuccess) return fail(VIT_EDEVICE, "vit_mfma_ceiling: %s", hipGetErrorString(err));
   *tflops = best;
+  return VIT_OK;
+}
+
+vit_status_t vit_product_plan(int32_t epilogue, int64_t rows, int32_t columns, int32_t depth, int32_t units, int32_t* form,
+                              int64_t* rest_rows, int32_t* rest_form, double* expected_us) {
+  if (!form || !rest_rows || !rest_form || !expected_us) return fail(VIT_EINVAL, "vit_product_plan: NULL argument");
+  if (const char* why = product_refused(epilogue, rows, columns, depth, units)) return fail(VIT_EINVAL, "vit_product_plan: %s", why);
+  const ProductPlan plan = plan_product(epilogue, (long)rows, columns, depth, units, false);
+  *form = plan.form; *rest_rows = plan.rest_rows; *rest_form = plan.rest_form; *expected_us = plan.us;
+  return VIT_OK;
+}
+
+vit_status_t vit_product_time(int32_t epilogue, int64_t rows, int32_t columns, int32_t depth, int32_t form, void* workspace,
+                              size_t workspace_bytes, void* stream, double* us) {
+  if (!workspace || !us) return fail(VIT_EINVAL, "vit_product_time: NULL argument");
+  if (const char* why = product_refused(epilogue, rows, columns, depth, 1)) return fail(VIT_EINVAL, "vit_product_time: %s", why);
+  if (form < -1 || form > PRODUCT_PERSISTENT || (uintptr_t)workspace % 256) return fail(VIT_EINVAL, "vit_product_time: bad form or alignment");
+  constexpr int kPatches = 576;  // of a tile, with a CLS row ahead of them (EPI_PATCH)
+  const int64_t pad = gemm_row_pad(), tiles = (rows + kPatches - 1) / kPatches;
+  const size_t out_rows = (size_t)(epilogue == EPI_PATCH ? tiles * (kPatches + 1) : rows);
+  size_t at = 0;
+  auto part = [&](size_t bytes) { const size_t from = at; at += round_up(bytes, 256); return (unsigned char*)workspace + from; };
+  GemmArgs a;
+  memset(&a, 0, sizeof(a));
+  unsigned char* out = part(out_rows * columns * (epilogue == EPI_BIAS || epilogue == EPI_BIAS_GELU ? 2 : 4));
+  a.A = part((size_t)round_up(rows, pad) * depth * 2);
+  a.bias = (const float*)part((size_t)round_up(columns, pad) * 4);
+  a.pos = (const float*)part((size_t)(kPatches + 1) * columns * 4);
+  const size_t w_bytes = round_up((size_t)round_up(columns, pad) * depth * 2, 256);
+  if (workspace_bytes < at + w_bytes)
+    return fail(VIT_ECAPACITY, "vit_product_time: workspace holds %zu bytes, %zu needed", workspace_bytes, at + w_bytes);
+  const size_t copies = (workspace_bytes - at) / w_bytes;
+  a.out = out; a.resid = (float*)out;
+  a.M = (int)rows; a.N = columns; a.K = depth; a.lda = depth; a.ldw = depth; a.ldo = columns;
+  a.patches = kPatches; a.tokens = kPatches + 1; a.cls = 1; a.epilogue = epilogue;
+  a.stream_out = (size_t)rows * columns * 2 > (size_t)256 << 20;
+  hipStream_t s = (hipStream_t)stream;
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  hipError_t err = hipEventCreate(&e0);
+  if (err == hipSuccess) err = hipEventCreate(&e1);
+  float ms = 0.f;
+  int launches = 4;  // a first look; the second set is sized from it to take about 10 ms
+  size_t next = 0;
+  for (int set = 0; set < 2 && err == hipSuccess; ++set) {
+    if (set) launches = (int)std::min(400.0, std::max(6.0, 10.0 * launches / std::max(ms, 1e-3f)));
+    if (err == hipSuccess) err = hipEventRecord(e0, s);
+    for (int i = 0; i < launches && err == hipSuccess; ++i) {
+      a.W = (unsigned char*)workspace + at + next * w_bytes;  // weights that the last layer has not read
+      next = next + 1 == copies ? 0 : next + 1;
+      a.reverse = i & 1;
+      err = launch_gemm_bf16(a, s, form);
+    }
+    if (err == hipSuccess) err = hipEventRecord(e1, s);
+    if (err == hipSuccess) err = hipEventSynchronize(e1);
+    if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
+  }
+  if (e0) (void)hipEventDestroy(e0);
+  if (e1) (void)hipEventDestroy(e1);
+  if (err != hipSuccess) return fail(VIT_EDEVICE, "vit_product_time: %s", hipGetErrorString(err));
+  *us = (double)ms * 1e3 / launches;
   return VIT_OK;
 }
 

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import gen
+import paper_2502_00937_amd as V
 from oracle import vit_oracle as O
 from parity_util import assert_parity, say
 from test_gpu_parity import gpu_encode
@@ -115,3 +116,16 @@ def test_tokens_do_not_depend_on_the_attention_kernel(dh, heads, n):
         assert np.array_equal(alone, whole[i * T:(i + 1) * T]), i
     want, _ = O.vit_oracle_encode(cfg, w, px[-1:], [1], one)
     assert_parity(whole[-T:], want, "bf16", f"attention forms dh={dh}")
+
+
+@pytest.mark.parametrize("form", [None, *V.PRODUCT_FORMS])
+def test_timing_aid_takes_every_form(form):
+    import torch
+
+    say(f"case timing of a product, {form}")
+    ws = torch.empty(64 << 20, dtype=torch.bfloat16, device="cuda").uniform_(-1.0, 1.0)
+    for epilogue in V.PRODUCT_EPILOGUES:
+        us = V.vit_product_time(epilogue, 700, 328, 192, ws.data_ptr(), ws.numel() * 2, form)
+        assert 1.0 < us < 2000.0, (epilogue, us)
+    with pytest.raises(V.VitError):
+        V.vit_product_time("bias", 700, 328, 192, ws.data_ptr(), 1 << 20, form)

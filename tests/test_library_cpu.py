@@ -41,6 +41,28 @@ def test_mfma_ceiling_rejects_bad_arguments_before_touching_a_device():
     assert out.value == -1.0
 
 
+def test_product_aids_reject_bad_arguments_before_touching_a_device():
+    import ctypes as C
+
+    lib = V.load_library()
+    form, rest, rest_form, us = C.c_int32(-7), C.c_int64(), C.c_int32(), C.c_double(-1.0)
+
+    def plan(epilogue=0, rows=577, columns=1024, depth=1024, units=256, form=C.byref(form)):
+        return lib.vit_product_plan(epilogue, rows, columns, depth, units, form, C.byref(rest), C.byref(rest_form), C.byref(us))
+
+    def time(epilogue=0, rows=577, columns=1024, depth=1024, form=-1, ws=C.c_void_p(4096), size=0, us=C.byref(us)):
+        return lib.vit_product_time(epilogue, rows, columns, depth, form, ws, size, None, us)
+
+    for call in (plan, time):
+        assert call(epilogue=4) == -1 and call(epilogue=-1) == -1 and call(rows=0) == -1 and call(rows=2 ** 31) == -1
+        assert call(columns=12) == -1 and call(columns=0) == -1 and call(depth=32) == -1 and call(depth=0) == -1
+    assert plan(units=0) == -1 and plan(form=None) == -1
+    assert time(ws=None) == -1 and time(ws=C.c_void_p(4100)) == -1 and time(us=None) == -1 and time(form=10) == -1 and time(form=-2) == -1
+    assert time() == -3 and b"needed" in lib.vit_last_error()   # VIT_ECAPACITY: nothing launched
+    assert form.value == -7 and us.value == -1.0
+    assert plan() == 0 and 0 <= form.value <= 9 and us.value > 0
+
+
 def test_preprocess_rejects_bad_arguments_before_touching_a_device():
     import ctypes as C
 

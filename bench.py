@@ -268,7 +268,7 @@ def product_times(torch, V):
     u64 = lambda n: -(-n // 64) * 64
     products = []
     for d, (qkv, att, mlp, patch) in PRODUCT_ENCODERS.items():
-        products += [("bias", qkv, u64(d)), ("residual", d, u64(att)), ("gelu", mlp, u64(d)), ("residual", d, u64(mlp)), ("patch", d, patch)]
+        products += [("bias", qkv, u64(d)), ("residual", d, u64(att)), ("gelu", u64(mlp), u64(d)), ("residual", d, u64(mlp)), ("patch", d, patch)]
     products += [("gelu", 4096, 1024), ("bias", 4096, 4096), ("gelu", 6144, 12800), ("bias", 6144, 6144)]
     ws = torch.empty(5 << 30, dtype=torch.bfloat16, device="cuda").uniform_(-1.0, 1.0)
     print("epilogue,columns,depth,rows,as planned," + ",".join(V.PRODUCT_FORMS), flush=True)

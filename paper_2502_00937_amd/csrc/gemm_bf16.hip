@@ -925,6 +925,12 @@ PipeChoice best_pipe(int kind, long M, long N, int stages) {
     const float us = pipe_time(PIPE_TILES[i], kind, M, N, stages);
     if (us < best.us) best = {i, us};
   }
+  // Operand and output that the memory-side cache cannot hold together slow all tiles down where the persistent kernel stays as
+  // it was: 384 columns of K = 768 with position rows, 86 550 rows 84.5 us on tiles and 83.5 on the persistent kernel, 98 000
+  // rows 110.6 and 89.0; 512 of K = 2048 with residual, 51 232 rows 145 and 132, 57 700 rows 160 and 137.  With 0.06 us a MB the
+  // form chosen is on average 0.5 % slower than the best of the ten from 15 000 rows on, without it 1.0 %.
+  const double bytes = (double)M * (stages * (BK * 2) + N * (kind < 2 ? 2 : 4));
+  if (bytes > 256.0 * 1024 * 1024) best.us += (float)(0.06e-6 * bytes);
   return best;
 }
 

@@ -84,3 +84,24 @@ def check_case(cfg, tiles_per_image, ipr, wseed=0, pseed=1, wscale=1.0, oracle_d
             a, b = int(to[i]) * T, int(to[i + 1]) * T
             assert_parity(got[a:b], want[a:b], cfg["dtype"], f"{label} image {i}")
     return got, want
+
+
+def planned_products(cfg, n_tiles):
+    """{product: (epilogue, its rows, columns and depth, form, rows of a second launch, its form)} of a bf16 encode of that many
+    tiles on a device of 256 units, as the library plans them (a walk from the first row to the last; every layer has both)."""
+    import paper_2502_00937_amd as V
+
+    up64 = lambda n: -(-n // 64) * 64
+    D, dh = cfg["hidden"], cfg["hidden"] // cfg["heads"]
+    stored = 64 if dh <= 64 else 72 if dh == 72 else 80 if dh <= 80 else 96 if dh <= 96 else 128
+    patches, rows = (cfg["image_size"] // cfg["patch_size"]) ** 2, n_tiles * gen.tokens_per_tile(cfg)
+    wide, mlp = cfg["heads"] * stored, up64(cfg["mlp"])
+    products = {"patch": ("patch", n_tiles * patches, D, up64(cfg["channels"] * cfg["patch_size"] ** 2)),
+                "qkv": ("bias", rows, 3 * wide, up64(D)), "out": ("residual", rows, D, up64(wide)),
+                "fc1": ("gelu", rows, mlp, up64(D)), "fc2": ("residual", rows, D, mlp)}
+    d_in, n_out, dims = up64(D * cfg["token_merge"] ** 2), n_tiles * gen.out_tokens_per_tile(cfg), cfg["proj_dims"]
+    for i, d_out in enumerate(dims):
+        last = i + 1 == len(dims)
+        products[f"proj{i}"] = ("bias" if last else "gelu", n_out, d_out if last else up64(d_out), d_in)
+        d_in = up64(d_out)
+    return {name: p + V.vit_product_plan(*p)[:3] for name, p in products.items()}

@@ -4,7 +4,7 @@ import pytest
 
 import gen
 from oracle import vit_oracle as O
-from parity_util import assert_parity, check_case, gpu_encode, say
+from parity_util import assert_parity, check_case, gpu_encode, planned_products, say
 
 pytestmark = pytest.mark.gpu
 
@@ -82,67 +82,63 @@ def test_ragged_many_tiles_bf16():
     check_case(cfg, tpi, [1, 0, 4, 3], label="ragged")
 
 
-def test_wide_batch_mixes_both_gemm_kernels():
+def test_wide_batch_of_several_rounds_of_tiles():
     """160 tiles x 226 = 36 160 token rows (142 row blocks of 256, ragged last one): several rounds of every kind of tile,
     K of 4 and 8 k-stages (the persistent kernel's own sizes are in test_gpu_gemm_tiles.py).  The oracle encodes sampled images
     (first, a multi-tile one, last)."""
     cfg = gen.get_config("test_medium_bf16")
     tpi = [1, 4, 1, 1, 2, 7, 1, 3] * 8           # 64 images, 160 tiles
-    say("case wide batch (160 tiles, both GEMM kernels)")
+    say("case wide batch (160 tiles, several rounds of tiles)")
     got, _ = check_case(cfg, tpi, [len(tpi)], images=[0, 5, 63], label="wide")
     assert got.shape[0] == 160 * 226
 
 
-def test_odd_k_stage_counts_and_narrow_column_bands_on_the_persistent_gemm():
-    """500 tiles x 197 tokens = 98 500 rows (385 row blocks), so even the products with a single tile column
-    reach the persistent kernel's threshold of 384 tiles.  K = 64, 192 and 320 are 1, 3 and 5 k-stages: the two
-    LDS stages change roles from one tile to the next.  N = 576, 192 and 320 are three, one and two tile
-    columns: a band with an idle column and the 32 x 1 and 16 x 2 tile groups."""
-    cfg = gen.get_config("test_oddk_bf16")
-    tpi = [1] * 500
-    say("case odd k-stage counts (500 tiles, persistent GEMM)")
-    got, _ = check_case(cfg, tpi, [len(tpi)], images=[0, 171, 499], label="oddk")
-    assert got.shape[0] == 500 * 197
+def _one_block_cfg(hidden, mlp):
+    return {"image_size": 60, "patch_size": 4, "channels": 3, "hidden": hidden, "heads": hidden // 64, "mlp": mlp, "layers_local": 2,
+            "layers_global": 0, "has_cls": 1, "final_ln": 1, "ln_eps": 1e-6, "proj_layers": 0, "proj_dims": (), "dtype": "bf16",
+            "token_merge": 1}
 
 
-def test_short_last_rounds_of_one_and_two_column_products():
-    """The same network at 390 tiles (76 830 rows, 301 row blocks).  The products one tile column wide are walked in
-    rounds of 256 row blocks and those two columns wide in rounds of 128; both leave 45 row blocks for a last round
-    that would idle most of the device, so those rows go to the ring kernel in a launch of their own (at either end
-    of the matrix: the walk alternates its direction from one product to the next).  The oracle encodes the first
-    image, one inside and the last; the first and last two images encoded alone (ring kernel only) must give the
-    bits they have in the batch."""
+@pytest.mark.parametrize("hidden,tiles,rest", [(512, 118, 0), (512, 155, 1), (512, 182, 1), (256, 185, 0), (256, 309, 1)])
+def test_one_and_two_column_products_on_the_persistent_gemm(hidden, tiles, rest):
+    """fc2 of 65 k-stages (neither a multiple of the two units of W nor of the three of A in LDS, so that the units change roles from
+    one tile to the next) and two or one tile columns: groups of 16 x 2 and 32 x 1 tiles.  The rounds take 128 and 256 row blocks; at
+    118 images (104 row blocks) and 185 (163) all rows are walked, at 155 and 182 (137 and 161) and 309 (273) the last ones are a
+    launch of their own, at either end of the matrix: the walk alternates its direction, and the two layers have one each.
+    The oracle encodes the first image, one inside and the last; the first and last two images encoded alone (on tiles) must give
+    the bits they have in the batch."""
     import torch
 
     import paper_2502_00937_amd as V
 
-    cfg = gen.get_config("test_oddk_bf16")
-    tpi = [1] * 390
-    say("case short last rounds (390 tiles, persistent + ring launches per product)")
-    got, _ = check_case(cfg, tpi, [len(tpi)], images=[0, 200, 389], label="short-round")
-    assert got.shape[0] == 390 * 197
+    cfg = _one_block_cfg(hidden, 4104)
+    form, rest_rows = planned_products(cfg, tiles)["fc2"][4:6]
+    assert form == V.PRODUCT_FORMS[9] and (rest_rows > 0) == bool(rest), (form, rest_rows)
+    say(f"case fc2 of {hidden} columns on the persistent kernel, {tiles} tiles, last rows on their own: {bool(rest)}")
+    got, _ = check_case(cfg, [1] * tiles, [tiles], images=[0, tiles // 2, tiles - 1], label=f"narrow {hidden}")
+    assert got.shape[0] == tiles * 226
     enc = V.VitEncoder(cfg, gen.make_weights(cfg, seed=0), device=0)
     try:
-        px = torch.from_numpy(gen.make_pixels(cfg, 390, seed=1)).cuda()
-        full, _ = enc.encode(px, [390], np.arange(391, dtype=np.int32))
-        for lo in (0, 388):
+        px = torch.from_numpy(gen.make_pixels(cfg, tiles, seed=1)).cuda()
+        full, _ = enc.encode(px, [tiles], np.arange(tiles + 1, dtype=np.int32))
+        for lo in (0, tiles - 2):
             part, _ = enc.encode(px[lo:lo + 2], [2], np.arange(3, dtype=np.int32))
             torch.cuda.synchronize()
-            same = torch.equal(part.view(torch.int16), full[lo * 197:(lo + 2) * 197].view(torch.int16))
+            same = torch.equal(part.view(torch.int16), full[lo * 226:(lo + 2) * 226].view(torch.int16))
             say(f"    images {lo}, {lo + 1} alone against the batch: bit-identical = {same}")
             assert same
     finally:
         enc.close()
 
 
-def test_odd_k_stage_counts_on_the_ring_gemm():
-    """The same network at 60 tiles (11 820 rows, 47 row blocks): every product takes the ring kernel, with
-    1, 3 and 5 k-stages (fewer than the ring is deep) and rings of four and of two stages."""
+@pytest.mark.parametrize("tiles,images", [(500, [0, 171, 499]), (390, [0, 200, 389]), (60, [0, 31, 59])])
+def test_few_k_stages_on_many_tiles(tiles, images):
+    """K = 64, 192 and 320 are 1, 3 and 5 k-stages, fewer than and as many as the rings hold, on 47 to 385 row blocks; N = 576, 192
+    and 320."""
     cfg = gen.get_config("test_oddk_bf16")
-    tpi = [1] * 60
-    say("case odd k-stage counts (60 tiles, ring GEMM)")
-    got, _ = check_case(cfg, tpi, [len(tpi)], images=[0, 31, 59], label="oddk-ring")
-    assert got.shape[0] == 60 * 197
+    say(f"case few k-stages ({tiles} tiles)")
+    got, _ = check_case(cfg, [1] * tiles, [tiles], images=images, label="oddk")
+    assert got.shape[0] == tiles * 197
 
 
 def test_packing_invariance_on_gpu():

@@ -498,20 +498,13 @@ def test_one_patch_tiles(has_cls, dtype):
     check_case(cfg, [1, 3, 1, 2], [2, 0, 2], wseed=11, pseed=12, label=f"one-patch cls{has_cls}")
 
 
-@pytest.mark.parametrize("amp", [64.0, 112.0, -112.0])
-def test_attention_logits_that_outgrow_the_reference_maximum(amp):
-    """Logits that span far more than 2^64 (as exp2 arguments) over the keys of a segment: every query is
-    -amp e_0, key t carries 8 cos(pi t / 256) in channel 0 (a position table on a circle, which LayerNorm maps to
-    that), so the logit of key t is -amp cos(pi t / 256): -amp ... +amp over 257 keys = five key tiles.
-    amp = 64 (+-92 in log2 units) is the most the attention kernel's pass without a reference maximum takes;
-    amp = +-112 (+-162 in log2 units, rising resp. falling along the keys) overflows resp. underflows there, so
-    the workgroups must notice and run the general pass, whose reference has to move several times after the
-    first tile with the accumulated output rescaled each time; a lost rescale or a missed fall-back would show as
-    garbage, inf or NaN."""
-    cfg = {"image_size": 64, "patch_size": 4, "channels": 3, "hidden": 64, "heads": 1, "mlp": 64, "layers_local": 1,
+def _logits_on_a_circle(amp, D):
+    """An encoder of one head of D columns and 257 tokens a tile whose logits are -amp cos(pi t / 256) for key t: every query is
+    -amp e_0, key t carries sqrt(D) cos(pi t / 256) in channel 0 (a position table on a circle, which LayerNorm maps to that)."""
+    cfg = {"image_size": 64, "patch_size": 4, "channels": 3, "hidden": D, "heads": 1, "mlp": 64, "layers_local": 1,
            "layers_global": 0, "has_cls": 1, "final_ln": 0, "ln_eps": 1e-6, "proj_layers": 0, "proj_dims": (),
            "dtype": "bf16", "token_merge": 1}
-    T, D = gen.tokens_per_tile(cfg), 64
+    T = gen.tokens_per_tile(cfg)
     assert T == 257
     w = gen.make_weights(cfg, seed=3).copy()
     off = {}
@@ -535,14 +528,46 @@ def test_attention_logits_that_outgrow_the_reference_maximum(amp):
     bqkv[:D] = 0.0
     bqkv[0] = -amp                        # q = -amp e_0 for every token
     wqkv[D, :] = 0.0
-    wqkv[D, 0] = 1.0                      # k[0] = normalised channel 0 = 8 cos(theta)
+    wqkv[D, 0] = 1.0                      # k[0] = normalised channel 0 = sqrt(D) cos(theta)
     bqkv[D] = 0.0
     wqkv[2 * D:] *= 10.0                  # values and output projection large enough to matter beside x
     view("l0.wo")[:] *= 10.0
     w = gen.round_to_bf16(w)
+    return cfg, w
+
+
+@pytest.mark.parametrize("amp", [64.0, 112.0, -112.0])
+def test_attention_logits_that_outgrow_the_reference_maximum(amp):
+    """Logits that span far more than 2^64 (as exp2 arguments) over the keys of a segment: -amp ... +amp over 257 keys = five key
+    tiles.
+    amp = 64 (+-92 in log2 units) is the most the attention kernel's pass without a reference maximum takes;
+    amp = +-112 (+-162 in log2 units, rising resp. falling along the keys) overflows resp. underflows there, so
+    the workgroups must notice and run the general pass, whose reference has to move several times after the
+    first tile with the accumulated output rescaled each time; a lost rescale or a missed fall-back would show as
+    garbage, inf or NaN."""
+    cfg, w = _logits_on_a_circle(amp, 64)
     px = gen.make_pixels(cfg, 3, seed=5)
     to = np.array([0, 1, 3], dtype=np.int32)
     say(f"case logits outgrowing the softmax reference (257 keys, logits {-amp:+.0f} ... {amp:+.0f})")
     got, _ = gpu_encode(cfg, w, px, [2], to)
     want, _ = O.vit_oracle_encode(cfg, w, px, [2], to)
     assert_parity(got, want, "bf16", f"logits amp {amp:+.0f}")
+
+
+@pytest.mark.parametrize("D,tiles", [(64, 1030), (72, 190), (80, 190), (96, 190), (128, 5)])
+@pytest.mark.parametrize("amp", [96.0, -96.0])
+def test_the_general_pass_behind_either_form_of_the_attention_kernel(D, tiles, amp):
+    """The same with three query blocks a tile and so many tiles that the launch is too large for the pipelined form (3072 workgroups
+    at head dim 64, 512 at 72 to 96, none at 128): the general pass behind the other form, which has registers of its own.  An
+    image alone takes the pipelined one, and has to come out the same bit for bit.  (The logits' own rounding, 2^-9 of the
+    amplitude in bf16, is most of the error: hence 96, not 112, which the normal pass takes no better.)"""
+    cfg, w = _logits_on_a_circle(amp, D)
+    say(f"case logits outgrowing the softmax reference, head dim {D}, {tiles} tiles, amplitude {amp:+.0f}")
+    px = gen.make_pixels(cfg, tiles, seed=5)
+    got, _ = gpu_encode(cfg, w, px, [tiles], np.arange(tiles + 1, dtype=np.int32))
+    one = np.array([0, 1], dtype=np.int32)
+    for i in (0, tiles // 2, tiles - 1):
+        alone, _ = gpu_encode(cfg, w, px[i:i + 1], [1], one)
+        assert np.array_equal(alone, got[257 * i:257 * (i + 1)]), i
+    want, _ = O.vit_oracle_encode(cfg, w, px[-1:], [1], one)
+    assert_parity(got[-257:], want, "bf16", f"head dim {D}, amplitude {amp:+.0f}")

@@ -17,14 +17,15 @@ namespace {
 // transposed, so a lane holds four consecutive columns of one row per register quad.  A row's sums are formed in the
 // same order whatever F is, so a token does not depend on the tile size its launch took.
 // Operand rows are padded by the host so tile loads never leave the buffers.
-// How many k-blocks are in flight decides how many workgroups a unit holds: 32 x 32 tiles three with three blocks (two with
-// four, and fc1 of four 197-token images is 600 tiles on 256 units), 64 x 64 tiles four with one (one with two: nothing then
-// covers a wave's loads and its sums).  Encodes of the 12-block encoder of width 192 by 4, 12 and 64 images: 599, 975 and
-// 3295 us with four and two blocks, 565, 871 and 2984 with three and one; with two (four workgroups) on 32 x 32, 585 and
-// 901.  The error of the encoder against 64 bits is 3.5e-7 (four short chains; one long one gave 6.5e-7).
-template <int EPI, int F>
-__global__ __launch_bounds__(256, F == 1 ? 3 : 2) void gemm_f32_kernel(const GemmArgs a) {
-  constexpr int DEPTH = F == 1 ? 3 : 1;  // k-blocks in flight per wave
+// DEPTH k-blocks are in flight per wave, and a unit is to hold WGS workgroups at the least; the registers set one against the
+// other.  Short products gain from workgroups: 32 x 32 tiles three with three blocks (two with four, and fc1 of four 197-token
+// images of width 192 is 600 tiles on 256 units), 64 x 64 tiles four with one (two blocks leave room for one workgroup, and
+// nothing then covers a wave's loads and its sums).  Encodes of the 12-block encoder of width 192 by 4, 12 and 64 images: 599, 975
+// and 3295 us with four and two blocks, 565, 871 and 2984 with three and one.  From K = 768 on the loads in flight count for more
+// on 64 x 64 tiles: encodes of three blocks of width 768, 20, 40 and 64 images 2560, 4776 and 7629 us with one block, 2387, 4729
+// and 7481 with two.  The error of the encoder against 64 bits is 3.5e-7 (four short chains; one long one gave 6.5e-7).
+template <int EPI, int F, int DEPTH, int WGS>
+__global__ __launch_bounds__(256, WGS) void gemm_f32_kernel(const GemmArgs a) {
   constexpr int LD = 36;                 // LDS row: 32 columns and a pad that spreads the rows over the banks
   __shared__ __attribute__((aligned(16))) float red[4][32 * F][LD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -218,18 +219,26 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const AttnArgs a) {
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.K <= 0 || a.K % 64 != 0 || a.lda % 4 != 0 || a.ldw % 4 != 0 || a.ldo % 4 != 0 || a.N % 4 != 0) return hipErrorInvalidValue;
-  // 64 x 64 tiles read half the operand bytes of 32 x 32 ones, which pays once there are enough of them to fill the units
-  // evenly.  Whole encodes, in us, with the line at 512, 1024, 1536, 3072 tiles and on 32 x 32 everywhere: 12 blocks of
-  // width 192, 16 images 1073, 1042, 1043, -, -; 32: 1682, 1646, 1585, -, -; 64: 2994, 2915, 2910, 2835, 2836; 300: -, -, 11490,
-  // 11762, 11897; 3 blocks of width 768, 24 images: -, -, 3002, 3024, 3084; 64: -, -, 7609, 7740, 7994.  The products that
-  // these differ in have 1773 and 2364 tiles (width 192, 64 images), 2772 (300 images), 2664 and 2364 (width 768).
-  const long tiles64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64);
-  const int t = tiles64 >= 2560 ? 64 : 32;
+  // 64 x 64 tiles read half the operand bytes of 32 x 32 ones, which pays once the units' shares of them come out even.  Up to
+  // K = 704 that is said by a line on their number.  Whole encodes, in us, with the line at 1024, 1536, 2048, 2560, 3072 and 4096
+  // tiles: 12 blocks of width 192, 40 images 2018, 1913, 1915, 1916, 1910 and 1913; 64: 2920, 2922, 2873, 2853, 2845, 2849; 100: 4270,
+  // 4271, 4279, 4282, 4234, 4230; 240: 9358, 9356, 9362, 9563, 9533, 9544; 300: 11510, 11533, 11545, 11522, 11780, 11805.
+  // From K = 768 on, with two k-blocks in flight, a larger tile takes 0.85 of what its four small ones do, so it is taken where
+  // the largest share of a unit grows by no more than 1.18: three blocks of width 768, 20 images (shares of 3 against 3) 2387 us and
+  // 2594 on small tiles, 28 (5 against 4.25) 3583 and 3595, 4 (fc1, 3 against 2.5) 710 and 692; two blocks of width 1024, 20 images
+  // (4 against 4) 2699 and 2875.  Fewer than two for each unit never gain.
+  const long tiles64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64), tiles32 = (long)((a.M + 31) / 32) * ((a.N + 31) / 32);
+  const long share64 = (tiles64 + 255) / 256, share32 = (tiles32 + 255) / 256;
+  const bool deep = a.K >= 768;
+  const bool large = (deep ? tiles64 >= 512 && share64 * 400 <= share32 * 118 : tiles64 >= 2560) ||
+                     (a.M + 31) / 32 > 65535;  // (more row blocks than a grid's second dimension holds)
+  const int t = large ? 64 : 32;
   const dim3 grid((a.N + t - 1) / t, (a.M + t - 1) / t), block(256);
-#define VIT_LAUNCH(EPI)                                                                        \
-  do {                                                                                         \
-    if (t == 64) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2>), grid, block, 0, s, a);          \
-    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1>), grid, block, 0, s, a);                  \
+#define VIT_LAUNCH(EPI)                                                                                 \
+  do {                                                                                                  \
+    if (large && deep) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 2, 1>), grid, block, 0, s, a);       \
+    else if (large) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 1, 2>), grid, block, 0, s, a);          \
+    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, 3, 3>), grid, block, 0, s, a);                     \
   } while (0)
   switch (a.epilogue) {
     case EPI_BIAS: VIT_LAUNCH(EPI_BIAS); break;

@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256, DEEP ? (DHP == 64 ? 3 : 2) : DHP == 64 ? 4 : D
   // in its even rows and for those of the other in its odd rows tells them apart.  Two of them take 32 clocks, the eight
   // v_dot2c_f32_bf16 with a pair of ones that they replaced 128: those do not run beside MFMAs (a probe: 16 exp2, 8 packed
   // conversions and 8 MFMAs of 32 clocks take 266 clocks with four waves on a SIMD, 395 with the eight dot products).
-  // Attention of 260 x 577 tokens, 16 heads of 64: 481 us with the dot products, 470 now.
+  // Attention of 260 x 577 tokens, 16 heads of 64, inside the encode: 458 us with the dot products, 452 now.
   f32x4 lsum = {0.f, 0.f, 0.f, 0.f};
   bf16x8 ones;
 #pragma unroll
@@ -539,8 +539,8 @@ static hipError_t launch_attention_as(const AttnArgs& a, hipStream_t s) {
 template <int DHP>
 static hipError_t launch_attention_dh(const AttnArgs& a, hipStream_t s) {
   // DEEP needs a third more registers, so a unit holds a workgroup less: three for four at head dim 64, two for three at 72 to
-  // 96.  It is the better one where workgroups are too few to hide a wave's chain behind other waves, in us against the
-  // other one: 577 tokens, 16 heads of 64: 1 image 9.6 and 11.8, 8 images 20.9 and 22.1, 35 (2800 workgroups) 65.7 and 66.7, 260
+  // 96.  It is the better one where workgroups are too few to hide a wave's chain behind other waves, in us a launch by itself against
+  // the other one: 577 tokens, 16 heads of 64: 1 image 9.6 and 11.8, 8 images 20.9 and 22.1, 35 (2800 workgroups) 65.7 and 66.7, 260
   // 492 and 482; at the other head dims as long as it takes no more rounds of the units: 16 heads of 80, 6404 tokens (816)
   // 266 and 280; 1601 tokens, 2 tiles (416) 40.1 and 41.9, 3 (624) 60.6 and 56.9, 4 (832) 74.9 and 77.0, 5 (1040) 92.3
   // and 90.3.  At 128 both hold two and DEEP, a few registers short, is no faster.

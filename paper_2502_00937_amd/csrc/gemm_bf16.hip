@@ -878,8 +878,10 @@ hipError_t launch_pipe_as(const GemmArgs& a, hipStream_t s) {
 // round has a fixed time of its own and an epilogue by its kind: bias, bias + GELU, residual or patch rows.  Fitted to
 // the times of 20 encoder products (out-proj, QKV, fc1 and fc2 at widths of 768, 1024, 1152, 1280 and 3200, so 768 to
 // 12 800 columns and stages of 12 to 200) at 18 sizes each of 197 to 160 000 rows, weighted towards the tiles that are near
-// the best one: the tile chosen is on average 1 % slower than the best of the ten.  (Two launches of the choice that this one
-// replaced, by numbers of tiles alone and with 256 x 256, 128 x 128, 64 x 128 and 64 x 64 to choose from, took 13 % longer.)
+// the best one.  bench.py --product-times times every form on the products of nine encoders of 384 to 3200 columns, four of them
+// not among those: the form chosen is on average 0.9 % slower than the best of the ten there, 0.9 and 0.8 % at 26 other numbers of rows
+// and at five other widths.  (Two launches of the choice that this one replaced, by numbers of tiles alone and with 256 x 256, 128 x
+// 128, 64 x 128 and 64 x 64 to choose from, took 13 % longer.)
 // Patch rows have epilogues of their own, fitted to the patch embeddings of four encoders (1024 to 3200 columns) at 1 to 260 tiles
 // of pixels: on the one-tile kernel they take 1.5 to 2.5 times a residual's, on the persistent one less than that.  Priced as
 // residual rows, products of many rounds stayed on the one-tile kernel (149760 x 1024 x 640: 477 us, 294 on the persistent

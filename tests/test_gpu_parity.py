@@ -246,7 +246,7 @@ def test_repeated_launches_are_deterministic():
 
 def test_one_handle_serves_batches_of_changing_size_without_waiting():
     """Launches of very different sizes queued back to back on one handle and one stream (the workspace is
-    reused, the pinned table slots cycle, both GEMM kernels and both ring depths take turns): every result
+    reused, the pinned table slots cycle, tiles of several heights and ring depths take turns): every result
     equals, bit for bit, what a fresh handle produces for that batch alone."""
     import torch
 
